@@ -66,3 +66,43 @@ def test_invalid_arguments_are_rejected(abm):
         books.params = abm.lob_params(**{"cap": 8, **kw})
         with pytest.raises(abm.AbmError):
             books.init()
+
+
+@pytest.mark.parametrize("n_books,kw", [
+    (4, dict(cap=63, traders=64, expiry=4, seed=21)),       # runs and turns of 64, one short
+    (4, dict(cap=257, traders=129, spread=3, seed=22)),     # one past a pass of four runs
+    (3, dict(cap=1024, traders=300, spread=400, expiry=60, seed=23)),   # over 64 new orders a side
+    (3, dict(cap=1024, traders=700, T_order=2 ** 32 - 1, spread=2, seed=24)),  # over 256 a side
+    (3, dict(cap=1000, traders=1000, T_order=2 ** 32 - 1, spread=1, max_qty=1, expiry=2,
+             seed=25)),                                     # matches past the first 64 of a side
+])
+def test_list_and_match_sizes(abm, orc, n_books, kw):
+    """Run, turn and match sizes at which the step takes another branch."""
+    books, st = _run(abm, n_books, (13, 2), **kw)
+    _check(abm, orc, books, st, 15)
+
+
+@pytest.mark.parametrize("shift", [0, 3, -40])
+def test_book_supplied_by_the_caller(abm, orc, shift):
+    """A run continued from a copy of its book in new arrays, with the times of
+    its orders moved: the same expiry and priorities as the oracle's."""
+    kw = dict(cap=200, traders=60, expiry=15, seed=31)
+    a, _ = _run(abm, 1, (12,), **kw)
+    b = abm.OrderBooks(abm.lob_params(**kw), 1)
+    b.init()
+    for f in abm.LOB_FIELDS:
+        b.orders[f].copy_(a.orders[f])
+    b.orders["time"][b.orders["alive"] != 0] += shift
+    b.last_price.copy_(a.last_price)
+    b.step = a.step
+    OP = orc.lob_params(**kw)
+    S = orc.lob_init(OP)
+    orc.lob_run(OP, S, 12)
+    S.orders["time"][S.orders["alive"] != 0] += shift
+    st = torch.zeros((9, 1, 8), dtype=torch.int64, device="cuda")
+    b.run(9, st)
+    exp = np.array([[d[k] for k in orc.LOB_STATS] for d in orc.lob_run(OP, S, 9)])
+    torch.cuda.synchronize()
+    assert np.array_equal(st[:, 0].cpu().numpy(), exp)
+    for f in abm.LOB_FIELDS:
+        assert np.array_equal(b.orders[f][0].cpu().numpy(), S.orders[f]), f
