@@ -75,3 +75,18 @@ def test_invalid_arguments_are_rejected(abm):
     roads.init()
     with pytest.raises(abm.AbmError):
         roads.run(-1)
+
+
+@pytest.mark.parametrize("length", [3, 23, 24, 300, 301, 599, 600])
+def test_road_lengths_at_the_edges_of_the_thread_layout(abm, orc, length):
+    """No cells between the columns of the first wave but one; a full wave of
+    cells and one more; the last length of one and of two cells per thread."""
+    roads, stats = _run(abm, length, 3, (7, 33), T_spawn=3 * 2 ** 30, seed=length)
+    _check_roads(abm, orc, roads, stats, 40)
+
+
+def test_a_crowded_road_spawns_into_the_last_free_slots(abm, orc):
+    """Every cell but a few taken: the lowest free slots run out and come back."""
+    roads, stats = _run(abm, 12, 20, (200,), T_green=2 ** 28, T_spawn=2 ** 32 - 1, seed=77)
+    assert int(stats[..., 0].max()) == 36
+    _check_roads(abm, orc, roads, stats, 200)
