@@ -34,11 +34,16 @@
 // pass C clears it whole every step.  The global table of such a model is not touched.  The launch
 // gives each workgroup the LDS its occupancy leaves free, so no workgroup
 // is displaced for it.
+// Models of up to 256 x 256 cells whose live agents fit are taken before that
+// by workgroups that hold the whole model in LDS (k_batched_chip, see
+// onchip.hpp); what does not fit, or outgrows it, is left to the passes above.
 // Grass is stored as the step at which a cell is grown again (0 = grown from
 // the start), so the per-cell regrowth pass of the one-model path disappears:
 // a cell is grown at step t iff ready <= t; eating at step t sets ready = t + R.
 // The countdown of the model definition is max(0, ready - steps_done).
 #include <hip/hip_runtime.h>
+
+#include <atomic>
 
 #include "abm.h"
 #include "common.hpp"
@@ -53,6 +58,11 @@ constexpr uint32_t kTagBits = 4;     // claim-key tag: periods of 14 steps
 constexpr uint32_t kDxPacked = 0x9224u;  // see predation.hip: dir -> dx + 1, 2 bits each
 constexpr uint32_t kDyPacked = 0xA940u;
 
+// Words of the workspace header: the queues of the team models, of the models
+// of one workgroup and of those run on the chip, and the lengths of the lists
+// k_classify makes of the latter two.
+enum QueueWord : int { kQueueTeam = 0, kQueueSolo, kQueueChip, kChipModels, kSoloModels, kQueueWords };
+
 struct BatchArgs {
     abm_model_desc* models;
     const int32_t* order;      // queue order of model indices
@@ -62,7 +72,9 @@ struct BatchArgs {
     uint64_t* claims;          // packed, 3 words per cell
     int32_t *sx, *sy, *se, *sa;
     int32_t *wx, *wy, *we, *wa;
-    uint32_t* queue;           // two model queue counters (reset before the launch)
+    uint32_t* queue;           // model queue counters (see QueueWord; reset before the launch)
+    int32_t listed;            // the models of one workgroup come from the lists of k_classify
+    int32_t chip_bytes;        // LDS of a workgroup of k_batched_chip
     int32_t* scratch;          // per-workgroup breeder list
     int64_t scratch_stride;    // ints per workgroup
     uint64_t* err;             // workspace error word
@@ -232,6 +244,14 @@ __device__ __forceinline__ bool on_grid(const ModelView& v, int32_t x, int32_t y
     return x >= 0 && x < v.W && y >= 0 && y < v.H;
 }
 
+}  // namespace
+}  // namespace abm
+
+#include "onchip.hpp"
+
+namespace abm {
+namespace {
+
 // A team of K workgroups advancing one model together (K = 1: one workgroup
 // alone).  Member r owns the r-th contiguous K-th of each species' slots and
 // keeps its own breeder list; members exchange per-range counts.  Members of a
@@ -333,9 +353,14 @@ __device__ __forceinline__ void prey_match(const ModelView& v, uint64_t skey, co
 // is blockDim * ITEMS slots; item k of lane l of wave w is slot
 // c0 + (w * ITEMS + k) * 64 + l, so each load instruction of a wave covers 64
 // consecutive slots and the ITEMS loads of a lane are issued together.
+// A step's statistics of a model of one workgroup, added up in LDS.
+struct StepCounts {
+    int32_t live[2], grass, eaten, births[2], starved[2];
+};
+
 template <int ITEMS, bool LOCAL>
 __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool last, Team& tm,
-                           uint32_t* lds, uint32_t* live_out) {
+                           uint32_t* lds, uint32_t* live_out, StepCounts* counts = nullptr) {
     uint64_t* const claims = LOCAL ? local_claims() : v.claims;
     // LOCAL: the atomics of pass A are complete at the barrier that ends it
     auto rd = [](const uint64_t* p) { return LOCAL ? *p : ld_claim(p); };
@@ -413,6 +438,7 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
                 if (al[k] == 0) continue;
                 const int32_t i = c0 + lbase + k * 64;
                 ++live;
+                if (counts) atomicAdd(&counts->live[s], 1);
                 const uint32_t d = draw(skey, uint32_t(i), move_p[s]) >> 29;
                 const int32_t x =
                     wrap_step(v.x[s][i], int32_t((kDxPacked >> (2 * d)) & 3u) - 1, v.W);
@@ -488,6 +514,7 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
                             e += v.gain[0];
                             v.e[0][i] = e;
                             v.ready[c] = int32_t(t) + v.R;
+                            if (counts) atomicAdd(&counts->grass, 1);
                         }
                         if (v.multi) {
                             eaten = al[k] == 2;   // taken by a wolf of its cell
@@ -497,6 +524,7 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
                             eaten = true;
                         }
                         nfree += eaten ? 1u : 0u;
+                        if (counts && eaten) atomicAdd(&counts->eaten, 1);
                     } else if (!v.multi && claimed(rd(cw + 1)) &&
                                rd(cw + 2) == tagged_key(tag_hi, sb, skey, i, kWolfEatKey)) {
                         e += v.gain[1];
@@ -621,10 +649,13 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
                     v.e[s][p] = ep - ec;
                     v.al[s][i] = 1;
                     top[s] = i + 1;
+                    if (counts) atomicAdd(&counts->births[s], 1);
                 } else if (i < end) {
                     // a breeder's energy stays positive, so no slot read by a child dies
                     // here, whichever of its two values another member's child leaves
-                    if (al[k] == 2 || (al[k] != 0 && v.e[s][i] < 0))
+                    const bool starves = al[k] != 0 && al[k] != 2 && v.e[s][i] < 0;
+                    if (counts && starves) atomicAdd(&counts->starved[s], 1);
+                    if (al[k] == 2 || starves)
                         v.al[s][i] = 0;
                     else if (al[k] != 0)
                         top[s] = i + 1;
@@ -644,6 +675,20 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
     return team_sync(tm);
 }
 
+__device__ __forceinline__ void set_tags(ModelView& v, int64_t max_cap) {
+    // claim keys: slots below 2^sb (caps are at most 2^30), a tag of up to
+    // kTagBits bits above the 32-bit draw; tags tag_top down to 1 (0 alone when
+    // one tag bit is left, re-arming every step); all-ones has a tag no step uses
+    uint32_t sb = 1;
+    while (sb < 31 && (int64_t(1) << sb) < max_cap) ++sb;
+    const uint32_t tag_bits = 32 - sb < kTagBits ? 32 - sb : kTagBits;
+    const uint64_t t_max = (uint64_t(1) << tag_bits) - 1;
+    v.sb = sb;
+    v.tag_top = t_max > 1 ? t_max - 1 : 0;
+    v.period = t_max > 1 ? uint32_t(t_max - 1) : 1u;
+    v.tag_mask = ~uint64_t(0) << (32 + sb);
+}
+
 __device__ ModelView view_of(const BatchArgs& a, const abm_model_desc* d) {
     ModelView v;
     v.W = d->W;
@@ -655,18 +700,7 @@ __device__ ModelView view_of(const BatchArgs& a, const abm_model_desc* d) {
     v.T[1] = d->T_w;
     v.seed = d->seed;
     v.multi = d->multi_prey != 0;
-    // claim keys: slots below 2^sb (caps are at most 2^30), a tag of up to
-    // kTagBits bits above the 32-bit draw; tags tag_top down to 1 (0 alone when
-    // one tag bit is left, re-arming every step); all-ones has a tag no step uses
-    const int64_t max_cap = d->cap_s > d->cap_w ? d->cap_s : d->cap_w;
-    uint32_t sb = 1;
-    while (sb < 31 && (int64_t(1) << sb) < max_cap) ++sb;
-    const uint32_t tag_bits = 32 - sb < kTagBits ? 32 - sb : kTagBits;
-    const uint64_t t_max = (uint64_t(1) << tag_bits) - 1;
-    v.sb = sb;
-    v.tag_top = t_max > 1 ? t_max - 1 : 0;
-    v.period = t_max > 1 ? uint32_t(t_max - 1) : 1u;
-    v.tag_mask = ~uint64_t(0) << (32 + sb);
+    set_tags(v, d->cap_s > d->cap_w ? d->cap_s : d->cap_w);
     v.link[0] = a.link_s ? a.link_s + d->sheep_off : nullptr;
     v.link[1] = a.link_w ? a.link_w + d->wolf_off : nullptr;
     v.cap[0] = int32_t(d->cap_s);
@@ -759,12 +793,13 @@ __device__ bool balance_team(const ModelView& v, Team& tm, uint32_t* lds) {
     return true;
 }
 
-// Runs model m's pending steps (at most max_steps) with team tm; member 0
+// Runs model m's pending steps (at most `max_steps`) with team tm; member 0
 // updates the descriptor.  A model of a single workgroup (no team) keeps its
 // claim table in LDS when its 3 W H words fit in a.lds_words.  False if a
 // team barrier failed.
 template <int ITEMS>
-__device__ bool run_model(const BatchArgs& a, int32_t m, Team& tm, uint32_t* lds) {
+__device__ bool run_model(const BatchArgs& a, int32_t m, int32_t max_steps, Team& tm,
+                          uint32_t* lds) {
     abm_model_desc* d = a.models + m;
     if (d->cap_s + d->cap_w > a.scratch_stride || (d->multi_prey && !(a.link_s && a.link_w))) {
         // the descriptor does not fit the breeder list (max_cap too small), or
@@ -776,7 +811,7 @@ __device__ bool run_model(const BatchArgs& a, int32_t m, Team& tm, uint32_t* lds
     const ModelView v = view_of(a, d);
     const int32_t t0 = d->step;
     int32_t t1 = d->steps_target;
-    if (t1 - t0 > a.max_steps) t1 = t0 + a.max_steps;
+    if (t1 - t0 > max_steps) t1 = t0 + max_steps;
     if (tm.K > 1 && t1 > t0 && !balance_team<ITEMS>(v, tm, lds)) return false;
     uint64_t updates = 0;
     const bool local = tm.K == 1 && 3 * int64_t(v.W) * v.H <= a.lds_words;
@@ -810,7 +845,7 @@ template <int ITEMS>
 __global__ __launch_bounds__(1024) void k_batched_run(BatchArgs a) {
     __shared__ uint32_t lds[16];
     __shared__ int32_t s_pre[2 * (kMaxTeam + 1) + 3];
-    __shared__ int32_t s_ok, s_model;
+    __shared__ int32_t s_ok, s_model, s_steps;
     __shared__ int32_t s_bound[2 * (kMaxTeam + 1)];
     __shared__ int32_t s_mark[2];
     const uint32_t b = blockIdx.x;
@@ -834,7 +869,7 @@ __global__ __launch_bounds__(1024) void k_batched_run(BatchArgs a) {
         int32_t* mailbox = a.team_mail + team;
         for (;;) {
             if (threadIdx.x == 0 && tm.r == 0) {
-                const uint32_t q = atomicAdd(a.queue + 0, 1u);
+                const uint32_t q = atomicAdd(a.queue + kQueueTeam, 1u);
                 __hip_atomic_store(mailbox, q < uint32_t(a.n_team) ? a.order[q] : -1,
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -848,7 +883,7 @@ __global__ __launch_bounds__(1024) void k_batched_run(BatchArgs a) {
             // loop below writes it straight away)
             __syncthreads();
             if (m < 0) break;
-            if (!run_model<ITEMS>(a, m, tm, lds)) return;
+            if (!run_model<ITEMS>(a, m, a.max_steps, tm, lds)) return;
         }
     }
     tm.K = 1;
@@ -857,14 +892,192 @@ __global__ __launch_bounds__(1024) void k_batched_run(BatchArgs a) {
     tm.ctr = nullptr;
     for (;;) {
         if (threadIdx.x == 0) {
-            const uint32_t q = uint32_t(a.n_team) + atomicAdd(a.queue + 1, 1u);
-            s_model = q < uint32_t(a.n_models) ? a.order[q] : -1;
+            if (a.listed) {
+                const uint32_t n = a.queue[kSoloModels];
+                const uint32_t q = n > 0 ? atomicAdd(a.queue + kQueueSolo, 1u) : 0u;
+                const int64_t entry = q < n ? a.models[q].live_w : -1;
+                s_model = int32_t(entry);
+                s_steps = int32_t(entry >> 32);
+            } else {
+                const uint32_t q = uint32_t(a.n_team) + atomicAdd(a.queue + kQueueSolo, 1u);
+                s_model = q < uint32_t(a.n_models) ? a.order[q] : -1;
+                s_steps = a.max_steps;
+            }
+        }
+        __syncthreads();
+        const int32_t m = s_model, steps = s_steps;
+        __syncthreads();
+        if (m < 0) break;
+        run_model<ITEMS>(a, m, steps, tm, lds);
+        __syncthreads();   // (thread 0 rejoins its wave: see k_batched_chip)
+    }
+}
+
+// The models of one workgroup with steps to do, in launch order, as two lists:
+// those that may run on the chip (entry k in models[k].live_s) and the others
+// (models[k].live_w, with the steps it may run above bit 32).  The descriptors'
+// live counts are written when the run ends and serve as the lists' memory
+// until then.  One workgroup.
+__global__ __launch_bounds__(1024) void k_classify(BatchArgs a) {
+    __shared__ uint32_t s_cnt[2][16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t n[2] = {0, 0};
+    for (int32_t i0 = a.n_team; i0 < a.n_models; i0 += 1024) {
+        const int32_t i = i0 + int32_t(threadIdx.x);
+        int32_t m = 0;
+        bool chip = false, solo = false;
+        if (i < a.n_models) {
+            m = a.order[i];
+            const abm_model_desc& d = a.models[m];
+            const bool pending = d.steps_target > d.step;
+            const int64_t cells = int64_t(d.W) * d.H;
+            chip = pending && !d.multi_prey && d.W >= 1 && d.H >= 1 && d.W <= kChipSide &&
+                   d.H <= kChipSide && d.R >= 1 && d.R <= kChipMaxR && d.gain_s >= 0 &&
+                   d.gain_w >= 0 && d.gain_s <= kChipMaxGain && d.gain_w <= kChipMaxGain &&
+                   d.cap_s + d.cap_w <= a.scratch_stride;
+            // room for the rows of the initial agents and an eighth more
+            const int64_t rows = chip ? (int64_t(a.chip_bytes) - chip_fixed_bytes<int16_t>(cells)) /
+                                            chip_row_bytes<int16_t>() : 0;
+            chip = chip && rows >= 2 && rows * 64 >= (d.n_s0 + d.n_w0) * 9 / 8;
+            solo = pending && !chip;
+        }
+        const uint64_t b[2] = {__ballot(chip), __ballot(solo)};
+        __syncthreads();
+        if (lane == 0)
+            for (int k = 0; k < 2; ++k) s_cnt[k][wave] = uint32_t(__popcll(b[k]));
+        __syncthreads();
+        for (int k = 0; k < 2; ++k) {
+            uint32_t at = n[k];
+            for (int w = 0; w < wave; ++w) at += s_cnt[k][w];
+            for (int w = 0; w < 16; ++w) n[k] += s_cnt[k][w];
+            at += lane_rank(b[k]);
+            if (k == 0 && chip) a.models[at].live_s = m;
+            if (k == 1 && solo) a.models[at].live_w = (int64_t(a.max_steps) << 32) | m;
+        }
+    }
+    if (threadIdx.x == 0) {
+        a.queue[kChipModels] = n[0];
+        a.queue[kSoloModels] = n[1];
+    }
+}
+
+// Models on the chip: one workgroup, and so one CU, per model.  A model that
+// does not fit, or outgrows the chip, goes (on) to the list of the others.
+__global__ __launch_bounds__(kChipThreads) void k_batched_chip(BatchArgs a) {
+    extern __shared__ uint4 chip_lds[];
+    __shared__ ChipShared sh;
+    __shared__ int32_t s_model;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            const uint32_t q = atomicAdd(a.queue + kQueueChip, 1u);
+            s_model = q < a.queue[kChipModels] ? int32_t(a.models[q].live_s) : -1;
         }
         __syncthreads();
         const int32_t m = s_model;
         __syncthreads();
-        if (m < 0) break;
-        run_model<ITEMS>(a, m, tm, lds);
+        if (m < 0) return;
+        abm_model_desc* d = a.models + m;
+        const ModelView v = view_of(a, d);
+        const int32_t t0 = d->step;
+        const int32_t t1 = d->steps_target - t0 > a.max_steps ? t0 + a.max_steps : d->steps_target;
+        ChipStats st = {nullptr, 0};
+        const int32_t t = run_on_chip<int16_t, false>(
+            v, sh, reinterpret_cast<char*>(chip_lds), a.chip_bytes,
+            a.scratch + int64_t(blockIdx.x) * a.scratch_stride, t0, t1, &st);
+        if (threadIdx.x == 0) {
+            d->step = t;
+            d->updates += int64_t(st.updates);
+            if (t < t1)
+                a.models[atomicAdd(a.queue + kSoloModels, 1u)].live_w = (int64_t(t1 - t) << 32) | m;
+        }
+        // (without it the compiler joins this branch of thread 0 to the one the
+        // loop begins with and runs its lane apart from the wave's others, which
+        // then read the last model again, without end)
+        __syncthreads();
+    }
+}
+
+// One small model (the one-model call): its grass as countdowns, statistics
+// rows per step.
+struct SmallArgs {
+    int32_t W, H, R, gain[2];
+    uint32_t T[2], seed;
+    int32_t cap[2];
+    int32_t* grass;
+    uint64_t* claims;
+    int32_t *x[2], *y[2], *e[2], *al[2];
+    int32_t* scratch;          // cap[0] + cap[1] ints
+    uint64_t* err;
+    int64_t* stats;            // [n_steps][8] or null
+    int32_t t0, n_steps, chip_bytes;
+};
+
+// The whole call in one workgroup, on the chip.  A state that the chip form
+// does not hold (agents off the grid, countdowns above 254) is stepped in
+// global memory instead, as a batch's model of one workgroup is.
+__global__ __launch_bounds__(kChipThreads) void k_predation_small(SmallArgs a) {
+    extern __shared__ uint4 chip_lds[];
+    __shared__ ChipShared sh;
+    __shared__ StepCounts counts;
+    __shared__ uint32_t lds[16];
+    __shared__ int32_t s_pre[2 * 2 + 3], s_mark[2];
+    ModelView v;
+    v.W = a.W;
+    v.H = a.H;
+    v.R = a.R;
+    v.seed = a.seed;
+    v.multi = false;
+    v.ready = a.grass;
+    v.claims = a.claims;
+    for (int s = 0; s < 2; ++s) {
+        v.gain[s] = a.gain[s];
+        v.T[s] = a.T[s];
+        v.cap[s] = a.cap[s];
+        v.link[s] = nullptr;
+        v.x[s] = a.x[s];
+        v.y[s] = a.y[s];
+        v.e[s] = a.e[s];
+        v.al[s] = a.al[s];
+    }
+    set_tags(v, a.cap[0] > a.cap[1] ? a.cap[0] : a.cap[1]);
+    const int32_t t1 = a.t0 + a.n_steps;
+    ChipStats st = {a.stats, 0};
+    const int32_t t = run_on_chip<int32_t, true>(v, sh, reinterpret_cast<char*>(chip_lds),
+                                                 a.chip_bytes, a.scratch, a.t0, t1, &st);
+    if (t == t1) return;
+    const int64_t cells = int64_t(a.W) * a.H;
+    for (int64_t c = threadIdx.x; c < cells; c += blockDim.x)
+        v.ready[c] = int32_t(uint32_t(t) + uint32_t(v.ready[c]));
+    for (int64_t w = threadIdx.x; w < 3 * cells; w += blockDim.x) rearm(v.claims + w);
+    Team tm = {};
+    tm.K = 1;
+    tm.scratch = a.scratch;
+    tm.err = a.err;
+    tm.s_pre = s_pre;
+    tm.s_mark = s_mark;
+    if (threadIdx.x < 2) s_mark[threadIdx.x] = INT32_MAX;
+    __builtin_amdgcn_s_waitcnt(0);
+    for (int32_t k = t; k < t1; ++k) {
+        if (threadIdx.x == 0) counts = StepCounts{};
+        __syncthreads();
+        uint32_t live;
+        model_step<1, false>(v, uint32_t(k), uint32_t(t), k + 1 == t1, tm, lds, &live, &counts);
+        if (threadIdx.x == 0 && a.stats) {
+            int64_t* r = a.stats + 8 * int64_t(k - a.t0);
+            r[0] = counts.live[0];
+            r[1] = counts.live[1];
+            r[2] = counts.grass;
+            r[3] = counts.eaten;
+            r[4] = counts.births[0];
+            r[5] = counts.births[1];
+            r[6] = counts.starved[0];
+            r[7] = counts.starved[1];
+        }
+        __syncthreads();
+    }
+    for (int64_t c = threadIdx.x; c < cells; c += blockDim.x) {
+        const int32_t d = int32_t(uint32_t(v.ready[c]) - uint32_t(t1));
+        v.ready[c] = d > 0 ? d : 0;
     }
 }
 
@@ -944,7 +1157,7 @@ __global__ __launch_bounds__(256) void k_batched_count(abm_model_desc* models, c
 // Clears the queue counters and the team barrier counters of a run.
 __global__ void k_reset_queue(uint32_t* q, uint32_t* team_ctr, int32_t n_teams) {
     const int32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i == 0) *reinterpret_cast<uint64_t*>(q) = 0;
+    if (i < kQueueWords) q[i] = 0;
     if (i < n_teams) team_ctr[i] = 0;
 }
 
@@ -1039,7 +1252,86 @@ bool run_shape(int items, int block, int* n_cu, int* per_cu, int64_t* lds_bytes)
     return true;
 }
 
+// Dynamic LDS a workgroup of the on-chip kernels can take on the current
+// device (the per-workgroup limit less their static LDS), looked up once per
+// device; 0 if a query fails.
+constexpr int kChipDevices = 64;
+std::atomic<int> g_chip_bytes[kChipDevices];
+
+int chip_lds_bytes() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kChipDevices) return 0;
+    int n = g_chip_bytes[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        int lds_block = 0;
+        hipFuncAttributes fb, fs;
+        if (hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
+                hipSuccess ||
+            hipFuncGetAttributes(&fb, reinterpret_cast<const void*>(k_batched_chip)) != hipSuccess ||
+            hipFuncGetAttributes(&fs, reinterpret_cast<const void*>(k_predation_small)) != hipSuccess)
+            return 0;
+        const size_t fixed = fb.sharedSizeBytes > fs.sharedSizeBytes ? fb.sharedSizeBytes : fs.sharedSizeBytes;
+        n = (lds_block - int(fixed)) / 1024 * 1024;
+        if (n < 1024) n = 1024;       // (holds no model)
+        g_chip_bytes[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 }  // namespace
+
+namespace abm {
+
+// A small model advanced by one workgroup on the chip: every slot of both
+// species and every cell fit its LDS, so whatever the populations do the call
+// is one launch.  A step takes the workgroup less than the three dependent
+// launches of the general path at every size that fits: 6.0 us against 29.0
+// at 64 x 64 cells with 500 agents, 8.3 against 32.0 with 5120, 25 against 38
+// at the largest (20544 slots, all alive at the start; a lone step from that
+// state, five agents a cell, is the one exception: see kChipPosts).
+int launch_small_predation(const abm_predation_params* p, const abm_predation_state* s,
+                           int32_t n_steps, const Workspace& w, hipStream_t st, bool* taken) {
+    *taken = false;
+    if (p->W > kChipSide || p->H > kChipSide || p->R > kChipMaxR || p->multi_prey ||
+        uint64_t(s->step) + uint64_t(n_steps) > 0x7FFFFFFFull)
+        return ABM_OK;
+    const int64_t cells = int64_t(p->W) * p->H;
+    const int64_t rows = tiles_for(p->cap_s, 64) + tiles_for(p->cap_w, 64);
+    const int64_t need = chip_fixed_bytes<int32_t>(cells) + rows * chip_row_bytes<int32_t>();
+    const int bytes = chip_lds_bytes();
+    if (need > bytes || rows < 2) return ABM_OK;
+    SmallArgs a;
+    a.W = p->W;
+    a.H = p->H;
+    a.R = p->R;
+    a.gain[0] = p->gain_s;
+    a.gain[1] = p->gain_w;
+    a.T[0] = p->T_s;
+    a.T[1] = p->T_w;
+    a.seed = p->seed;
+    a.cap[0] = int32_t(p->cap_s);
+    a.cap[1] = int32_t(p->cap_w);
+    a.grass = s->grass;
+    a.claims = s->claims;
+    const abm_species* sp[2] = {&s->sheep, &s->wolves};
+    for (int k = 0; k < 2; ++k) {
+        a.x[k] = sp[k]->x;
+        a.y[k] = sp[k]->y;
+        a.e[k] = sp[k]->e;
+        a.al[k] = sp[k]->alive;
+    }
+    a.scratch = w.list_a;             // (both lists: twice the larger capacity)
+    a.err = w.hdr + kHdrError;
+    a.stats = s->stats;
+    a.t0 = int32_t(s->step);
+    a.n_steps = n_steps;
+    a.chip_bytes = int32_t(need);
+    hipLaunchKernelGGL(k_predation_small, dim3(1), dim3(kChipThreads), size_t(need), st, a);
+    *taken = true;
+    return launch_status("predation_step");
+}
+
+}  // namespace abm
 
 extern "C" int64_t abm_batched_lds_cells(int32_t block_threads, int32_t items) {
     if (block_threads < 256 || block_threads > 1024 || (block_threads & 63)) return 0;
@@ -1139,6 +1431,24 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     const int n_teams = team_wgs / K;
     hipLaunchKernelGGL(k_reset_queue, dim3((n_teams + 255) / 256 + 1), dim3(256), 0, st, a.queue,
                        a.team_ctr, n_teams);
+    a.listed = 0;
+    a.chip_bytes = 0;
+    // Models of one workgroup go to the chip where there are no teams (4096
+    // models of 32^2 to 256^2 cells x 50 steps: 50.4 to 8.9 ms).  Beside teams
+    // they run in the time those take anyway, and a launch before them only
+    // delays the teams (96 models of 32^2 to 1024^2: 34.9 to 35.1 ms).
+    if (!(tune && tune->global_claims) && n_team == 0) {
+        const int chip = chip_lds_bytes();
+        if (chip > 0) {
+            a.listed = 1;
+            a.chip_bytes = chip;
+            hipLaunchKernelGGL(k_classify, dim3(1), dim3(1024), 0, st, a);
+            const int solo = b->n_models - n_team;
+            const int wgs = n_cu < grid ? n_cu : grid;
+            hipLaunchKernelGGL(k_batched_chip, dim3(wgs < solo ? wgs : solo), dim3(kChipThreads),
+                               size_t(chip), st, a);
+        }
+    }
     const size_t dyn = size_t(lds_bytes);
     switch (items) {
         case 1: hipLaunchKernelGGL(k_batched_run<1>, dim3(grid), dim3(block), dyn, st, a); break;

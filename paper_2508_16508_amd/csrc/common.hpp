@@ -129,4 +129,9 @@ namespace abm {
 // bit 29 = 1, so the two never coincide on one workspace.
 int next_epoch(const Workspace& w, hipStream_t st, EpochArg* out);
 
+// Runs a predation call on a model that one workgroup's LDS holds (*taken),
+// or leaves it to the caller.
+int launch_small_predation(const abm_predation_params* p, const abm_predation_state* s,
+                           int32_t n_steps, const Workspace& w, hipStream_t st, bool* taken);
+
 }  // namespace abm

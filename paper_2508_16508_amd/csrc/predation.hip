@@ -1,6 +1,10 @@
 // predation.hip -- abm_predation_init / abm_predation_step: the wolf-sheep-
 // grass model of Sec. 5.1 (Fig. 2) on one GPU, one model per launch sequence.
 //
+// A model whose slots and cells all fit one workgroup's LDS is advanced there,
+// a call being one launch (launch_small_predation); what follows is the
+// general path.
+//
 // Inside a call the state is kept in two working forms (converted at the call's
 // start and back at its end): grass holds the step at which a cell is grown
 // again (grown at step t iff ready <= t), so no per-step regrow pass is needed,
@@ -897,6 +901,12 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
     if (n_steps == 0) return ABM_OK;
     Workspace w = carve(ws, cap);
     hipStream_t st = as_stream(stream);
+    bool taken = false;
+    rc = launch_small_predation(p, s, n_steps, w, st, &taken);
+    if (taken) {
+        if (rc == ABM_OK) s->step += uint32_t(n_steps);
+        return rc;
+    }
     const int64_t G = int64_t(p->W) * p->H;
 
     StepArgs a;
