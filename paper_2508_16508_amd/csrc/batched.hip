@@ -1286,7 +1286,7 @@ namespace abm {
 // species and every cell fit its LDS, so whatever the populations do the call
 // is one launch.  A step takes the workgroup less than the three dependent
 // launches of the general path at every size that fits: 6.0 us against 29.0
-// at 64 x 64 cells with 500 agents, 8.3 against 32.0 with 5120, 25 against 38
+// at 64 x 64 cells with 500 agents, 8.3 against 32.0 with 5120, 17 against 37
 // at the largest (20544 slots, all alive at the start; a lone step from that
 // state, five agents a cell, is the one exception: see kChipPosts).
 int launch_small_predation(const abm_predation_params* p, const abm_predation_state* s,

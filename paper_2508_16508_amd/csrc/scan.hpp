@@ -70,6 +70,9 @@ __device__ __forceinline__ uint32_t lane_rank(uint64_t ballot) {
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(ballot), 0u));
 }
 
+// The lowest k bits set (all 32 from k = 32 on).
+__device__ __forceinline__ uint32_t low_bits(uint32_t k) { return k >= 32u ? ~0u : (1u << k) - 1u; }
+
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);

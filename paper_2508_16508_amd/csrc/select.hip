@@ -197,8 +197,6 @@ __global__ __launch_bounds__(kBlock) void k_select(SelArgs a) {
 // records and stored whole; unlisted lines are never visited.
 constexpr int kLinesPerPass = 32;     // lines per work item (four chunk rows of a wave)
 
-__device__ __forceinline__ uint32_t low_bits(uint32_t k) { return k >= 32u ? ~0u : (1u << k) - 1u; }
-
 // The `keep` lowest set bits of b.
 __device__ __forceinline__ uint32_t lowest_set(uint32_t b, uint32_t keep) {
     uint32_t out = 0;

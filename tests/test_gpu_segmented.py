@@ -122,3 +122,62 @@ def test_resolve_conflicts_batched(abm, orc):
         assert np.array_equal(hb[to[m]:to[m + 1]], eb), m
         assert np.array_equal(hw[to[m]:to[m + 1]], ew), m
         assert np.array_equal(hwon[co[m]:co[m + 1]], ewon), m
+
+
+# segments of one or a few slots (several starts in one 16-byte chunk), lengths around the 32
+# slots of a line and the 8192 of a tile, empty segments, packed lengths of any remainder mod 4
+@pytest.mark.parametrize("rem", [0, 1, 2, 3])
+@pytest.mark.parametrize("kind", ["ones", "few", "lines", "tiles", "holes"])
+def test_segment_starts_inside_lines(abm, orc, kind, rem):
+    g = np.random.default_rng(len(kind) * 7 + rem)
+    lens = {"ones": np.ones(9000, np.int64), "few": g.integers(1, 6, 5000),
+            "lines": g.integers(30, 35, 600), "tiles": g.choice([8191, 8192, 8193], 5),
+            "holes": g.choice([0, 0, 0, 1, 2, 70, 3000], 400)}[kind]
+    lens = np.append(lens, 4 - (int(lens.sum()) - rem) % 4)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n, A = int(off[-1]), 3
+    q = g.integers(0, np.maximum(1, lens) + 2)
+    roff = np.concatenate([[0], np.cumsum(q)]).astype(np.int64)
+    attrs = g.integers(-9, 9, (A, n)).astype(np.int32)
+    recs = g.integers(100, 10 ** 6, (A, max(1, int(roff[-1])))).astype(np.int32)
+    mask = (g.random(n) < 0.6).astype(np.uint8) * 7
+    alive = (g.random(n) < 0.5).astype(np.int32) * 3
+    kill = (g.random(n) < 0.3).astype(np.uint8)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    d_attrs, d_alive = dev(attrs), dev(alive)
+    ap, dr = abm.select_update_batched(d_attrs, dev(off), dev(mask), dev(recs), dev(roff))
+    rm = abm.remove_agents_batched(d_alive, dev(off), dev(kill))
+    ad, dd = abm.add_agents_batched(d_attrs, d_alive, dev(off), dev(recs), dev(roff))
+    ap, dr, rm, ad, dd = (t.cpu().numpy() for t in (ap, dr, rm, ad, dd))
+    e_attrs, e_alive = attrs.copy(), alive.copy()
+    for m in range(len(lens)):
+        s, r = slice(off[m], off[m + 1]), recs[:, roff[m]:roff[m + 1]]
+        sel = np.flatnonzero(mask[s])[:r.shape[1]]
+        e_attrs[:, s][:, sel] = r[:, :sel.size]
+        assert (int(ap[m]), int(dr[m])) == (sel.size, r.shape[1] - sel.size), m
+        gone = (kill[s] != 0) & (e_alive[s] != 0)
+        e_alive[s][gone] = 0
+        assert int(rm[m]) == int(gone.sum()), m
+        free = np.flatnonzero(e_alive[s] == 0)[:r.shape[1]]
+        e_attrs[:, s][:, free] = r[:, :free.size]
+        e_alive[s][free] = 1
+        assert (int(ad[m]), int(dd[m])) == (free.size, r.shape[1] - free.size), m
+    assert np.array_equal(d_attrs.cpu().numpy(), e_attrs)
+    assert np.array_equal(d_alive.cpu().numpy(), e_alive)
+
+
+def test_records_far_from_the_first(abm):
+    """Two segments of one tile whose records lie 2^28 and more apart."""
+    far = 2 ** 28 + 100
+    recs = torch.zeros((1, far + 40), dtype=torch.int32, device="cuda")
+    recs[0, :8] = torch.arange(8, device="cuda")
+    recs[0, far:far + 40] = 1000 + torch.arange(40, device="cuda")
+    off = torch.tensor([0, 10, 20, 90], device="cuda")
+    roff = torch.tensor([0, far - 164, far, far + 40], device="cuda")   # the second starts at 2^28 - 64
+    attrs = torch.full((1, 90), -1, dtype=torch.int32, device="cuda")
+    mask = torch.ones(90, dtype=torch.uint8, device="cuda")
+    ap, _ = abm.select_update_batched(attrs, off, mask, recs, roff)
+    a = attrs[0].cpu()
+    assert ap.tolist() == [10, 10, 40]
+    assert a[:10].tolist() == [0, 1, 2, 3, 4, 5, 6, 7, 0, 0] and a[10:20].tolist() == [0] * 10
+    assert a[20:60].tolist() == list(range(1000, 1040)) and a[60:].tolist() == [-1] * 30
