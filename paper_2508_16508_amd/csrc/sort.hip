@@ -7,8 +7,7 @@
 // packed into one record per agent first).  Each pass is
 //   histogram  per 4096-key tile, 256 bins in LDS, stored digit-major;
 //   scan       one workgroup per digit scans that digit's tile counts (the
-//              tile's offset within the digit's bucket), and one workgroup
-//              turns the 256 digit totals into bucket bases;
+//              tile's offset within the digit's bucket);
 //   scatter    each tile ranks its keys stably: a wave takes its 16 items in
 //              order, finds the lanes holding the same digit with eight
 //              ballots (one per digit bit), and ranks a lane after the
@@ -21,6 +20,12 @@
 // signed key becomes an unsigned one with the sign bit flipped (ascending)
 // and then all bits flipped (descending), so the descending sort keeps equal
 // keys in index order too.
+// A lane's 16 keys and slots are loaded together, before the ranks' chain of
+// LDS round trips: 2^24 keys take 20 us in the histogram and 77 in the scatter
+// (27 and 94 with each load behind the item before it), against 13 and 52 for
+// the bytes alone.  The gather is bound by the 128-byte lines it fetches for
+// 64-byte records (2^24 x 9 columns: 566 us, 5 TB/s) and the packing by the
+// bytes it moves (298 us, 5.6 TB/s).
 //
 // select_agents is a stable partition, set flags first: a count of the set flags
 // per 4096-flag tile, one scan of the tile counts, and a pass that stages
@@ -30,6 +35,7 @@
 #include "abm.h"
 #include "common.hpp"
 #include "scan.hpp"
+#include "wave.hpp"
 
 namespace abm {
 namespace {
@@ -53,7 +59,6 @@ struct PassArgs {
     int32_t* out_val;
     uint32_t* counts;          // [kBins][n_tiles]: tile counts, then tile offsets
     uint32_t* totals;          // [kBins]
-    uint32_t* base;            // [kBins]
     int64_t n;
     uint32_t n_tiles;
     uint32_t shift;
@@ -65,18 +70,35 @@ __device__ __forceinline__ int64_t slot_of(uint32_t t, int w, int k, int l) {
     return int64_t(t) * kTile + int64_t(w) * (kItems * 64) + k * 64 + l;
 }
 
-template <int SRC>
-__device__ __forceinline__ void load_item(const PassArgs& a, int64_t i, uint32_t& ukey,
-                                          int32_t& val, uint32_t& digit) {
-    if (SRC == kFromKeys) {
-        ukey = (uint32_t(a.key[i]) ^ 0x80000000u) ^ a.flip;
-        val = int32_t(i);
-        digit = (ukey >> a.shift) & 0xFFu;
-    } else {
-        ukey = a.in_key[i];
-        val = a.in_val[i];
-        digit = (ukey >> a.shift) & 0xFFu;
+// Tile of workgroup b in a scatter launch.  Workgroups go to the eight XCDs in
+// turn, so consecutive tiles would be written through eight L2s, and the ends
+// of a digit's runs, which neighbouring tiles share, leave those as partly
+// written lines.  Here each XCD takes a contiguous eighth of the tiles
+// (2^24 keys: 115 to 94 us a pass).
+constexpr uint32_t kXcds = 8;
+
+__device__ __forceinline__ uint32_t tile_of(uint32_t b, uint32_t n_tiles) {
+    return (b % kXcds) * ((n_tiles + kXcds - 1) / kXcds) + b / kXcds;
+}
+
+// Keys (and slots) of the lane's items; those past the end read as key 0.  In
+// a full tile every load is issued before the first is waited for.
+template <int SRC, bool VALS>
+__device__ __forceinline__ void load_items(const PassArgs& a, uint32_t t, int w, int lane,
+                                           uint32_t (&key)[kItems], int32_t (&val)[kItems]) {
+    const int64_t i0 = slot_of(t, w, 0, lane);
+    const bool full = (int64_t(t) + 1) * kTile <= a.n;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int64_t i = i0 + k * 64;
+        // (a slot that exists, so that the load needs no branch)
+        const int64_t at = full || i < a.n ? i : a.n - 1;
+        key[k] = SRC == kFromKeys ? uint32_t(a.key[at]) : a.in_key[at];
+        if (VALS) val[k] = SRC == kFromKeys ? int32_t(i) : a.in_val[at];
     }
+    if (SRC == kFromKeys)
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) key[k] = (key[k] ^ 0x80000000u) ^ a.flip;
 }
 
 template <int SRC>
@@ -84,17 +106,15 @@ __global__ __launch_bounds__(kBlock) void k_hist(PassArgs a) {
     __shared__ uint32_t hist[kBins];
     const uint32_t t = blockIdx.x;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t key[kItems];
+    int32_t val[kItems];
+    load_items<SRC, false>(a, t, w, lane, key, val);
     for (int d = threadIdx.x; d < kBins; d += kBlock) hist[d] = 0;
     __syncthreads();
+    const int64_t left = a.n - slot_of(t, w, 0, lane);
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const int64_t i = slot_of(t, w, k, lane);
-        if (i >= a.n) continue;
-        uint32_t ukey, digit;
-        int32_t val;
-        load_item<SRC>(a, i, ukey, val, digit);
-        atomicAdd(&hist[digit], 1u);
-    }
+    for (int k = 0; k < kItems; ++k)
+        if (k * 64 < left) atomicAdd(&hist[(key[k] >> a.shift) & 0xFFu], 1u);
     __syncthreads();
     for (int d = threadIdx.x; d < kBins; d += kBlock) a.counts[int64_t(d) * a.n_tiles + t] = hist[d];
 }
@@ -144,23 +164,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_rows(uint32_t* rows, uint
     if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
-__global__ __launch_bounds__(kBins) void k_digit_base(PassArgs a) {
-    __shared__ uint32_t lds[kBins / 64 + 1];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint32_t v = a.totals[threadIdx.x];
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) lds[w] = x;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int q = 0; q < w; ++q) before += lds[q];
-    a.base[threadIdx.x] = before + x - v;
-}
-
 // Lanes of the wave whose digit equals this lane's (among the active lanes).
 __device__ __forceinline__ uint64_t same_digit_lanes(uint32_t digit, bool active, int bits) {
     uint64_t m = __ballot(active);
@@ -178,35 +181,39 @@ __global__ __launch_bounds__(kBlock) void k_scatter(PassArgs a) {
     __shared__ uint32_t dstart[kBins];           // start of each digit within the tile
     __shared__ uint32_t skey[kTile];             // the tile in digit order
     __shared__ int32_t sval[kTile];
-    const uint32_t t = blockIdx.x;
+    const uint32_t t = tile_of(blockIdx.x, a.n_tiles);
+    if (t >= a.n_tiles) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t key[kItems], rank[kItems];
+    int32_t val[kItems];
+    load_items<SRC, true>(a, t, w, lane, key, val);
+    // thread d: the digit's keys before this tile's (in the whole range), less
+    // the base that is added below
+    const uint32_t before_tile = a.counts[int64_t(threadIdx.x) * a.n_tiles + t];
+    const uint32_t digit_total = a.totals[threadIdx.x];
     for (int d = threadIdx.x; d < kWaves * kBins; d += kBlock) (&wcount[0][0])[d] = 0;
     __syncthreads();
-    uint32_t key[kItems], dig[kItems], rank[kItems];
-    int32_t val[kItems];
+    const int64_t left = a.n - slot_of(t, w, 0, lane);
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-        const int64_t i = slot_of(t, w, k, lane);
-        const bool active = i < a.n;
-        key[k] = 0;
-        val[k] = 0;
-        dig[k] = 0;
-        if (active) load_item<SRC>(a, i, key[k], val[k], dig[k]);
-        const uint64_t peers = same_digit_lanes(dig[k], active, 8);
+        const bool active = k * 64 < left;
+        const uint32_t dig = (key[k] >> a.shift) & 0xFFu;
+        const uint64_t peers = same_digit_lanes(dig, active, 8);
         // the lowest peer reads and advances the wave's counter for this digit
-        const uint32_t before = active ? wcount[w][dig[k]] : 0u;
+        const uint32_t before = active ? wcount[w][dig] : 0u;
         rank[k] = before + uint32_t(__popcll(peers & below));
         // every peer has read the counter before the leader advances it
         __builtin_amdgcn_wave_barrier();
         if (active && (peers & below) == 0)
-            wcount[w][dig[k]] = before + uint32_t(__popcll(peers));
+            wcount[w][dig] = before + uint32_t(__popcll(peers));
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     // per digit: exclusive offsets of the waves, and the digit's tile total
+    static_assert(kBins == kBlock, "a thread per digit");
     uint32_t dtot = 0;
-    if (threadIdx.x < kBins) {
+    {
         const int d = threadIdx.x;
         for (int q = 0; q < kWaves; ++q) {
             const uint32_t c = wcount[q][d];
@@ -214,43 +221,40 @@ __global__ __launch_bounds__(kBlock) void k_scatter(PassArgs a) {
             dtot += c;
         }
     }
-    // exclusive scan of the digit totals: where each digit starts in the tile
+    // where each digit starts in the tile and in the whole range: exclusive
+    // scans over the digits
+    __shared__ int64_t goff[kBins];              // ... the latter less the former
     {
-        uint32_t x = dtot;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
+        const uint32_t in_tile = uint32_t(wave_incl_sum(int32_t(dtot)));
+        const uint32_t in_all = uint32_t(wave_incl_sum(int32_t(digit_total)));
+        __shared__ uint32_t wtot[2][kWaves];
+        if (lane == 63) {
+            wtot[0][w] = in_tile;
+            wtot[1][w] = in_all;
         }
-        __shared__ uint32_t wtot[kWaves];
-        if (lane == 63) wtot[w] = x;
         __syncthreads();
-        uint32_t before = 0;
-        for (int q = 0; q < w; ++q) before += wtot[q];
-        if (threadIdx.x < kBins) dstart[threadIdx.x] = before + x - dtot;
+        uint32_t b0 = in_tile - dtot, b1 = in_all - digit_total;
+        for (int q = 0; q < w; ++q) {
+            b0 += wtot[0][q];
+            b1 += wtot[1][q];
+        }
+        dstart[threadIdx.x] = b0;
+        goff[threadIdx.x] = int64_t(b1) + before_tile - int64_t(b0);
     }
     __syncthreads();
-    // where each digit's run of this tile goes, less its start in the tile
-    // (read from global memory once per digit, not once per key)
-    __shared__ int64_t goff[kBins];
-    if (threadIdx.x < kBins) {
-        const int d = threadIdx.x;
-        goff[d] = int64_t(a.base[d]) + a.counts[int64_t(d) * a.n_tiles + t] - int64_t(dstart[d]);
-    }
     // stage the tile in digit order
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-        const int64_t i = slot_of(t, w, k, lane);
-        if (i >= a.n) continue;
-        const uint32_t d = dig[k];
+        if (k * 64 >= left) continue;
+        const uint32_t d = (key[k] >> a.shift) & 0xFFu;
         const uint32_t p = dstart[d] + wcount[w][d] + rank[k];
         skey[p] = key[k];
         sval[p] = val[k];
     }
     __syncthreads();
     // consecutive threads write consecutive positions of a digit's run
-    const int64_t left = a.n - int64_t(t) * kTile;
-    const int32_t n_tile = left < kTile ? int32_t(left) : int32_t(kTile);
+    const int64_t rest = a.n - int64_t(t) * kTile;
+    const int32_t n_tile = rest < kTile ? int32_t(rest) : int32_t(kTile);
     for (int32_t p = threadIdx.x; p < n_tile; p += kBlock) {
         const uint32_t kk = skey[p];
         const int64_t dst = goff[(kk >> a.shift) & 0xFFu] + p;
@@ -285,6 +289,7 @@ struct GatherArgs {
     int32_t n_cols;
     int32_t* rec;                 // n records of RW words
     const int32_t* perm;
+    int32_t* perm_out;            // the caller's copy, or null
     int64_t n;
 };
 
@@ -305,6 +310,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_small(GatherArgs g) {
     for (int64_t j = int64_t(blockIdx.x) * kBlock + threadIdx.x; j < g.n;
          j += int64_t(gridDim.x) * kBlock) {
         const int64_t p = g.perm[j];
+        if (g.perm_out) g.perm_out[j] = int32_t(p);
         if (RW == 1) {
             g.col[0][j] = g.rec[p];
         } else {
@@ -377,6 +383,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_recs(GatherArgs g) {
                 r[4 * v + 2] = t.z;
                 r[4 * v + 3] = t.w;
             }
+            if (g.perm_out) g.perm_out[j] = g.perm[j];
 #pragma unroll
             for (int c = 0; c < RW; ++c)
                 if (c < g.n_cols) g.col[c][j] = r[c];
@@ -510,7 +517,7 @@ struct SortWs {
     uint32_t *key_a, *key_b;   // the other ping-pong buffers ...
     int32_t* val_a;
     int32_t* rec;              // ... whose region the records reuse afterwards
-    uint32_t *counts, *totals, *base;
+    uint32_t *counts, *totals;
 };
 
 uint32_t tiles_of(int64_t n) { return uint32_t((n + kTile - 1) / kTile); }
@@ -544,8 +551,6 @@ SortWs carve_sort(void* ws, int64_t n, int n_cols) {
     s.counts = reinterpret_cast<uint32_t*>(p);
     p += round256(4 * int64_t(kBins) * tiles_of(m));
     s.totals = reinterpret_cast<uint32_t*>(p);
-    p += round256(4 * kBins);
-    s.base = reinterpret_cast<uint32_t*>(p);
     return s;
 }
 
@@ -554,8 +559,8 @@ void launch_pass(const PassArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(k_hist<SRC>, dim3(a.n_tiles), dim3(kBlock), 0, st, a);
     hipLaunchKernelGGL(k_scan_rows, dim3(kBins), dim3(kScanThreads), 0, st, a.counts, a.n_tiles,
                        a.totals);
-    hipLaunchKernelGGL(k_digit_base, dim3(1), dim3(kBins), 0, st, a);
-    hipLaunchKernelGGL(k_scatter<SRC>, dim3(a.n_tiles), dim3(kBlock), 0, st, a);
+    const uint32_t grid = (a.n_tiles + kXcds - 1) / kXcds * kXcds;
+    hipLaunchKernelGGL(k_scatter<SRC>, dim3(grid), dim3(kBlock), 0, st, a);
 }
 
 int check_sort_ws(void* ws, size_t ws_bytes, int64_t n, int n_cols) {
@@ -607,7 +612,6 @@ extern "C" int abm_sort_agents(const abm_soa* dst, const int32_t* key, int32_t d
     a.key = key;
     a.counts = s.counts;
     a.totals = s.totals;
-    a.base = s.base;
     a.n = n;
     a.n_tiles = tiles_of(n);
     a.flip = descending ? ~0u : 0u;
@@ -635,6 +639,7 @@ extern "C" int abm_sort_agents(const abm_soa* dst, const int32_t* key, int32_t d
         ga.n_cols = n_cols;
         ga.rec = s.rec;
         ga.perm = vin;
+        ga.perm_out = perm;
         ga.n = n;
         switch (rec_words(n_cols)) {
             case 1: gather_cols<1>(ga, st); break;
@@ -645,7 +650,8 @@ extern "C" int abm_sort_agents(const abm_soa* dst, const int32_t* key, int32_t d
             default: gather_cols<32>(ga, st); break;
         }
     }
-    if (perm) hipLaunchKernelGGL(k_copy, stream_grid(n), dim3(kBlock), 0, st, vin, perm, n);
+    if (perm && n_cols == 0)
+        hipLaunchKernelGGL(k_copy, stream_grid(n), dim3(kBlock), 0, st, vin, perm, n);
     return launch_status("sort_agents");
 }
 
