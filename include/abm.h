@@ -182,6 +182,16 @@ ABM_API int abm_resolve_conflicts(int64_t n_claims, const int32_t* target, const
                           const uint8_t* active, int64_t n_targets, uint64_t* best,
                           int32_t* winner, uint8_t* won, void* stream);
 
+/* The same with a workspace, which lets a call with many claims partition them
+ * by target instead of posting every key with a device-wide atomic.  The
+ * results are equal.  abm_resolve_workspace_bytes: the bytes it needs (ws is
+ * 256-byte aligned), or 0 when the call would not use them (ws may be NULL). */
+ABM_API size_t abm_resolve_workspace_bytes(int64_t n_claims, int64_t n_targets);
+ABM_API int abm_resolve_conflicts_ws(int64_t n_claims, const int32_t* target, const uint32_t* prio,
+                             const uint8_t* active, int64_t n_targets, uint64_t* best,
+                             int32_t* winner, uint8_t* won, void* ws, size_t ws_bytes,
+                             void* stream);
+
 /* ---------------------------------------------------------------------------
  * Predation model (Sec. 5.1, Fig. 2: Wilensky's wolf-sheep-grass on a 2-D
  * toroidal lattice).  Each step runs, in order:

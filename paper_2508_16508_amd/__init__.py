@@ -25,7 +25,8 @@ ABM_OP_SELECT_INDICES, ABM_OP_PREDATION = 4, 5
 # Every symbol include/abm.h declares.
 EXPORTED = (
     "abm_workspace_bytes", "abm_workspace_init", "abm_select_update", "abm_select_indices",
-    "abm_add_agents", "abm_remove_agents", "abm_resolve_conflicts", "abm_predation_init",
+    "abm_add_agents", "abm_remove_agents", "abm_resolve_conflicts",
+    "abm_resolve_conflicts_ws", "abm_resolve_workspace_bytes", "abm_predation_init",
     "abm_predation_step", "abm_last_error", "abm_version", "abm_batched_workspace_bytes",
     "abm_predation_batched_init", "abm_predation_run_batched", "abm_predation_batched_grass",
     "abm_select_update_batched", "abm_add_agents_batched", "abm_remove_agents_batched",
@@ -127,6 +128,9 @@ def lib():
         L.abm_add_agents.argtypes = [C.POINTER(Soa), C.POINTER(Records), vp, vp, vp, sz, vp]
         L.abm_remove_agents.argtypes = [C.POINTER(Soa), vp, vp, vp, sz, vp]
         L.abm_resolve_conflicts.argtypes = [i64, vp, vp, vp, i64, vp, vp, vp, vp]
+        L.abm_resolve_workspace_bytes.restype = sz
+        L.abm_resolve_workspace_bytes.argtypes = [i64, i64]
+        L.abm_resolve_conflicts_ws.argtypes = [i64, vp, vp, vp, i64, vp, vp, vp, vp, sz, vp]
         L.abm_predation_init.argtypes = [C.POINTER(PredationParams),
                                          C.POINTER(PredationStatePtrs), vp]
         L.abm_predation_step.argtypes = [C.POINTER(PredationParams),
@@ -387,8 +391,14 @@ def resolve_conflicts(target, prio, n_targets, active=None, best=None, winner=No
         winner = torch.empty(max(1, n_targets), dtype=torch.int32, device=dev)
     if won is None:
         won = torch.empty(max(1, n), dtype=torch.uint8, device=dev)
-    _check(lib().abm_resolve_conflicts(n, _p(target), _p(prio), _p(active), n_targets, _p(best),
-                                       _p(winner), _p(won), _stream(stream)))
+    ws, need = None, int(lib().abm_resolve_workspace_bytes(n, n_targets))
+    if need:
+        with torch.cuda.stream(stream):   # (freed in the order of the stream that uses it)
+            raw = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+        off = (-raw.data_ptr()) % 256
+        ws = raw[off: off + need]
+    _check(lib().abm_resolve_conflicts_ws(n, _p(target), _p(prio), _p(active), n_targets, _p(best),
+                                          _p(winner), _p(won), _p(ws), need, _stream(stream)))
     return best, winner, won
 
 

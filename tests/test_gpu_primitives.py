@@ -214,6 +214,45 @@ def test_resolve_conflicts_full_priority_range(abm, orc):
     assert np.array_equal(host(won), ewon)
 
 
+# claims enough to be partitioned by target: one target, fewer targets than ranges, ranges of
+# one and several targets, the largest span of a range and one target more (not partitioned);
+# crowded: most claims on a few neighbouring targets, so that their range is cut
+@pytest.mark.parametrize("crowded", [False, True])
+@pytest.mark.parametrize("n_targets", [1, 7, 512, 513, 70_001, 1 << 20, 512 << 14, (512 << 14) + 1])
+def test_resolve_conflicts_partitioned(abm, orc, n_targets, crowded):
+    n = (1 << 20) + 4097
+    assert (abm.lib().abm_resolve_workspace_bytes(n, n_targets) > 0) == (n_targets <= 512 << 14)
+    g = np.random.default_rng(n_targets + crowded)
+    target = g.integers(-1, n_targets + 1, size=n).astype(np.int32)
+    if crowded:
+        target[g.random(n) < 0.9] = n_targets // 2
+        target[::5] = n_targets // 2 + g.integers(0, 3, target[::5].size)
+    prio = g.integers(0, 2 ** 32, size=n, dtype=np.uint64).astype(np.uint32) >> (20 if crowded else 0)
+    active = (g.random(n) < 0.9).astype(np.uint8) * 3
+    eb, ew, ewon = orc.resolve_conflicts(target, prio, n_targets, active=active)
+    best, winner, won = abm.resolve_conflicts(dev(target), dev(prio.view(np.int32)).view(torch.uint32),
+                                              n_targets, active=dev(active))
+    assert np.array_equal(host(best), eb)
+    assert np.array_equal(host(winner), ew)
+    assert np.array_equal(host(won), ewon)
+
+
+def test_resolve_conflicts_partitioned_on_a_side_stream(abm, orc):
+    n, nt = 1 << 20, 50_000
+    g = np.random.default_rng(8)
+    target = g.integers(0, nt, size=n).astype(np.int32)
+    prio = g.integers(0, 4, size=n).astype(np.uint32)
+    exp = orc.resolve_conflicts(target, prio, nt)
+    d_target, d_prio = dev(target), dev(prio.view(np.int32)).view(torch.uint32)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    got = abm.resolve_conflicts(d_target, d_prio, nt, stream=side)
+    torch.zeros(3 * n, dtype=torch.int64, device="cuda").fill_(-1)   # takes what was freed
+    side.synchronize()
+    for a, e in zip(got, exp):
+        assert np.array_equal(host(a), e)
+
+
 def test_graph_replay_select_add_remove(abm, orc):
     """select_update, add_agents and remove_agents recorded once into a graph and
     replayed with fresh inputs copied in between: the device-side epoch keeps
