@@ -167,7 +167,8 @@ def lib():
         L.abm_version.restype = C.c_char_p
         for name in EXPORTED:
             if name not in ("abm_workspace_bytes", "abm_last_error", "abm_version",
-                            "abm_batched_workspace_bytes", "abm_sort_workspace_bytes"):
+                            "abm_batched_workspace_bytes", "abm_sort_workspace_bytes",
+                            "abm_resolve_workspace_bytes"):
                 getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
@@ -179,8 +180,14 @@ def _check(rc: int):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+
+
+# the current stream's handle without a Stream object around it (0.6 us against 3)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
 def _p(t):
@@ -207,7 +214,9 @@ def _rows(t: torch.Tensor, name: str):
     _require(t, torch.int32, name)
     if t.dim() != 2:
         raise ValueError(f"{name} must be [n_attrs, length]")
-    return [t[a].data_ptr() for a in range(t.shape[0])], t.shape[1]
+    n_rows, n = t.shape
+    base = t.data_ptr()
+    return [base + 4 * n * a for a in range(n_rows)], n
 
 
 def make_soa(attrs, alive=None) -> Soa:
@@ -253,7 +262,15 @@ def workspace_error(ws: torch.Tensor) -> int:
 
 
 def _counts(device, *given):
-    return [g if g is not None else torch.zeros(1, dtype=torch.int64, device=device) for g in given]
+    """Count outputs: every call writes them whole, so none is cleared before."""
+    return [g if g is not None else torch.empty(1, dtype=torch.int64, device=device) for g in given]
+
+
+def _segment_counts(n_seg, device):
+    """One count per segment, each written by the call (none: a single 0)."""
+    if n_seg == 0:
+        return torch.zeros(1, dtype=torch.int64, device=device)
+    return torch.empty(n_seg, dtype=torch.int64, device=device)
 
 
 def select_update(attrs, sel_mask, recs, upd_mask=None, ws=None, applied=None, dropped=None,
@@ -420,10 +437,8 @@ def select_update_batched(attrs, slot_off, sel_mask, recs, rec_off, ws=None, app
     dev = slot_off.device
     if ws is None:
         ws = workspace(dst.capacity, ABM_OP_SELECT_UPDATE, dev, stream)
-    applied = applied if applied is not None else torch.zeros(max(1, n_seg), dtype=torch.int64,
-                                                               device=dev)
-    dropped = dropped if dropped is not None else torch.zeros(max(1, n_seg), dtype=torch.int64,
-                                                               device=dev)
+    applied = applied if applied is not None else _segment_counts(n_seg, dev)
+    dropped = dropped if dropped is not None else _segment_counts(n_seg, dev)
     _check(lib().abm_select_update_batched(n_seg, C.byref(dst), _p(slot_off), _p(sel_mask),
                                            C.byref(upd), _p(rec_off), _p(applied), _p(dropped),
                                            _p(ws), ws.numel(), _stream(stream)))
@@ -437,8 +452,7 @@ def add_agents_batched(attrs, alive, slot_off, recs, rec_off, ws=None, stream=No
     dev = slot_off.device
     if ws is None:
         ws = workspace(dst.capacity, ABM_OP_ADD_AGENTS, dev, stream)
-    added = torch.zeros(max(1, n_seg), dtype=torch.int64, device=dev)
-    dropped = torch.zeros(max(1, n_seg), dtype=torch.int64, device=dev)
+    added, dropped = _segment_counts(n_seg, dev), _segment_counts(n_seg, dev)
     _check(lib().abm_add_agents_batched(n_seg, C.byref(dst), _p(slot_off), C.byref(nb),
                                         _p(rec_off), _p(added), _p(dropped), _p(ws), ws.numel(),
                                         _stream(stream)))
@@ -456,7 +470,7 @@ def remove_agents_batched(alive, slot_off, kill_mask, ws=None, stream=None):
     dev = slot_off.device
     if ws is None:
         ws = workspace(alive.numel(), ABM_OP_REMOVE_AGENTS, dev, stream)
-    removed = torch.zeros(max(1, n_seg), dtype=torch.int64, device=dev)
+    removed = _segment_counts(n_seg, dev)
     _check(lib().abm_remove_agents_batched(n_seg, C.byref(s), _p(slot_off), _p(kill_mask),
                                            _p(removed), _p(ws), ws.numel(), _stream(stream)))
     return removed
