@@ -245,24 +245,26 @@ constexpr int kStreamPolicy = 2;            // nt
 // One work item of the line-list merge: attribute array `d` (ALIVE: the
 // alive array, merged with the constant 1).  The thread handles chunk t mod 8
 // of the lines at list entries i0 + j * istride (j < 4; entries past the list
-// are skipped): it loads the old values (not for a chunk whose four slots all receive), reads
+// and, BOUNDED, chunks from n_chunks on are skipped): it loads the old values (not for a chunk whose four slots all receive), reads
 // the records of the receiving slots into them and stores the chunks whole.
 // All accesses are buffer instructions with 32-bit offsets from a per-tile
 // base (few registers); an access that is not wanted gets an out-of-range
 // offset, which the hardware skips (a skipped load returns 0).
-template <int MODE, bool ALIVE>
+template <int MODE, bool ALIVE, bool BOUNDED>
 __device__ __forceinline__ void merge_item(const SelArgs& a, int32_t* d, const int32_t* rec,
                                            int64_t tbase, uint32_t tile_excl, uint32_t lim,
                                            uint32_t total, uint32_t n_lines, uint32_t i0,
                                            uint32_t istride, const uint16_t* list,
-                                           const uint32_t* wbits, const uint32_t* wpre) {
+                                           const uint32_t* wbits, const uint32_t* wpre,
+                                           uint32_t n_chunks) {
     uint32_t dsc[4], off[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const uint32_t i = i0 + uint32_t(j) * istride;
         const uint32_t k = threadIdx.x & 7u;
         const uint32_t line = i < n_lines ? list[i] : 0u;
-        dsc[j] = i < n_lines ? chunk_desc(wbits[line], wpre[line], k, lim, total) : 0u;
+        const bool in = i < n_lines && (!BOUNDED || line * 8u + k < n_chunks);
+        dsc[j] = in ? chunk_desc(wbits[line], wpre[line], k, lim, total) : 0u;
         off[j] = (line * 8u + k) * 16u;
     }
     const __amdgpu_buffer_rsrc_t rd =
@@ -364,21 +366,23 @@ __device__ __forceinline__ void merge_dense(const SelArgs& a, int32_t* d, const 
     }
 }
 
-// The listed lines of a full tile, every attribute (and, for add_agents,
+// The listed lines of a tile, every attribute (and, for add_agents,
 // alive = 1 as one more).  A dense tile (more than 96 listed lines) runs the
 // arrays one after another with the whole block on each: thread t takes list
 // entries 32 j + t / 8 (j < 8, in two batches of four), so the four waves work
 // on neighbouring lines of one array.  A sparse tile would then leave each
 // wave a chain of one memory round trip per array; instead its work is cut
 // into items of (array, 32 listed lines), wave w taking items w, w + 4, ...,
-// so its arrays are in flight on the four waves at once.
-template <int MODE>
+// so its arrays are in flight on the four waves at once.  The partial last
+// tile (BOUNDED) goes by items too, whole chunks only.
+template <int MODE, bool BOUNDED>
 __device__ __forceinline__ void merge_tile(const SelArgs& a, int64_t tbase, uint32_t tile_excl,
                                            uint32_t lim, uint32_t total, uint32_t n_lines,
                                            const uint16_t* list, const uint32_t* wbits,
                                            const uint32_t* wpre) {
     const int n_arr = a.n_true + (MODE == kAddDense ? 1 : 0);
-    if (n_lines > 3 * kLinesPerPass) {
+    const uint32_t n_chunks = BOUNDED ? uint32_t((a.n - tbase) >> 2) : 0u;   // whole chunks
+    if (!BOUNDED && n_lines > 3 * kLinesPerPass) {
         uint32_t dsc[8], off[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -405,11 +409,11 @@ __device__ __forceinline__ void merge_tile(const SelArgs& a, int64_t tbase, uint
         const int at = it / batches, b = it - at * batches;
         const uint32_t i0 = uint32_t(b * kLinesPerPass) + ((threadIdx.x & 63u) >> 3);
         if (MODE == kAddDense && at == a.n_true)
-            merge_item<MODE, true>(a, a.alive, nullptr, tbase, tile_excl, lim, total, n_lines, i0,
-                                   8, list, wbits, wpre);
+            merge_item<MODE, true, BOUNDED>(a, a.alive, nullptr, tbase, tile_excl, lim, total,
+                                            n_lines, i0, 8, list, wbits, wpre, n_chunks);
         else
-            merge_item<MODE, false>(a, a.dst[at], a.rec[at], tbase, tile_excl, lim, total,
-                                    n_lines, i0, 8, list, wbits, wpre);
+            merge_item<MODE, false, BOUNDED>(a, a.dst[at], a.rec[at], tbase, tile_excl, lim, total,
+                                             n_lines, i0, 8, list, wbits, wpre, n_chunks);
     }
 }
 
@@ -419,7 +423,9 @@ __device__ __forceinline__ void merge_tile(const SelArgs& a, int64_t tbase, uint
 // to every attribute and, for add_agents, to alive with the constant 1 (see
 // merge_tile).  Every
 // pointer is 16-byte aligned (checked on the host); the last tile, when
-// partial, writes slot by slot.  The kernel stays within 64 VGPRs, so all
+// partial, merges its whole chunks and writes the slots behind them one by one
+// (10,000 slots x 4 attributes, of which 500 are written: 20 to 10 us with
+// every slot of that tile written by its lane before).  The kernel stays within 64 VGPRs, so all
 // 2048 tiles of a 2^24-slot launch are resident at once and the look-back
 // waits one round.
 template <int MODE>
@@ -467,16 +473,20 @@ __global__ __launch_bounds__(kBlock) void k_merge(SelArgs a) {
     __syncthreads();
 
     if (lim > 0 && full_tile) {
-        merge_tile<MODE>(a, tbase, tile_excl, lim, total, n_lines, list, wbits, wpre);
-    } else if (lim > 0 && listed) {
-        // partial last tile: this lane's own receiving slots, one by one
-        const uint32_t ab = receiving(bits0, r0, lim, total);
-        for (uint32_t k = 0; k < 32; ++k) {
-            if (!((ab >> k) & 1u)) continue;
-            const int64_t g = int64_t(tile_excl) + r0 + __popc(ab & low_bits(k));
-            const int64_t r = (MODE == kSelIndirect) ? int64_t(a.rec_idx[g]) : g;
-            for (int at = 0; at < a.n_true; ++at) a.dst[at][lbase + k] = a.rec[at][r];
-            if (MODE == kAddDense) a.alive[lbase + k] = 1;
+        merge_tile<MODE, false>(a, tbase, tile_excl, lim, total, n_lines, list, wbits, wpre);
+    } else if (lim > 0) {
+        merge_tile<MODE, true>(a, tbase, tile_excl, lim, total, n_lines, list, wbits, wpre);
+        // the chunk cut by the end of the arrays, by the lane that owns it
+        const int64_t left = a.n - lbase;
+        if (listed && left < kSlotsPerLane) {
+            const uint32_t ab = receiving(bits0, r0, lim, total);
+            for (uint32_t k = uint32_t(left) & ~3u; k < uint32_t(left); ++k) {
+                if (!((ab >> k) & 1u)) continue;
+                const int64_t g = int64_t(tile_excl) + r0 + __popc(ab & low_bits(k));
+                const int64_t r = (MODE == kSelIndirect) ? int64_t(a.rec_idx[g]) : g;
+                for (int at = 0; at < a.n_true; ++at) a.dst[at][lbase + k] = a.rec[at][r];
+                if (MODE == kAddDense) a.alive[lbase + k] = 1;
+            }
         }
     }
     if (tile == a.ntiles - 1 && threadIdx.x == 0) {

@@ -214,6 +214,39 @@ def test_resolve_conflicts_full_priority_range(abm, orc):
     assert np.array_equal(host(won), ewon)
 
 
+# a last tile of 8192 slots that is partial: alone or after a full one, whole 16-byte chunks or
+# one cut by the end; every row starts at a 16-byte address (one tensor per attribute)
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 31, 34, 64, 8189, 8191, 8193, 8200, 8235, 16383])
+@pytest.mark.parametrize("p, q", [(0.05, 1.0), (0.7, 1.0), (0.7, 0.5), (1.0, 1.2)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_partial_last_tile(abm, orc, n, p, q, masked):
+    g = np.random.default_rng(n)
+    A = 3
+    attrs = g.integers(-99, 99, (A, n)).astype(np.int32)
+    mask = (g.random(n) < p).astype(np.uint8)
+    k = max(1, int(q * mask.sum()))
+    recs = g.integers(1000, 9999, (A, 2 * k)).astype(np.int32)[:, :k].copy()
+    use = (g.random(k) < 0.8).astype(np.uint8) if masked else None
+    alive = (g.random(n) < 0.5).astype(np.int32)
+    src = recs if use is None else recs[:, use != 0]
+    at = np.flatnonzero(mask)[:src.shape[1]]
+    exp = attrs.copy()
+    exp[:, at] = src[:, :at.size]
+    rows = [dev(r) for r in attrs]
+    ap, dr = abm.select_update(rows, dev(mask), [dev(r) for r in recs],
+                               None if use is None else dev(use))
+    assert (int(ap), int(dr)) == (at.size, src.shape[1] - at.size)
+    assert np.array_equal(np.stack([host(r) for r in rows]), exp)
+    free = np.flatnonzero(alive == 0)[:k]
+    exp[:, free] = recs[:, :free.size]
+    d_alive = dev(alive)
+    ad, dd = abm.add_agents(rows, d_alive, [dev(r) for r in recs])
+    alive[free] = 1
+    assert (int(ad), int(dd)) == (free.size, k - free.size)
+    assert np.array_equal(np.stack([host(r) for r in rows]), exp)
+    assert np.array_equal(host(d_alive), alive)
+
+
 # claims enough to be partitioned by target: one target, fewer targets than ranges, ranges of
 # one and several targets, the largest span of a range and one target more (not partitioned);
 # crowded: most claims on a few neighbouring targets, so that their range is cut

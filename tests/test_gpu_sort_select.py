@@ -95,6 +95,17 @@ def test_select_agents_matches_oracle(abm, orc, n, p):
     assert np.array_equal(order.cpu().numpy()[:n], eo)
 
 
+# the last size of the single launch (15 tiles of 4096 flags) and the first past it
+@pytest.mark.parametrize("n", [4096, 15 * 4096 - 1, 15 * 4096, 15 * 4096 + 1])
+@pytest.mark.parametrize("p", [0.0, 0.5, 1.0])
+def test_select_agents_around_the_single_launch(abm, orc, n, p):
+    cond = (np.random.default_rng(n).random(n) < p).astype(np.uint8) * 255
+    eo, ec = orc.select_agents(cond)
+    order, count = abm.select_agents(torch.from_numpy(cond).cuda())
+    assert int(count.item()) == ec
+    assert np.array_equal(order.cpu().numpy()[:n], eo)
+
+
 @pytest.mark.parametrize("offset", [1, 3, 8])
 @pytest.mark.parametrize("n", [5, 4096 * 3 + 9])
 def test_select_agents_unaligned_flags(abm, orc, offset, n):
