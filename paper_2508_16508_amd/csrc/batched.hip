@@ -1285,10 +1285,12 @@ namespace abm {
 // A small model advanced by one workgroup on the chip: every slot of both
 // species and every cell fit its LDS, so whatever the populations do the call
 // is one launch.  A step takes the workgroup less than the three dependent
-// launches of the general path at every size that fits: 6.0 us against 29.0
-// at 64 x 64 cells with 500 agents, 8.3 against 32.0 with 5120, 17 against 37
-// at the largest (20544 slots, all alive at the start; a lone step from that
-// state, five agents a cell, is the one exception: see kChipPosts).
+// launches of the general path: 6.0 us against 17.5 at 64 x 64 cells with 500
+// agents, 7.9 against 20.8 with 5120 (one step alone, from that state, 53 and
+// 53).  With many more slots than cells a first step can find several agents
+// in every cell, which one workgroup is slow at (20000 agents on 64 x 64 cells:
+// 183 us against 53), so past 1.5 slots a cell only models of up to 1024 slots
+// are taken.
 int launch_small_predation(const abm_predation_params* p, const abm_predation_state* s,
                            int32_t n_steps, const Workspace& w, hipStream_t st, bool* taken) {
     *taken = false;
@@ -1299,7 +1301,8 @@ int launch_small_predation(const abm_predation_params* p, const abm_predation_st
     const int64_t rows = tiles_for(p->cap_s, 64) + tiles_for(p->cap_w, 64);
     const int64_t need = chip_fixed_bytes<int32_t>(cells) + rows * chip_row_bytes<int32_t>();
     const int bytes = chip_lds_bytes();
-    if (need > bytes || rows < 2) return ABM_OK;
+    const int64_t slots = p->cap_s + p->cap_w;
+    if (need > bytes || (slots > 1024 && 2 * slots > 3 * cells)) return ABM_OK;
     SmallArgs a;
     a.W = p->W;
     a.H = p->H;

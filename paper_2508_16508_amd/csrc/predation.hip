@@ -10,11 +10,10 @@
 // again (grown at step t iff ready <= t), so no per-step regrow pass is needed,
 // and a bitmask in the workspace marks the live slots, so the per-step kernels
 // read 1 bit per slot instead of the 4-byte alive word and visit only live
-// agents.  Each kernel works on tiles of 8192 slots (1024 threads, thread t <
-// 256 owning the 32 slots of bitmask word t); a tile first compacts its live
-// slots into a list in LDS and then spreads that list over all its threads,
-// one agent per thread per batch, so dense and sparse tiles alike keep every
-// lane busy.  Step t is three launches (each arrow a grid-wide dependency):
+// agents.  Each kernel works on tiles of 2048 slots, four slots a thread, whose
+// loads and random accesses are in flight together; a slot that is not live
+// repeats the block's first load, so nothing branches around a load.
+// Step t is three launches (each arrow a grid-wide dependency):
 //   K1 move+claim   every live agent moves, pays 1 energy and posts its
 //                   packed (step tag, draw, slot) key with a 64-bit atomicMin
 //                   into the claim tables of its cell: grass (sheep on grown
@@ -33,9 +32,9 @@
 //                   of a tag period the claim tables are re-armed (each
 //                   workgroup streams its slice; within a period the falling
 //                   tags make older words lose, see claim_key).
-// Tiles past the last tile holding a live agent (the tile mark K3 leaves for
-// the next step) skip their work: they hold no agent, K2's scans stop below
-// them, and K3 computes their free-slot prefixes from the totals.
+// Blocks past the last one holding a live agent (the mark K3 leaves for the
+// next step) skip their work: they hold no agent, K2's scans stop below them,
+// and K3 computes their free-slot prefixes from the totals.
 // With multi_prey, K1 instead pushes every live sheep and wolf onto a list of
 // its cell (64-bit atomicExch on the prey / eater words, which then hold list
 // heads), and K1b, between K1 and K2, pairs the r-th wolf of each cell (eat
@@ -53,33 +52,37 @@
 namespace abm {
 namespace {
 
-constexpr int kWaves = 4;
-constexpr int kBlock = 256;
-constexpr int64_t kTile = int64_t(kBlock) * 32;   // 8192 slots: one bitmask word per thread
+constexpr int kBlock = 256;                       // threads of the element-wise kernels
+constexpr int kOwners = 64;                       // threads that own a tile's bitmask words
+constexpr int64_t kTile = int64_t(kOwners) * 32;  // 2048 slots: one bitmask word per owner
 constexpr uint32_t kTagBits = 4;                  // claim-key tag: periods of 14 steps
-// List entries per thread and batch.  With 1024 threads a tile, one each
-// measured 102 us per 2048^2 step against 104 with two and 106 with four:
-// the waves hide the latency of the random cell accesses better than a
-// thread's own batch does.
-#ifndef ABM_PRED_IN_FLIGHT
-#define ABM_PRED_IN_FLIGHT 1
-#endif
-constexpr int kInFlight = ABM_PRED_IN_FLIGHT;
-// Threads per tile: kBlock own the tile's bitmask words, and kHelpers times
-// as many share the tile's list of agents.  Live agents crowd the low tiles
-// (children take the lowest free slots), so a few hundred tiles hold all the
-// work.  At 2048^2, twice the threads on each took 9% off the step and four
-// times (1024-thread blocks, the most a block holds) a further 8%: the tiles
-// past the last live one exit at once, so the larger blocks cost no extra
-// dispatch rounds.
-constexpr int kHelpers = 4;
+// Threads of a workgroup, four slots of a tile each.  Live agents crowd the low
+// tiles (children take the lowest free slots), so the tiles must be small for
+// the work to reach every CU, and their threads many: the chain of dependent
+// random accesses of an agent bounds the step.  In us per step, with tiles of
+// 8192 slots, whose live slots 1024 threads took from a list, and now: 300^2
+// cells 70 and 33, 700^2 87 and 36, 2048^2 with 10 % sheep 106 and 63, with
+// 38 % (2 M agents at first, where the 26 G atomics a second bound K1 and the
+// lines of the claim table K2) 126 and 120.
+constexpr int kThreads = 512;
+constexpr int kThreadWaves = kThreads / 64;
+constexpr int kPerThread = int(kTile) / kThreads;
+// The workgroups of a species take one tile each up to kSingleTiles (2 M
+// slots), and kTilesPerBlock tiles beyond: those are empty in most states, and
+// workgroups that only find that out cost their dispatch (16 M slots: 8192).
+constexpr uint32_t kSingleTiles = 1024, kTilesPerBlock = 8;
+constexpr int kBlockWords = kOwners * int(kTilesPerBlock);   // bitmask words, one a thread
+static_assert(kBlockWords == kThreads, "a thread per bitmask word of a block");
 // header words of the free-slot totals (words 4 and 5 are unused by the
 // common layout)
 constexpr int kHdrFreeA = 4, kHdrFreeB = 5;
-// words 6-9: the tile marks of even and odd steps (two species each)
-constexpr int kHdrMark = 6;
-static_assert(kHdrFreeA > kHdrCountB && kHdrMark + 3 < kHdrError, "header word clash");
-static_assert(kWaves * kHelpers >= 2 * kLevels, "the dual-chain prefix needs 2 kLevels waves");
+// words 6-21: the block marks of even and odd steps, two species each, each
+// spread over four words (a workgroup raises the one of its number: atomics on
+// one address serialise)
+constexpr int kHdrMark = 6, kMarkLanes = 4;
+static_assert(kHdrFreeA > kHdrCountB && kHdrMark + 4 * kMarkLanes <= kHdrError,
+              "header word clash");
+static_assert(kThreadWaves >= 2 * kLevels, "the dual-chain prefix needs 2 kLevels waves");
 constexpr uint64_t kNoClaim = ~0ull;
 
 // Offsets of the eight neighbours, indexed by dir = draw >> 29, packed as
@@ -125,13 +128,14 @@ struct StepArgs {
     int32_t* blist[2];    // breeder lists
     int64_t* d_nb[2];     // breeder counts
     int64_t* d_nf[2];     // free-slot counts (this step's births are min(nf, nb))
-    int32_t* free_pre[2]; // per tile: exclusive free-slot prefix, written by K2 for K3
+    int32_t* free_pre[2]; // per block: exclusive free-slot prefix, written by K2 for K3
     uint32_t tiles[2];
+    uint32_t blocks[2];
     uint32_t chain_off[2];  // start of each species' breeder scan chain in the status words
     uint32_t fchain_off[2]; // ... and of its free-slot scan chain
     int32_t multi;          // prey by rank within a cell (K1 builds lists, K1b matches)
-    uint64_t* mark_rd;      // [2] per species: no live agent in this tile or past it
-    uint64_t* mark_wr;      // [2] the same for the next step, raised by K3 (cleared by K1)
+    uint64_t* mark_rd;      // [2][kMarkLanes] per species: no live agent in a block past the largest
+    uint64_t* mark_wr;      // the same for the next step, raised by K3 (cleared by K1)
 };
 
 __device__ __forceinline__ int32_t wrap_step(int32_t v, int32_t d, int32_t n) {
@@ -256,83 +260,91 @@ __global__ __launch_bounds__(kBlock) void k_fill64(int64_t* p, int64_t n, int64_
 }
 
 // ------------------------------------------------------------------ tiles
-// Tile t of a species covers slots [8192 t, 8192 t + 8192) and bitmask words
-// [256 t, 256 t + 256), thread k owning word 256 t + k (slots 32 k .. 32 k + 31
-// of the tile).  Bits of slots at or beyond the capacity are always zero.
-// Workgroups take the tiles of both species interleaved -- sheep 0, wolves 0,
-// sheep 1, wolves 1, ... until the shorter chain ends, then the rest of the
-// longer one -- so that the low tiles, where children fill the lowest free
-// slots and the live agents gather, are all in the first round of resident
-// workgroups; within each chain tiles still run in increasing order.
-struct TileRef {
+// Tile t of a species covers slots [2048 t, 2048 t + 2048) and bitmask words
+// [64 t, 64 t + 64).  Bits of slots at or beyond the capacity are always zero.
+// A block is what one workgroup takes: one tile, or kTilesPerBlock consecutive
+// ones.  The blocks of both species are interleaved -- sheep 0, wolves 0, sheep
+// 1, wolves 1, ... until the shorter chain ends, then the rest of the longer
+// one -- so that the low tiles, where children fill the lowest free slots and
+// the live agents gather, are all in the first round of resident workgroups;
+// within each chain blocks still run in increasing order.
+struct Block {
     int s;            // species
-    uint32_t tile;    // tile within the species' scan chain
+    uint32_t q;       // block within the species' scan chain
+    uint32_t words;   // bitmask words, 64 per tile
+    int64_t word0;    // the first of them
     int64_t base;     // first slot
 };
 
-__device__ __forceinline__ TileRef tile_of(const StepArgs& a) {
-    const uint32_t m = a.tiles[0] < a.tiles[1] ? a.tiles[0] : a.tiles[1];
-    const uint32_t b = blockIdx.x;
-    TileRef r;
-    if (b < 2 * m) {
-        r.s = int(b & 1u);
-        r.tile = b >> 1;
+__host__ __device__ __forceinline__ uint32_t blocks_of(uint32_t tiles) {
+    return tiles <= kSingleTiles
+               ? tiles
+               : kSingleTiles + (tiles - kSingleTiles + kTilesPerBlock - 1) / kTilesPerBlock;
+}
+
+__device__ __forceinline__ uint32_t first_tile(uint32_t q) {
+    return q < kSingleTiles ? q : kSingleTiles + (q - kSingleTiles) * kTilesPerBlock;
+}
+
+__device__ __forceinline__ Block block_of(const StepArgs& a) {
+    const uint32_t m = a.blocks[0] < a.blocks[1] ? a.blocks[0] : a.blocks[1];
+    const uint32_t n = blockIdx.x;
+    Block b;
+    if (n < 2 * m) {
+        b.s = int(n & 1u);
+        b.q = n >> 1;
     } else {
-        r.s = a.tiles[0] > a.tiles[1] ? 0 : 1;
-        r.tile = m + (b - 2 * m);
+        b.s = a.blocks[0] > a.blocks[1] ? 0 : 1;
+        b.q = m + (n - 2 * m);
     }
-    r.base = int64_t(r.tile) * kTile;
-    return r;
+    const uint32_t t = first_tile(b.q), left = (b.s ? a.tiles[1] : a.tiles[0]) - t;
+    b.words = kOwners * (b.q < kSingleTiles ? 1u : (left < kTilesPerBlock ? left : kTilesPerBlock));
+    b.word0 = int64_t(t) * kOwners;
+    b.base = int64_t(t) * kTile;
+    return b;
 }
 
-// Block-wide list, in slot order, of the tile offsets of the set bits of each
-// thread's mask (thread t owns offsets 32 t .. 32 t + 31).  Returns the list
-// length (the same in every thread); *first receives the list index of this
-// thread's first set bit.  Contains three block barriers; the list is
-// complete when it returns.
-template <int WAVES = kWaves>
-__device__ __forceinline__ uint32_t block_list(uint32_t mask, uint16_t* list, uint32_t* wl,
-                                               uint32_t* first) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t c = __popc(mask);
-    uint32_t excl = 0, wtot = 0;
+// Blocks of species s from which on no agent is alive.
+__device__ __forceinline__ uint32_t mark_of(const StepArgs& a, int s) {
+    uint64_t m = 0;
 #pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        const uint64_t bal = __ballot((c >> b) & 1u);
-        excl += lane_rank(bal) << b;
-        wtot += static_cast<uint32_t>(__popcll(bal)) << b;
+    for (int l = 0; l < kMarkLanes; ++l) {
+        const uint64_t v = a.mark_rd[s * kMarkLanes + l];
+        m = v > m ? v : m;
     }
-    __syncthreads();   // earlier readers of wl and list are done
-    if (lane == 0) wl[wave] = wtot;
-    __syncthreads();
-    uint32_t before = 0, total = 0;
+    return uint32_t(m);
+}
+
+// The arrays from slot `base` on.
+__device__ __forceinline__ Species species_at(const Species& s, int64_t base) {
+    return Species{s.x + base, s.y + base, s.e + base, s.alive + base};
+}
+
+// Slot (within the block) k of this thread in the tile whose words start at w0
+// of the block, and whether its bit is set.
+__device__ __forceinline__ uint32_t slot_in_block(uint32_t w0, int k) {
+    return w0 * 32u + uint32_t(k) * kThreads + threadIdx.x;
+}
+
+__device__ __forceinline__ uint32_t live_of(const StepArgs& a, const Block& b, uint32_t w0) {
+    uint32_t word[kPerThread], live = 0;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-        const uint32_t v = wl[w];
-        before += w < wave ? v : 0u;
-        total += v;
-    }
-    uint32_t r = before + excl;
-    *first = r;
-    for (uint32_t m = mask; m; m &= m - 1u) list[r++] = uint16_t(threadIdx.x * 32u + (__ffs(m) - 1));
-    __syncthreads();
-    return __builtin_amdgcn_readfirstlane(total);
+    for (int k = 0; k < kPerThread; ++k)
+        word[k] = a.bits[b.s][b.word0 + (slot_in_block(w0, k) >> 5)];
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) live |= ((word[k] >> (threadIdx.x & 31)) & 1u) << k;
+    return live;
 }
 
-// A list entry is a 13-bit tile offset; a kernel may tag it with a 2-bit
-// flag in bits 14-15 once it has read the offset.
-__device__ __forceinline__ void tag(uint16_t* list, uint32_t j, uint32_t f) {
-    list[j] = uint16_t((list[j] & 0x1FFFu) | (f << 14));
+// Bit `slot` of a block's masks in LDS.
+__device__ __forceinline__ void set_bit(uint32_t* masks, uint32_t slot) {
+    atomicOr(&masks[slot >> 5], 1u << (slot & 31u));
 }
 
-// The bits of `mask` whose list entries (in slot order from `first`) carry
-// flag value v.
-__device__ __forceinline__ uint32_t flagged(uint32_t mask, uint32_t first, const uint16_t* list,
-                                            uint32_t v) {
-    uint32_t out = 0, r = first;
-    for (uint32_t m = mask; m; m &= m - 1u, ++r)
-        if ((list[r] >> 14) == v) out |= m & (0u - m);
-    return out;
+// The slots of word w (of the block) below the capacity.
+__device__ __forceinline__ uint32_t word_in_cap(const Block& b, uint32_t w, int64_t cap) {
+    const int64_t left = w < b.words ? cap - b.base - int64_t(w) * 32 : 0;
+    return left <= 0 ? 0u : low_bits(left < 32 ? uint32_t(left) : 32u);
 }
 
 __device__ __forceinline__ bool grown(int32_t ready, uint32_t step) {
@@ -342,7 +354,6 @@ __device__ __forceinline__ bool grown(int32_t ready, uint32_t step) {
 // Tile-local part of a rank: this thread's exclusive rank of its count c
 // (0 <= c < 64) in thread order, and the tile total.  lds holds one word per
 // wave.  Two block barriers.
-template <int WAVES>
 __device__ __forceinline__ uint32_t rank_block(uint32_t c, uint32_t* thread_excl, uint32_t* lds) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t excl = 0, wtot = 0;
@@ -357,7 +368,7 @@ __device__ __forceinline__ uint32_t rank_block(uint32_t c, uint32_t* thread_excl
     __syncthreads();
     uint32_t before = 0, total = 0;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
+    for (int w = 0; w < kThreadWaves; ++w) {
         const uint32_t v = lds[w];
         before += w < wave ? v : 0u;
         total += v;
@@ -418,80 +429,75 @@ __device__ __forceinline__ void hier_prefix2(uint64_t* chain_a, uint64_t* chain_
 }
 
 // ------------------------------------------------------------------ K1
-template <int H>
-__global__ __launch_bounds__(kBlock * H) void k_move_claim(StepArgs a) {
-    constexpr int kThreads = kBlock * H;
-    __shared__ uint16_t list[kTile];
-    __shared__ uint32_t wl[kWaves * H];
-    __shared__ uint32_t lds[kWaves * H];
-    const TileRef t = tile_of(a);
-    const int s = t.s;
-    const Species sp = a.sp[s];
+__global__ __launch_bounds__(kThreads) void k_move_claim(StepArgs a) {
+    __shared__ uint32_t lds[kThreadWaves];
+    const Block b = block_of(a);
+    const int s = b.s;
     // the previous step's statistics, folded by the last workgroup (a tile
     // past the live agents, so it has time to spare); this step adds to the
     // other half of the accumulators
     if (a.fold_row && blockIdx.x == gridDim.x - 1)
         fold_stats(a.acc + (kHalfLanes - a.acc_par), a.fold_row);
-    // the next step's tile marks start from zero (K3 raises them)
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 2) a.mark_wr[threadIdx.x] = 0;
-    if (t.tile >= uint32_t(a.mark_rd[s])) return;   // past the last live tile
-    const uint32_t mask =
-        threadIdx.x < kBlock ? a.bits[s][int64_t(t.tile) * kBlock + threadIdx.x] : 0u;
-    if (!__syncthreads_or(mask != 0u)) return;   // no live agent in the tile
-    uint32_t first;
-    const uint32_t n = block_list<kWaves * H>(mask, list, wl, &first);
+    // the next step's marks start from zero (K3 raises them)
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 2 * kMarkLanes) a.mark_wr[threadIdx.x] = 0;
+    if (b.q >= mark_of(a, s)) return;   // past the last live agent
+    const Species sp = species_at(a.sp[s], b.base);
+    const uint32_t base = uint32_t(b.base);
     const uint64_t skey = stream_key(a.seed, a.step);
-    for (uint32_t j0 = 0; j0 < n; j0 += kInFlight * kThreads) {
-        int64_t i[kInFlight], c[kInFlight];
-        int32_t x[kInFlight], y[kInFlight];
-        bool on[kInFlight];
+    uint32_t count = 0;
+    for (uint32_t w0 = 0; w0 < b.words; w0 += kOwners) {
+        const uint32_t live = live_of(a, b, w0);
+        if (__ballot(live != 0u) == 0) continue;   // (the wave's)
+        count += __popc(live);
+        uint32_t i[kPerThread];
+        int32_t c[kPerThread];
+        int32_t x[kPerThread], y[kPerThread], e[kPerThread];
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            const uint32_t j = j0 + uint32_t(q * kThreads) + threadIdx.x;
-            on[q] = j < n;
-            i[q] = t.base + (on[q] ? list[j] : 0);
-            if (on[q]) {
-                x[q] = sp.x[i[q]];
-                y[q] = sp.y[i[q]];
-            }
+        for (int k = 0; k < kPerThread; ++k) {
+            // (a dead slot's loads go to the block's first: no branch around them)
+            i[k] = (live >> k) & 1u ? slot_in_block(w0, k) : 0u;
+            x[k] = sp.x[i[k]];
+            y[k] = sp.y[i[k]];
+            e[k] = sp.e[i[k]];
         }
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            if (!on[q]) continue;
-            const uint32_t d = draw(skey, uint32_t(i[q]), s ? kWolfMove : kSheepMove) >> 29;
-            x[q] = wrap_step(x[q], int32_t((kDxPacked >> (2 * d)) & 3u) - 1, a.W);
-            y[q] = wrap_step(y[q], int32_t((kDyPacked >> (2 * d)) & 3u) - 1, a.H);
-            sp.x[i[q]] = x[q];
-            sp.y[i[q]] = y[q];
-            sp.e[i[q]] -= 1;
-            c[q] = cell_of(x[q], y[q], a.W, a.H);
+        for (int k = 0; k < kPerThread; ++k) {
+            c[k] = -1;
+            if (!((live >> k) & 1u)) continue;
+            const uint32_t d = draw(skey, base + i[k], s ? kWolfMove : kSheepMove) >> 29;
+            x[k] = wrap_step(x[k], int32_t((kDxPacked >> (2 * d)) & 3u) - 1, a.W);
+            y[k] = wrap_step(y[k], int32_t((kDyPacked >> (2 * d)) & 3u) - 1, a.H);
+            sp.x[i[k]] = x[k];
+            sp.y[i[k]] = y[k];
+            sp.e[i[k]] = e[k] - 1;
+            c[k] = int32_t(cell_of(x[k], y[k], a.W, a.H));
         }
+        bool grows[kPerThread];
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            if (!on[q] || c[q] < 0) continue;
+        for (int k = 0; k < kPerThread; ++k)
+            grows[k] = s == 0 && c[k] >= 0 && grown(a.ready[c[k]], a.step);
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            if (c[k] < 0) continue;
+            uint64_t* const cell = a.claims + 3 * int64_t(c[k]);
+            if (grows[k])
+                atomicMin(reinterpret_cast<unsigned long long*>(cell),
+                          (unsigned long long)claim_key(a, skey, base + i[k], kSheepGrassKey));
             if (a.multi) {
                 // push slot i onto the list of its cell; the list ends at a word
                 // of an earlier step (or all-ones)
-                if (s == 0 && grown(a.ready[c[q]], a.step))
-                    atomicMin(reinterpret_cast<unsigned long long*>(a.claims + 3 * c[q]),
-                              (unsigned long long)claim_key(a, skey, i[q], kSheepGrassKey));
-                uint64_t* head = a.claims + 3 * c[q] + (s ? 2 : 1);
-                const uint64_t prev = atomicExch(reinterpret_cast<unsigned long long*>(head),
-                                                 (unsigned long long)(a.tag_hi | uint64_t(i[q])));
-                a.blist[s][i[q]] = head_slot(a, prev);
-            } else if (s == 0) {
-                if (grown(a.ready[c[q]], a.step))
-                    atomicMin(reinterpret_cast<unsigned long long*>(a.claims + 3 * c[q]),
-                              (unsigned long long)claim_key(a, skey, i[q], kSheepGrassKey));
-                atomicMin(reinterpret_cast<unsigned long long*>(a.claims + 3 * c[q] + 1),
-                          (unsigned long long)claim_key(a, skey, i[q], kSheepPreyKey));
+                const uint64_t prev =
+                    atomicExch(reinterpret_cast<unsigned long long*>(cell + (s ? 2 : 1)),
+                               (unsigned long long)(a.tag_hi | uint64_t(base + i[k])));
+                a.blist[s][base + i[k]] = head_slot(a, prev);
             } else {
-                atomicMin(reinterpret_cast<unsigned long long*>(a.claims + 3 * c[q] + 2),
-                          (unsigned long long)claim_key(a, skey, i[q], kWolfEatKey));
+                atomicMin(reinterpret_cast<unsigned long long*>(cell + (s ? 2 : 1)),
+                          (unsigned long long)claim_key(a, skey, base + i[k],
+                                                        s ? kWolfEatKey : kSheepPreyKey));
             }
         }
     }
-    if (a.stats) block_add(__popc(mask), a.acc + a.acc_par, s ? kLiveW : kLiveS, lds);
+    if (a.stats) block_add(count, a.acc + a.acc_par, s ? kLiveW : kLiveS, lds);
 }
 
 // K1b (multi_prey): wolf j of cell c takes rank r among the wolves of c (eat
@@ -525,109 +531,111 @@ __global__ __launch_bounds__(kBlock) void k_prey_match(StepArgs a) {
 }
 
 // ------------------------------------------------------------------ K2
-// H x kBlock threads: threads below kBlock own the tile's bitmask words, all
-// of them take part in the tile's list of agents (as in K1 and K3).
-template <int H>
-__global__ __launch_bounds__(kBlock * H) void k_eat_breeders(StepArgs a) {
-    constexpr int kThreads = kBlock * H;
-    __shared__ uint16_t list[kTile];
-    __shared__ uint32_t wl[kWaves * H];
-    __shared__ uint32_t lds[2 * kWaves * H + 1];
-    const TileRef t = tile_of(a);
-    const int s = t.s;
-    const Species sp = a.sp[s];
+__global__ __launch_bounds__(kThreads) void k_eat_breeders(StepArgs a) {
+    __shared__ uint32_t breeds[kBlockWords], gone[kBlockWords];
+    __shared__ uint32_t lds[2 * kThreadWaves + 1];
     const uint32_t epoch = read_epoch(a.epoch);
+    const Block b = block_of(a);
+    const int s = b.s;
     const int64_t cap = s ? a.cap_w : a.cap_s;
-    // tiles at or past the mark hold no live agent: no breeder, every slot
-    // free; they take no part in the scans (no tile below them reads their
+    // blocks at or past the mark hold no live agent: no breeder, every slot
+    // free; they take no part in the scans (no block below them reads their
     // words), and K3 derives their free-slot prefixes from the totals
-    const uint32_t mark = uint32_t(a.mark_rd[s]);
-    const uint32_t last = mark > 0 ? mark - 1 : 0;   // the tile that writes the totals
-    const int64_t past = cap - int64_t(mark) * kTile > 0 ? cap - int64_t(mark) * kTile : 0;
-    if (t.tile >= mark) {
-        if (mark == 0 && t.tile == 0 && threadIdx.x == 0) {
+    const uint32_t mark = mark_of(a, s);
+    if (b.q >= mark) {
+        if (mark == 0 && b.q == 0 && threadIdx.x == 0) {
             *a.d_nb[s] = 0;
             *a.d_nf[s] = cap;
         }
         return;
     }
-    const uint32_t mask =
-        threadIdx.x < kBlock ? a.bits[s][int64_t(t.tile) * kBlock + threadIdx.x] : 0u;
-    // (a tile with no live agent skips the list: it still takes part in both scans)
-    uint32_t first = 0, n = 0;
-    if (__syncthreads_or(mask != 0u)) n = block_list<kWaves * H>(mask, list, wl, &first);
+    const Species sp = species_at(a.sp[s], b.base);
+    const uint32_t base = uint32_t(b.base);
+    breeds[threadIdx.x] = 0;
+    gone[threadIdx.x] = 0;
+    __syncthreads();
     const uint64_t skey = stream_key(a.seed, a.step);
     uint32_t grass_eaten = 0, sheep_eaten = 0;
-    for (uint32_t j0 = 0; j0 < n; j0 += kInFlight * kThreads) {
-        int64_t i[kInFlight], c[kInFlight];
-        int32_t e[kInFlight];
-        bool on[kInFlight], eaten[kInFlight];
+    for (uint32_t w0 = 0; w0 < b.words; w0 += kOwners) {
+        const uint32_t live = live_of(a, b, w0);
+        if (__ballot(live != 0u) == 0) continue;   // (the wave's)
+        uint32_t i[kPerThread];
+        int32_t c[kPerThread], e[kPerThread];
+        uint32_t eaten = 0;
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            const uint32_t j = j0 + uint32_t(q * kThreads) + threadIdx.x;
-            on[q] = j < n;
-            i[q] = t.base + (on[q] ? list[j] : 0);
-            c[q] = on[q] ? cell_of(sp.x[i[q]], sp.y[i[q]], a.W, a.H) : -1;
-            e[q] = on[q] ? sp.e[i[q]] : 0;
-            eaten[q] = s == 0 && a.multi && on[q] && sp.alive[i[q]] == 2;
+        for (int k = 0; k < kPerThread; ++k) {
+            const bool on = (live >> k) & 1u;
+            i[k] = on ? slot_in_block(w0, k) : 0u;
+            const int32_t x = sp.x[i[k]], y = sp.y[i[k]];
+            e[k] = sp.e[i[k]];
+            c[k] = on ? int32_t(cell_of(x, y, a.W, a.H)) : -1;
+            if (a.multi && s == 0 && on && sp.alive[i[k]] == 2) eaten |= 1u << k;
+        }
+        uint64_t mine[kPerThread], other[kPerThread];
+#pragma unroll
+        for (int k = 0; k < kPerThread; ++k) {
+            // sheep: the grass word and the eater's; wolves: the eater's and the prey's
+            const uint64_t* cell = a.claims + 3 * int64_t(c[k] < 0 ? 0 : c[k]);
+            mine[k] = cell[s ? 2 : 0];
+            other[k] = cell[s ? 1 : 2];
         }
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            if (!on[q] || c[q] < 0) continue;
+        for (int k = 0; k < kPerThread; ++k) {
+            if (c[k] < 0) continue;
             if (s == 0) {
-                if (a.claims[3 * c[q]] == claim_key(a, skey, i[q], kSheepGrassKey)) {
-                    e[q] += a.gain_s;
-                    sp.e[i[q]] = e[q];
-                    a.ready[c[q]] = int32_t(a.step + uint32_t(a.R));
+                if (mine[k] == claim_key(a, skey, base + i[k], kSheepGrassKey)) {
+                    e[k] += a.gain_s;
+                    sp.e[i[k]] = e[k];
+                    a.ready[c[k]] = int32_t(a.step + uint32_t(a.R));
                     ++grass_eaten;
                 }
-                if (!a.multi)
-                    eaten[q] = claimed(a, a.claims[3 * c[q] + 2]) &&
-                               a.claims[3 * c[q] + 1] == claim_key(a, skey, i[q], kSheepPreyKey);
-                if (eaten[q]) {
-                    if (!a.multi) sp.alive[i[q]] = 2;
-                    ++sheep_eaten;
+                if (!a.multi && claimed(a, other[k]) &&
+                    a.claims[3 * int64_t(c[k]) + 1] == claim_key(a, skey, base + i[k], kSheepPreyKey)) {
+                    sp.alive[i[k]] = 2;
+                    eaten |= 1u << k;
                 }
-            } else if (!a.multi && claimed(a, a.claims[3 * c[q] + 1]) &&
-                       a.claims[3 * c[q] + 2] == claim_key(a, skey, i[q], kWolfEatKey)) {
+            } else if (!a.multi && claimed(a, other[k]) &&
+                       mine[k] == claim_key(a, skey, base + i[k], kWolfEatKey)) {
                 // (multi_prey: K1b has already added the gain)
-                e[q] += a.gain_w;
-                sp.e[i[q]] = e[q];
+                e[k] += a.gain_w;
+                sp.e[i[k]] = e[k];
             }
         }
+        sheep_eaten += __popc(eaten);
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            if (!on[q]) continue;
-            const bool br = !eaten[q] && e[q] > 0 &&
-                            draw(skey, uint32_t(i[q]), s ? kWolfBreed : kSheepBreed) <
-                                (s ? a.T_w : a.T_s);
-            // 1: breeder, 2: eaten (its slot is free for this step's births)
-            tag(list, j0 + uint32_t(q * kThreads) + threadIdx.x, br ? 1u : (eaten[q] ? 2u : 0u));
+        for (int k = 0; k < kPerThread; ++k) {
+            if (!((live >> k) & 1u)) continue;
+            if ((eaten >> k) & 1u)
+                set_bit(gone, slot_in_block(w0, k));   // its slot is free for this step's births
+            else if (e[k] > 0 && draw(skey, base + i[k], s ? kWolfBreed : kSheepBreed) <
+                                     (s ? a.T_w : a.T_s))
+                set_bit(breeds, slot_in_block(w0, k));
         }
     }
     __syncthreads();
     // breeders (compacted in slot order for K3) and the slots free for this
-    // step's births (empty, or eaten this step), ranked over two chains at once
-    const bool owner = threadIdx.x < kBlock;
-    const uint32_t bm = flagged(mask, first, list, 1);
-    const uint32_t eaten_m = flagged(mask, first, list, 2);
-    const int64_t lane0 = t.base + int64_t(threadIdx.x) * 32;
-    const uint32_t in_cap = !owner || lane0 >= cap ? 0u
-                          : (cap - lane0 >= 32 ? ~0u : (1u << (cap - lane0)) - 1u);
-    const uint32_t free_m = ((~mask) & in_cap) | eaten_m;
+    // step's births (empty, or eaten this step), ranked over two chains at
+    // once; a thread per bitmask word of the block
+    const uint32_t w = threadIdx.x;
+    const uint32_t bm = breeds[w];
+    const uint32_t mask = w < b.words ? a.bits[s][b.word0 + w] : 0u;
+    const uint32_t free_m = (~mask & word_in_cap(b, w, cap)) | gone[w];
     uint32_t r0, rf;
-    const uint32_t total = rank_block<kWaves * H>(__popc(bm), &r0, lds);
-    const uint32_t total_f = rank_block<kWaves * H>(__popc(free_m), &rf, lds + kWaves * H);
-    uint32_t tile_excl, free_excl;
-    hier_prefix2(a.status + a.chain_off[s], a.status + a.fchain_off[s], a.status - 1, t.tile,
-                 a.tiles[s], epoch, total, total_f, lds, &tile_excl, &free_excl);
-    uint32_t r = tile_excl + r0;
+    const uint32_t total = rank_block(__popc(bm), &r0, lds);
+    const uint32_t total_f = rank_block(__popc(free_m), &rf, lds + kThreadWaves);
+    uint32_t excl, free_excl;
+    hier_prefix2(a.status + a.chain_off[s], a.status + a.fchain_off[s], a.status - 1, b.q,
+                 a.blocks[s], epoch, total, total_f, lds, &excl, &free_excl);
+    uint32_t r = excl + r0;
     for (uint32_t m = bm; m; m &= m - 1u)
-        a.blist[s][r++] = int32_t(t.base + threadIdx.x * 32u + (__ffs(m) - 1));
-    if (threadIdx.x == 0) a.free_pre[s][t.tile] = int32_t(free_excl);
-    if (t.tile == last && threadIdx.x == 0) {
-        *a.d_nb[s] = int64_t(tile_excl) + total;
-        *a.d_nf[s] = int64_t(free_excl) + total_f + past;
+        a.blist[s][r++] = int32_t(b.base + w * 32u + (__ffs(m) - 1));
+    if (threadIdx.x == 0) {
+        a.free_pre[s][b.q] = int32_t(free_excl);
+        if (b.q == mark - 1) {
+            const int64_t past = cap - int64_t(first_tile(mark)) * kTile;
+            *a.d_nb[s] = int64_t(excl) + total;
+            *a.d_nf[s] = int64_t(free_excl) + total_f + (past > 0 ? past : 0);
+        }
     }
     if (a.stats && s == 0) {
         block_add(grass_eaten, a.acc + a.acc_par, kGrassEaten, lds);
@@ -636,19 +644,13 @@ __global__ __launch_bounds__(kBlock * H) void k_eat_breeders(StepArgs a) {
 }
 
 // ------------------------------------------------------------------ K3
-template <int H>
-__global__ __launch_bounds__(kBlock * H) void k_breed_die(StepArgs a) {
-    constexpr int kThreads = kBlock * H;
-    __shared__ uint16_t list[kTile];
-    __shared__ uint32_t wl[kWaves * H];
-    __shared__ uint32_t lds[kWaves * H + 1];
-    const bool owner = threadIdx.x < kBlock;      // owns bitmask word threadIdx.x
-    const TileRef t = tile_of(a);
-    const int s = t.s;
-    const Species sp = a.sp[s];
+__global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
+    __shared__ uint16_t list[kTile * kTilesPerBlock];
+    __shared__ uint32_t gone[kBlockWords], starves[kBlockWords];
+    __shared__ uint32_t lds[kThreadWaves + 1];
+    const Block b = block_of(a);
+    const int s = b.s;
     const int64_t cap = s ? a.cap_w : a.cap_s;
-    const int64_t wi = int64_t(t.tile) * kBlock + threadIdx.x;
-    const uint32_t mask = owner ? a.bits[s][wi] : 0u;   // live at K1, eaten sheep included
     // at the end of a tag period this workgroup's slice of the claim tables is
     // re-armed for the next step (K2, the last reader, has finished): whole
     // lines, streamed
@@ -658,113 +660,87 @@ __global__ __launch_bounds__(kBlock * H) void k_breed_die(StepArgs a) {
         const int64_t hi = lo + per < words ? lo + per : words;
         for (int64_t w = lo + threadIdx.x; w < hi; w += kThreads) a.claims[w] = kNoClaim;
     }
-    const int64_t nb = *a.d_nb[s];
-    if (a.stats && t.tile == a.tiles[s] - 1 && threadIdx.x == 0) {
-        const int64_t nfree = *a.d_nf[s];
+    const int64_t nb = *a.d_nb[s], nfree = *a.d_nf[s];
+    if (a.stats && b.q == a.blocks[s] - 1 && threadIdx.x == 0)
         a.stats[s ? kBirthsW : kBirthsS] = nfree < nb ? nfree : nb;
-    }
-    // the tile's free-slot prefix: from K2's scan below the mark; past it every
-    // slot of every tile is free
-    const uint32_t mark = uint32_t(a.mark_rd[s]);
+    // the block's free-slot prefix: from K2's scan below the mark; past it every
+    // slot of every block is free
+    const uint32_t mark = mark_of(a, s);
     int64_t pre;
-    if (t.tile < mark) {
-        pre = a.free_pre[s][t.tile];
+    if (b.q < mark) {
+        pre = a.free_pre[s][b.q];
     } else {
-        const int64_t past = cap - int64_t(mark) * kTile > 0 ? cap - int64_t(mark) * kTile : 0;
-        pre = (*a.d_nf[s] - past) + int64_t(t.tile - mark) * kTile;
+        const int64_t first = int64_t(first_tile(mark)) * kTile;
+        pre = nfree - (cap - first > 0 ? cap - first : 0) + (b.base - first);
+        // with no live agent and no birth (its free slots rank past the
+        // breeders) there is nothing to do
+        if (pre >= nb) return;
     }
-    // a tile with no live agent and no birth (its free slots rank past the
-    // breeders) has nothing to do
-    const bool births_here = pre < nb;
-    if (t.tile >= mark && !births_here) return;
-    if (!__syncthreads_or(mask != 0u) && !births_here) return;
-    uint32_t first;
-    const uint32_t n = block_list<kWaves * H>(mask, list, wl, &first);
+    const Species sp = a.sp[s], here = species_at(sp, b.base);
+    gone[threadIdx.x] = 0;
+    starves[threadIdx.x] = 0;
+    __syncthreads();
     // eaten sheep become free slots, starving agents die
     uint32_t starved = 0;
-    for (uint32_t j0 = 0; j0 < n; j0 += kInFlight * kThreads) {
-        int64_t i[kInFlight];
-        int32_t al[kInFlight], e[kInFlight];
-        bool on[kInFlight];
+    for (uint32_t w0 = 0; w0 < b.words && b.q < mark; w0 += kOwners) {
+        const uint32_t live = live_of(a, b, w0);
+        if (__ballot(live != 0u) == 0) continue;   // (the wave's)
+        uint32_t i[kPerThread];
+        int32_t al[kPerThread], e[kPerThread];
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            const uint32_t j = j0 + uint32_t(q * kThreads) + threadIdx.x;
-            on[q] = j < n;
-            i[q] = t.base + (on[q] ? list[j] : 0);
-            al[q] = on[q] ? sp.alive[i[q]] : 0;
-            e[q] = on[q] ? sp.e[i[q]] : 0;
+        for (int k = 0; k < kPerThread; ++k) {
+            i[k] = (live >> k) & 1u ? slot_in_block(w0, k) : 0u;
+            al[k] = here.alive[i[k]];
+            e[k] = here.e[i[k]];
         }
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            if (!on[q]) continue;
-            uint32_t f = 0;
-            if (al[q] == 2) {
-                f = 1;                      // eaten: a free slot for this step's births
-                sp.alive[i[q]] = 0;
-            } else if (e[q] < 0) {
+        for (int k = 0; k < kPerThread; ++k) {
+            if (!((live >> k) & 1u)) continue;
+            if (al[k] == 2) {               // eaten: a free slot for this step's births
+                set_bit(gone, slot_in_block(w0, k));
+                here.alive[i[k]] = 0;
+            } else if (e[k] < 0) {
                 // a breeder's energy stays positive, so no slot read by a child dies here
-                f = 2;
-                sp.alive[i[q]] = 0;
+                set_bit(starves, slot_in_block(w0, k));
+                here.alive[i[k]] = 0;
                 ++starved;
             }
-            tag(list, j0 + uint32_t(q * kThreads) + threadIdx.x, f);
         }
     }
     __syncthreads();
-    const uint32_t eaten_m = flagged(mask, first, list, 1);
-    const uint32_t starved_m = flagged(mask, first, list, 2);
-    const int64_t lane0 = t.base + int64_t(threadIdx.x) * 32;
-    const uint32_t in_cap = !owner || lane0 >= cap ? 0u
-                          : (cap - lane0 >= 32 ? ~0u : (1u << (cap - lane0)) - 1u);
-    const uint32_t free_m = ((~mask) & in_cap) | eaten_m;
-    // (the same free slots K2 ranked: its chain gave this tile's prefix)
+    const uint32_t w = threadIdx.x;
+    const uint32_t mask = w < b.words ? a.bits[s][b.word0 + w] : 0u;   // live at K1
+    const uint32_t free_m = (~mask & word_in_cap(b, w, cap)) | gone[w];
+    // (the same free slots K2 ranked: its chain gave this block's prefix)
     uint32_t r0;
-    const uint32_t total = rank_block<kWaves * H>(__popc(free_m), &r0, lds);
-    const uint32_t tile_excl = uint32_t(pre);
-    const int64_t room = nb - int64_t(tile_excl);
+    const uint32_t total = rank_block(__popc(free_m), &r0, lds);
+    const uint32_t excl = uint32_t(pre);
+    const int64_t room = nb - int64_t(excl);
     const uint32_t births = room <= 0 ? 0u : (room < int64_t(total) ? uint32_t(room) : total);
-    // this lane's free slots of tile rank < births receive children
-    const uint32_t mine = births > r0 ? (births - r0 < 32u ? births - r0 : 32u) : 0u;
-    uint32_t born_m = 0;
-    {
-        uint32_t m = free_m;
-        for (uint32_t k = 0; k < mine && m; ++k, m &= m - 1u) born_m |= m & (0u - m);
+    // this word's free slots of block rank < births receive children; they are
+    // the block's first ones, so their rank is their place in the list
+    uint32_t born_m = 0, r = r0;
+    for (uint32_t m = free_m; m && r < births; m &= m - 1u, ++r) {
+        born_m |= m & (0u - m);
+        list[r] = uint16_t(w * 32u + (__ffs(m) - 1));
     }
-    const uint32_t live_m = (mask & ~eaten_m & ~starved_m) | born_m;
-    if (owner) a.bits[s][wi] = live_m;
-    // the next step's mark: past the last tile left with a live agent
+    const uint32_t live_m = (mask & ~gone[w] & ~starves[w]) | born_m;
+    if (w < b.words && live_m != mask) a.bits[s][b.word0 + w] = live_m;
+    // the next step's mark: past the last block left with a live agent
     if (__syncthreads_or(live_m != 0u) && threadIdx.x == 0)
-        atomicMax(reinterpret_cast<unsigned long long*>(a.mark_wr + s),
-                  (unsigned long long)(t.tile + 1));
-    // the children, spread over the block: list the free slots that receive one
-    uint32_t bfirst;
-    const uint32_t nborn = block_list<kWaves * H>(born_m, list, wl, &bfirst);
-    for (uint32_t j0 = 0; j0 < nborn; j0 += kInFlight * kThreads) {
-        int64_t ci[kInFlight], p[kInFlight];
-        int32_t px[kInFlight], py[kInFlight], pe[kInFlight];
-        bool on[kInFlight];
-#pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            const uint32_t j = j0 + uint32_t(q * kThreads) + threadIdx.x;
-            on[q] = j < nborn;
-            ci[q] = t.base + (on[q] ? list[j] : 0);
-            p[q] = on[q] ? a.blist[s][tile_excl + j] : 0;
-            if (on[q]) {
-                px[q] = sp.x[p[q]];
-                py[q] = sp.y[p[q]];
-                pe[q] = sp.e[p[q]];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kInFlight; ++q) {
-            if (!on[q]) continue;
-            const int32_t ec = pe[q] >> 1;
-            sp.x[ci[q]] = px[q];
-            sp.y[ci[q]] = py[q];
-            sp.e[ci[q]] = ec;
-            sp.e[p[q]] = pe[q] - ec;
-            sp.alive[ci[q]] = 1;
-        }
+        atomicMax(reinterpret_cast<unsigned long long*>(a.mark_wr + s * kMarkLanes +
+                                                        (b.q & (kMarkLanes - 1))),
+                  (unsigned long long)(b.q + 1));
+    // the children, spread over the workgroup
+    for (uint32_t j = threadIdx.x; j < births; j += kThreads) {
+        const int64_t ci = b.base + list[j], p = a.blist[s][excl + j];
+        const int32_t px = sp.x[p], py = sp.y[p], pe = sp.e[p];
+        const int32_t ec = pe >> 1;
+        sp.x[ci] = px;
+        sp.y[ci] = py;
+        sp.e[ci] = ec;
+        sp.e[p] = pe - ec;
+        sp.alive[ci] = 1;
     }
     if (a.stats) block_add(starved, a.acc + a.acc_par, s ? kStarvedW : kStarvedS, lds);
 }
@@ -775,7 +751,8 @@ __global__ __launch_bounds__(kBlock * H) void k_breed_die(StepArgs a) {
 __global__ __launch_bounds__(kBlock) void k_call_begin(StepArgs a, int64_t G, int64_t words_s,
                                                        int64_t words_w) {
     const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-    if (k < 2) a.mark_rd[k] = a.tiles[k];   // the first step visits every tile
+    // the first step visits every block
+    if (k < 2 * kMarkLanes) a.mark_rd[k] = a.blocks[k / kMarkLanes];
     if (k < G) {
         a.ready[k] = int32_t(a.step + uint32_t(a.ready[k]));
         a.claims[3 * k] = kNoClaim;
@@ -937,26 +914,28 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
     a.d_nf[1] = reinterpret_cast<int64_t*>(w.hdr + kHdrFreeB);
     a.tiles[0] = static_cast<uint32_t>(tiles_for(p->cap_s, kTile));
     a.tiles[1] = static_cast<uint32_t>(tiles_for(p->cap_w, kTile));
+    a.blocks[0] = blocks_of(a.tiles[0]);
+    a.blocks[1] = blocks_of(a.tiles[1]);
     // status words: the breeder chains of both species, then their free-slot
-    // chains, then the per-tile free prefixes (int32) K2 leaves for K3; the
-    // area is sized for 512-slot tiles, 16 times the chains of 8192-slot tiles
-    const int64_t cw0 = chain_words(a.tiles[0]), cw1 = chain_words(a.tiles[1]);
+    // chains, then the per-block free prefixes (int32) K2 leaves for K3; the
+    // area is sized for 512-slot tiles, four times the chains of 2048-slot tiles
+    const int64_t cw0 = chain_words(a.blocks[0]), cw1 = chain_words(a.blocks[1]);
     a.chain_off[0] = 0;
     a.chain_off[1] = static_cast<uint32_t>(cw0);
     a.fchain_off[0] = static_cast<uint32_t>(cw0 + cw1);
     a.fchain_off[1] = static_cast<uint32_t>(2 * cw0 + cw1);
-    const int64_t pre_words = 2 * (cw0 + cw1) + (int64_t(a.tiles[0]) + a.tiles[1] + 1) / 2;
+    const int64_t pre_words = 2 * (cw0 + cw1) + (int64_t(a.blocks[0]) + a.blocks[1] + 1) / 2;
     if (pre_words > status_words(p->cap_s > p->cap_w ? p->cap_s : p->cap_w))
         return fail(ABM_E_WORKSPACE, "predation_step: scan state does not fit the workspace");
     a.free_pre[0] = reinterpret_cast<int32_t*>(w.status + 2 * (cw0 + cw1));
-    a.free_pre[1] = a.free_pre[0] + a.tiles[0];
+    a.free_pre[1] = a.free_pre[0] + a.blocks[0];
     a.multi = p->multi_prey;
     a.step = s->step;
     a.stats = nullptr;
     a.acc_par = 0;
     a.fold_row = nullptr;
     a.mark_rd = w.hdr + kHdrMark;
-    a.mark_wr = w.hdr + kHdrMark + 2;
+    a.mark_wr = w.hdr + kHdrMark + 2 * kMarkLanes;
     // claim keys (claim_key): slots below 2^sb, a tag of up to kTagBits bits
     // sb + 32 bits up; a period of steps uses the tags t_max - 1 down to 1 (tag
     // 0 every step when only one tag bit is left), and its last step re-arms
@@ -971,10 +950,10 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
     a.sb = sb;
     a.tag_mask = ~uint64_t(0) << (32 + sb);
 
-    const int64_t words_s = int64_t(a.tiles[0]) * kBlock, words_w = int64_t(a.tiles[1]) * kBlock;
+    const int64_t words_s = int64_t(a.tiles[0]) * kOwners, words_w = int64_t(a.tiles[1]) * kOwners;
     int64_t edge = G > words_s ? G : words_s;
     if (words_w > edge) edge = words_w;
-    const dim3 tile_grid(a.tiles[0] + a.tiles[1]);
+    const dim3 grid(a.blocks[0] + a.blocks[1]), block(kThreads);
     // grass to ready steps, live bitmasks from alive, claim tables re-armed
     // (whatever the caller did to the state between calls)
     hipLaunchKernelGGL(k_call_begin, dim3(static_cast<uint32_t>(tiles_for(edge, kBlock))),
@@ -988,20 +967,20 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
         a.step = s->step + uint32_t(k);
         a.stats = s->stats ? s->stats + 8 * int64_t(k) : nullptr;
         a.acc_par = (k & 1) ? kHalfLanes : 0;
-        a.mark_rd = w.hdr + kHdrMark + 2 * (k & 1);
-        a.mark_wr = w.hdr + kHdrMark + 2 * ((k + 1) & 1);
+        a.mark_rd = w.hdr + kHdrMark + 2 * kMarkLanes * (k & 1);
+        a.mark_wr = w.hdr + kHdrMark + 2 * kMarkLanes * ((k + 1) & 1);
         a.fold_row = s->stats && k > 0 ? s->stats + 8 * int64_t(k - 1) : nullptr;
         const uint64_t phase = uint64_t(k) % period;
         a.tag_hi = ((t_max > 1 ? t_max - 1 : 0) - phase) << (32 + sb);
         a.rearm = phase == period - 1;
-        hipLaunchKernelGGL(k_move_claim<kHelpers>, tile_grid, dim3(kBlock * kHelpers), 0, st, a);
+        hipLaunchKernelGGL(k_move_claim, grid, block, 0, st, a);
         if (a.multi)
             hipLaunchKernelGGL(k_prey_match, dim3(static_cast<uint32_t>(tiles_for(p->cap_w, kBlock))),
                                dim3(kBlock), 0, st, a);
         rc = next_epoch(w, st, &a.epoch);
         if (rc != ABM_OK) return rc;
-        hipLaunchKernelGGL(k_eat_breeders<kHelpers>, tile_grid, dim3(kBlock * kHelpers), 0, st, a);
-        hipLaunchKernelGGL(k_breed_die<kHelpers>, tile_grid, dim3(kBlock * kHelpers), 0, st, a);
+        hipLaunchKernelGGL(k_eat_breeders, grid, block, 0, st, a);
+        hipLaunchKernelGGL(k_breed_die, grid, block, 0, st, a);
     }
     if (s->stats)
         hipLaunchKernelGGL(k_fold_stats, dim3(1), dim3(kBlock), 0, st, w.acc + a.acc_par, a.stats);

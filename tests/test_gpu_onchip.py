@@ -50,8 +50,12 @@ CASES = {
     "R 1": (dict(R=1), None),
     "R 200": (dict(R=200), None),
     "R 201": (dict(R=201), None),
-    "largest of one launch": (dict(cap_s=19520), None),
-    "one row more": (dict(cap_s=19584), None),
+    # the LDS holds 236 rows of 64 slots beside the cells; 1.5 slots a cell, and one more
+    "largest of one launch": (dict(W=170, H=170, cap_s=14080), None),
+    "one row more": (dict(W=170, H=170, cap_s=14144), None),
+    "slots a cell": (dict(cap_s=4096, cap_w=2048), None),
+    "a slot more": (dict(cap_s=4096, cap_w=2049), None),
+    "1024 slots": (dict(W=5, H=5, cap_s=900, cap_w=124, n_s0=300, n_w0=60), None),
     "full species": (dict(cap_s=400, cap_w=100, T_s=2 ** 31, T_w=2 ** 31), None),
     "no wolves": (dict(n_w0=0), None),
     "no agents": (dict(n_s0=0, n_w0=0), None),

@@ -198,3 +198,34 @@ def test_multi_prey_large_workload(abm, orc):
         assert st[t + 1][1] == live_w - sw + bw, t
         assert se <= min(live_s, live_w)
     assert abm.workspace_error(model.ws) == 0
+
+
+# 2048-slot tiles: one a workgroup up to slot 2^21, eight beyond.  Live agents only around the
+# edges of tiles, of the single tiles and of the last workgroup, so that children of the high
+# ones fill the low slots; capacities that end inside a word, a tile and a workgroup
+@pytest.mark.parametrize("multi", [0, 1])
+@pytest.mark.parametrize("cap_s", [2048, 2049, 5000, 2 ** 21, 2 ** 21 + 1, 2 ** 21 + 8 * 2048 + 70])
+def test_blocks_of_tiles(abm, orc, cap_s, multi):
+    kw = dict(W=300, H=257, cap_s=cap_s, cap_w=3000, n_s0=0, n_w0=900, T_s=2 ** 31, multi_prey=multi,
+              seed=cap_s)
+    P = orc.pred_params(**kw)
+    S = orc.predation_init(P)
+    g = np.random.default_rng(cap_s)
+    edges = [e + d for e in (0, 2048, 4096, 2 ** 21 - 2048, 2 ** 21, 2 ** 21 + 8 * 2048, cap_s)
+             for d in range(-20, 20) if 0 <= e + d < cap_s]
+    live = np.unique(edges)
+    S.sheep["alive"][live] = 1
+    S.sheep["x"][live] = g.integers(0, P.W, live.size)
+    S.sheep["y"][live] = g.integers(0, P.H, live.size)
+    S.sheep["e"][live] = g.integers(1, 40, live.size)
+    m = abm.predation_init(abm.predation_params(**kw))
+    m.grass.copy_(torch.from_numpy(S.grass))
+    for sp in ("sheep", "wolves"):
+        for f in ("x", "y", "e", "alive"):
+            getattr(m, sp)[f].copy_(torch.from_numpy(getattr(S, sp)[f]))
+    for steps in (1, 3, 12):
+        stats = torch.zeros((steps, 8), dtype=torch.int64, device="cuda")
+        m.run(steps, stats)
+        rows = orc.predation_run(P, S, steps)
+        assert stats.cpu().tolist() == [[r[k] for k in abm.STAT_NAMES] for r in rows]
+        _assert_same(m, S, f"after {steps} steps, {cap_s} slots")
