@@ -367,9 +367,10 @@ ABM_API int abm_predation_batched_init(const abm_batch* b, void* stream);
  * order (largest first balances the load).  With tune->team_size K > 1 the
  * first tune->team_models entries of order are each advanced by a team of K
  * workgroups that split the model's slots into K contiguous ranges and meet
- * at three device-wide team barriers per step; the results are the same as
- * with one workgroup per model.  Teams need 8 K resident workgroups (else
- * ABM_E_INVALID).  Claim tables of small models are kept in LDS unless
+ * at three device-wide team barriers per step, or, in runs of up to 256 steps
+ * whose workspace has room for it, all side by side by launches over the
+ * whole device; the results are the same as with one workgroup per model.
+ * Teams need 8 K resident workgroups (else ABM_E_INVALID).  Claim tables of small models are kept in LDS unless
  * tune->global_claims is set (abm_batched_lds_cells).  The workspace must hold abm_batched_workspace_bytes(max_cap,
  * n) bytes, n being the number of workgroups launched: at most the resident
  * count (or tune->workgroups), which the caller can use as the bound.

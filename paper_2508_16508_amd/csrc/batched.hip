@@ -3,7 +3,9 @@
 // paper Sec. 2 and Table 2, without requiring equal shapes).
 //
 // Each model is advanced by ONE workgroup for all of its steps, so every
-// phase boundary is a workgroup barrier instead of a kernel launch.  Workgroups
+// phase boundary is a workgroup barrier instead of a kernel launch; models too
+// large for that are advanced side by side by launches over the whole device
+// (launch_wide) or, in runs of very many steps, by teams of workgroups.  Workgroups
 // take models from a queue in a host-chosen order (largest first) until the
 // queue is empty; a model whose work is done is skipped.
 //
@@ -63,6 +65,16 @@ constexpr uint32_t kDyPacked = 0xA940u;
 // k_classify makes of the latter two.
 enum QueueWord : int { kQueueTeam = 0, kQueueSolo, kQueueChip, kChipModels, kSoloModels, kQueueWords };
 
+// Cells plus slots from which a model of one workgroup that does not fit the
+// chip joins the large ones (see launch_wide): one workgroup takes some 0.06 ms
+// a step for it and more as it grows, which the launches' total no longer hides.
+constexpr int64_t kWideSize = 1 << 15;
+// Steps of a run up to which it is done by launches: three or four are queued
+// for each of the max_steps steps, whether or not the models have that many
+// left (about 2.5 us a launch that finds nothing to do).  A recorded run keeps
+// them as graph nodes.
+constexpr int32_t kWideSteps = 256, kWideStepsRecorded = 64;
+
 struct BatchArgs {
     abm_model_desc* models;
     const int32_t* order;      // queue order of model indices
@@ -75,6 +87,8 @@ struct BatchArgs {
     uint32_t* queue;           // model queue counters (see QueueWord; reset before the launch)
     int32_t listed;            // the models of one workgroup come from the lists of k_classify
     int32_t chip_bytes;        // LDS of a workgroup of k_batched_chip
+    uint8_t* wide;             // order[n_team, n_wide): taken by launch_wide (written by k_classify)
+    int32_t n_wide;            // 0: none
     int32_t* scratch;          // per-workgroup breeder list
     int64_t scratch_stride;    // ints per workgroup
     uint64_t* err;             // workspace error word
@@ -940,6 +954,13 @@ __global__ __launch_bounds__(1024) void k_classify(BatchArgs a) {
                                             chip_row_bytes<int16_t>() : 0;
             chip = chip && rows >= 2 && rows * 64 >= (d.n_s0 + d.n_w0) * 9 / 8;
             solo = pending && !chip;
+            if (i < a.n_wide) {
+                const int64_t size = cells + d.cap_s + d.cap_w;
+                const bool wide = solo && size >= kWideSize && d.cap_s + d.cap_w <= a.scratch_stride &&
+                                  (!d.multi_prey || (a.link_s && a.link_w));
+                a.wide[i] = wide;
+                solo = solo && !wide;
+            }
         }
         const uint64_t b[2] = {__ballot(chip), __ballot(solo)};
         __syncthreads();
@@ -1138,16 +1159,33 @@ __global__ __launch_bounds__(256) void k_batched_grass(const abm_model_desc* mod
     }
 }
 
-// Live counts per model (stored into the descriptors).
-__global__ __launch_bounds__(256) void k_batched_count(abm_model_desc* models, const int32_t* sa,
-                                                      const int32_t* wa) {
-    __shared__ uint32_t lds[4];
+// Live counts per model (stored into the descriptors): eight loads of a thread
+// in flight (96 models of up to 1002^2 cells: 700 us one at a time, by 256
+// threads each; 57 so).
+constexpr int kCountThreads = 1024, kCountAhead = 8;
+
+__device__ __forceinline__ uint32_t count_live(const int32_t* alive, int64_t cap) {
+    uint32_t n = 0;
+    for (int64_t i0 = threadIdx.x; i0 < cap; i0 += kCountThreads * kCountAhead) {
+        int32_t v[kCountAhead];
+#pragma unroll
+        for (int k = 0; k < kCountAhead; ++k) {
+            const int64_t i = i0 + k * kCountThreads;
+            v[k] = alive[i < cap ? i : i0];
+        }
+#pragma unroll
+        for (int k = 0; k < kCountAhead; ++k) n += v[k] != 0 && i0 + k * kCountThreads < cap;
+    }
+    return n;
+}
+
+__global__ __launch_bounds__(kCountThreads) void k_batched_count(abm_model_desc* models,
+                                                                const int32_t* sa,
+                                                                const int32_t* wa) {
+    __shared__ uint32_t lds[kCountThreads / 64];
     abm_model_desc& d = models[blockIdx.x];
-    uint32_t ls = 0, lw = 0;
-    for (int64_t i = threadIdx.x; i < d.cap_s; i += 256) ls += sa[d.sheep_off + i] != 0;
-    for (int64_t i = threadIdx.x; i < d.cap_w; i += 256) lw += wa[d.wolf_off + i] != 0;
-    ls = block_sum32(ls, lds);
-    lw = block_sum32(lw, lds);
+    const uint32_t ls = block_sum32(count_live(sa + d.sheep_off, d.cap_s), lds);
+    const uint32_t lw = block_sum32(count_live(wa + d.wolf_off, d.cap_w), lds);
     if (threadIdx.x == 0) {
         d.live_s = ls;
         d.live_w = lw;
@@ -1185,6 +1223,7 @@ using namespace abm;
 // byte 248), the team area (barrier counter and model mailbox per team, member
 // counts per workgroup) and one breeder list (2 * max_cap ints) per workgroup.
 constexpr int64_t kTeamAreaWords = int64_t(kMaxWorkgroups) * (2 + kCountWords);
+constexpr int kMaxWideModels = kMaxWorkgroups;   // (a byte each in the team area's count words)
 
 extern "C" size_t abm_batched_workspace_bytes(int64_t max_cap, int32_t n_workgroups) {
     if (max_cap < 1 || max_cap > (int64_t(1) << 30) || n_workgroups < 1 ||
@@ -1429,6 +1468,26 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     a.scratch_stride = 2 * b->max_cap;
     a.n_team = n_team;
     a.lds_words = int32_t(lds_bytes / 8);
+    // The models that would run in teams, and the largest of the others, by
+    // launches over the whole device instead, all of them side by side, where
+    // the workspace has two shares for each
+    const int64_t shares = int64_t((ws_bytes - kHeaderBytes - 4 * kTeamAreaWords) /
+                                   size_t(8 * b->max_cap));
+    int n_wide = 0;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (n_team > 0 && hipStreamIsCapturing(st, &capture) != hipSuccess)
+        return fail(ABM_E_HIP, "hipStreamIsCapturing failed");
+    const int32_t most = capture == hipStreamCaptureStatusNone ? kWideSteps : kWideStepsRecorded;
+    if (n_team > 0 && max_steps <= most && 2 * int64_t(n_team) <= shares &&
+        n_team < kMaxWideModels && wide_fits(b->max_cap)) {
+        // (the order is largest first where it balances the load)
+        const int with = n_team + (n_team + 8 < 64 ? 64 : n_team + 8);
+        n_wide = b->n_models < with ? b->n_models : with;
+        if (n_wide > shares / 2) n_wide = int(shares / 2);
+        team_wgs = 0;
+        grid = resident < b->n_models - n_team ? resident : b->n_models - n_team;
+        if (grid > shares) grid = int(shares);
+    }
     a.team_k = uint32_t(K);
     a.team_wgs = uint32_t(team_wgs);
     const int n_teams = team_wgs / K;
@@ -1436,29 +1495,55 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
                        a.team_ctr, n_teams);
     a.listed = 0;
     a.chip_bytes = 0;
-    // Models of one workgroup go to the chip where there are no teams (4096
-    // models of 32^2 to 256^2 cells x 50 steps: 50.4 to 8.9 ms).  Beside teams
-    // they run in the time those take anyway, and a launch before them only
-    // delays the teams (96 models of 32^2 to 1024^2: 34.9 to 35.1 ms).
-    if (!(tune && tune->global_claims) && n_team == 0) {
+    // Models of one workgroup go to the chip (4096 models of 32^2 to 256^2 cells
+    // x 50 steps: 50.4 to 8.9 ms), unless there are teams: they run in the time
+    // those take anyway, and a launch before them only delays the teams.
+    a.wide = reinterpret_cast<uint8_t*>(a.team_counts);
+    a.n_wide = 0;
+    const bool chips = !(tune && tune->global_claims) && team_wgs == 0 && n_team < b->n_models;
+    if (chips) {
         const int chip = chip_lds_bytes();
         if (chip > 0) {
             a.listed = 1;
             a.chip_bytes = chip;
+            a.n_wide = n_wide;
             hipLaunchKernelGGL(k_classify, dim3(1), dim3(1024), 0, st, a);
-            const int solo = b->n_models - n_team;
-            const int wgs = n_cu < grid ? n_cu : grid;
-            hipLaunchKernelGGL(k_batched_chip, dim3(wgs < solo ? wgs : solo), dim3(kChipThreads),
-                               size_t(chip), st, a);
         }
     }
+    if (n_wide > 0) {
+        WideArgs w;
+        w.models = b->models;
+        w.order = order;
+        w.ready = b->ready;
+        w.claims = b->claims;
+        w.sheep = b->sheep;
+        w.wolves = b->wolves;
+        w.link_s = b->link_s;
+        w.link_w = b->link_w;
+        w.err = a.err;
+        w.taken = a.wide;
+        w.shares = reinterpret_cast<char*>(a.scratch);
+        w.share = 8 * b->max_cap;
+        w.max_cap = b->max_cap;
+        w.n = a.listed ? n_wide : n_team;
+        w.n_team = n_team;
+        w.max_steps = max_steps;
+        rc = launch_wide(w, st);
+        if (rc != ABM_OK) return rc;
+    }
+    if (a.listed) {
+        const int solo = b->n_models - n_team;
+        const int wgs = n_cu < grid ? n_cu : grid;
+        hipLaunchKernelGGL(k_batched_chip, dim3(wgs < solo ? wgs : solo), dim3(kChipThreads),
+                           size_t(a.chip_bytes), st, a);
+    }
     const size_t dyn = size_t(lds_bytes);
-    switch (items) {
+    if (grid > 0) switch (items) {
         case 1: hipLaunchKernelGGL(k_batched_run<1>, dim3(grid), dim3(block), dyn, st, a); break;
         case 2: hipLaunchKernelGGL(k_batched_run<2>, dim3(grid), dim3(block), dyn, st, a); break;
         default: hipLaunchKernelGGL(k_batched_run<4>, dim3(grid), dim3(block), dyn, st, a); break;
     }
-    hipLaunchKernelGGL(k_batched_count, dim3(b->n_models), dim3(256), 0, st, b->models,
+    hipLaunchKernelGGL(k_batched_count, dim3(b->n_models), dim3(kCountThreads), 0, st, b->models,
                        b->sheep.alive, b->wolves.alive);
     return launch_status("predation_run_batched");
 }

@@ -134,4 +134,25 @@ int next_epoch(const Workspace& w, hipStream_t st, EpochArg* out);
 int launch_small_predation(const abm_predation_params* p, const abm_predation_state* s,
                            int32_t n_steps, const Workspace& w, hipStream_t st, bool* taken);
 
+// The large models of a batch, order[0, n), advanced side by side by launches
+// over the whole device (predation.hip): those below n_team, and of the others
+// the ones marked in `taken`.
+struct WideArgs {
+    abm_model_desc* models;
+    const int32_t* order;
+    int32_t* ready;
+    uint64_t* claims;
+    abm_species sheep, wolves;
+    int32_t *link_s, *link_w;
+    uint64_t* err;
+    const uint8_t* taken;
+    char* shares;              // 2 n shares of workspace
+    int64_t share;             // bytes of one (8 max_cap)
+    int64_t max_cap;
+    int32_t n, n_team, max_steps;
+};
+
+bool wide_fits(int64_t max_cap);
+int launch_wide(const WideArgs& w, hipStream_t st);
+
 }  // namespace abm

@@ -124,6 +124,8 @@ struct StepArgs {
     int64_t* fold_row;    // stats row of the previous step, folded by K1 (or null)
     uint32_t step;
     uint64_t* status;
+    uint64_t* err;        // set when a wait of the scans gives up
+    unsigned long long* updates;   // live agents are added to it (or null)
     EpochArg epoch;
     int32_t* blist[2];    // breeder lists
     int64_t* d_nb[2];     // breeder counts
@@ -131,6 +133,7 @@ struct StepArgs {
     int32_t* free_pre[2]; // per block: exclusive free-slot prefix, written by K2 for K3
     uint32_t tiles[2];
     uint32_t blocks[2];
+    uint32_t turn;          // blocks of a species in turn: 2^turn (see Block)
     uint32_t chain_off[2];  // start of each species' breeder scan chain in the status words
     uint32_t fchain_off[2]; // ... and of its free-slot scan chain
     int32_t multi;          // prey by rank within a cell (K1 builds lists, K1b matches)
@@ -263,11 +266,15 @@ __global__ __launch_bounds__(kBlock) void k_fill64(int64_t* p, int64_t n, int64_
 // Tile t of a species covers slots [2048 t, 2048 t + 2048) and bitmask words
 // [64 t, 64 t + 64).  Bits of slots at or beyond the capacity are always zero.
 // A block is what one workgroup takes: one tile, or kTilesPerBlock consecutive
-// ones.  The blocks of both species are interleaved -- sheep 0, wolves 0, sheep
-// 1, wolves 1, ... until the shorter chain ends, then the rest of the longer
-// one -- so that the low tiles, where children fill the lowest free slots and
-// the live agents gather, are all in the first round of resident workgroups;
-// within each chain blocks still run in increasing order.
+// ones.  The blocks of both species are interleaved, 2^turn of each in turn
+// until the shorter chain ends, then the rest, so that the low tiles, where
+// children fill the lowest free slots and the live agents gather, are all in
+// the first round of resident workgroups; within each chain blocks still run
+// in increasing order.  Workgroups go to the eight XCDs in turn, so single
+// blocks leave all the sheep to four of them.  Small launches are better with
+// eight blocks in turn (us per step: 300^2 cells 31.3 against 32.9, 2048^2 with
+// a slot a cell 61.9 against 63.4), large ones, at the atomics' rate, with one
+// (2048^2 with four slots a cell, 3072 blocks: 120 against 124).
 struct Block {
     int s;            // species
     uint32_t q;       // block within the species' scan chain
@@ -286,16 +293,25 @@ __device__ __forceinline__ uint32_t first_tile(uint32_t q) {
     return q < kSingleTiles ? q : kSingleTiles + (q - kSingleTiles) * kTilesPerBlock;
 }
 
-__device__ __forceinline__ Block block_of(const StepArgs& a) {
-    const uint32_t m = a.blocks[0] < a.blocks[1] ? a.blocks[0] : a.blocks[1];
-    const uint32_t n = blockIdx.x;
+// The species' one of a pair (a subscript that is not a constant would put the
+// arguments in memory where they are a local copy).
+template <class T>
+__device__ __forceinline__ T pick(const T (&a)[2], int s) {
+    return s ? a[1] : a[0];
+}
+
+// Block n of the interleaved order.
+__device__ __forceinline__ Block block_of(const StepArgs& a, uint32_t n) {
+    const uint32_t low = (1u << a.turn) - 1u;
+    const uint32_t m = (a.blocks[0] < a.blocks[1] ? a.blocks[0] : a.blocks[1]) & ~low;
     Block b;
     if (n < 2 * m) {
-        b.s = int(n & 1u);
-        b.q = n >> 1;
+        b.s = int((n >> a.turn) & 1u);
+        b.q = ((n >> (a.turn + 1)) << a.turn) + (n & low);
     } else {
-        b.s = a.blocks[0] > a.blocks[1] ? 0 : 1;
-        b.q = m + (n - 2 * m);
+        const uint32_t r = n - 2 * m, rest0 = a.blocks[0] - m;
+        b.s = r < rest0 ? 0 : 1;
+        b.q = m + (b.s ? r - rest0 : r);
     }
     const uint32_t t = first_tile(b.q), left = (b.s ? a.tiles[1] : a.tiles[0]) - t;
     b.words = kOwners * (b.q < kSingleTiles ? 1u : (left < kTilesPerBlock ? left : kTilesPerBlock));
@@ -330,7 +346,7 @@ __device__ __forceinline__ uint32_t live_of(const StepArgs& a, const Block& b, u
     uint32_t word[kPerThread], live = 0;
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k)
-        word[k] = a.bits[b.s][b.word0 + (slot_in_block(w0, k) >> 5)];
+        word[k] = pick(a.bits, b.s)[b.word0 + (slot_in_block(w0, k) >> 5)];
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) live |= ((word[k] >> (threadIdx.x & 31)) & 1u) << k;
     return live;
@@ -429,19 +445,10 @@ __device__ __forceinline__ void hier_prefix2(uint64_t* chain_a, uint64_t* chain_
 }
 
 // ------------------------------------------------------------------ K1
-__global__ __launch_bounds__(kThreads) void k_move_claim(StepArgs a) {
-    __shared__ uint32_t lds[kThreadWaves];
-    const Block b = block_of(a);
+__device__ __forceinline__ void move_claim(const StepArgs& a, const Block& b, uint32_t* lds) {
     const int s = b.s;
-    // the previous step's statistics, folded by the last workgroup (a tile
-    // past the live agents, so it has time to spare); this step adds to the
-    // other half of the accumulators
-    if (a.fold_row && blockIdx.x == gridDim.x - 1)
-        fold_stats(a.acc + (kHalfLanes - a.acc_par), a.fold_row);
-    // the next step's marks start from zero (K3 raises them)
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 2 * kMarkLanes) a.mark_wr[threadIdx.x] = 0;
     if (b.q >= mark_of(a, s)) return;   // past the last live agent
-    const Species sp = species_at(a.sp[s], b.base);
+    const Species sp = species_at(pick(a.sp, s), b.base);
     const uint32_t base = uint32_t(b.base);
     const uint64_t skey = stream_key(a.seed, a.step);
     uint32_t count = 0;
@@ -489,7 +496,7 @@ __global__ __launch_bounds__(kThreads) void k_move_claim(StepArgs a) {
                 const uint64_t prev =
                     atomicExch(reinterpret_cast<unsigned long long*>(cell + (s ? 2 : 1)),
                                (unsigned long long)(a.tag_hi | uint64_t(base + i[k])));
-                a.blist[s][base + i[k]] = head_slot(a, prev);
+                pick(a.blist, s)[base + i[k]] = head_slot(a, prev);
             } else {
                 atomicMin(reinterpret_cast<unsigned long long*>(cell + (s ? 2 : 1)),
                           (unsigned long long)claim_key(a, skey, base + i[k],
@@ -498,6 +505,28 @@ __global__ __launch_bounds__(kThreads) void k_move_claim(StepArgs a) {
         }
     }
     if (a.stats) block_add(count, a.acc + a.acc_par, s ? kLiveW : kLiveS, lds);
+    if (a.updates) {
+        const uint32_t v = wave_sum(count);
+        if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t all = 0;
+            for (int w = 0; w < kThreadWaves; ++w) all += lds[w];
+            if (all) atomicAdd(a.updates, (unsigned long long)all);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_move_claim(StepArgs a) {
+    __shared__ uint32_t lds[kThreadWaves];
+    // the previous step's statistics, folded by the last workgroup (a tile
+    // past the live agents, so it has time to spare); this step adds to the
+    // other half of the accumulators
+    if (a.fold_row && blockIdx.x == gridDim.x - 1)
+        fold_stats(a.acc + (kHalfLanes - a.acc_par), a.fold_row);
+    // the next step's marks start from zero (K3 raises them)
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 2 * kMarkLanes) a.mark_wr[threadIdx.x] = 0;
+    move_claim(a, block_of(a, blockIdx.x), lds);
 }
 
 // K1b (multi_prey): wolf j of cell c takes rank r among the wolves of c (eat
@@ -506,8 +535,7 @@ __global__ __launch_bounds__(kThreads) void k_move_claim(StepArgs a) {
 // cell are short at the workloads' densities (a few agents), and the count is
 // quadratic in the sheep of one cell at worst.  Distinct wolves of a cell
 // have distinct ranks, so no sheep is taken twice.
-__global__ __launch_bounds__(kBlock) void k_prey_match(StepArgs a) {
-    const int64_t j = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+__device__ __forceinline__ void prey_match(const StepArgs& a, int64_t j) {
     if (j >= a.cap_w || a.sp[1].alive[j] == 0) return;
     const int64_t c = cell_of(a.sp[1].x[j], a.sp[1].y[j], a.W, a.H);
     if (c < 0) return;
@@ -530,12 +558,19 @@ __global__ __launch_bounds__(kBlock) void k_prey_match(StepArgs a) {
     }
 }
 
+__global__ __launch_bounds__(kBlock) void k_prey_match(StepArgs a) {
+    prey_match(a, int64_t(blockIdx.x) * kBlock + threadIdx.x);
+}
+
 // ------------------------------------------------------------------ K2
-__global__ __launch_bounds__(kThreads) void k_eat_breeders(StepArgs a) {
-    __shared__ uint32_t breeds[kBlockWords], gone[kBlockWords];
-    __shared__ uint32_t lds[2 * kThreadWaves + 1];
-    const uint32_t epoch = read_epoch(a.epoch);
-    const Block b = block_of(a);
+struct EatLds {
+    uint32_t breeds[kBlockWords], gone[kBlockWords];
+    uint32_t lds[2 * kThreadWaves + 1];
+};
+
+__device__ __forceinline__ void eat_breeders(const StepArgs& a, const Block& b, uint32_t epoch,
+                                             EatLds& sh) {
+    uint32_t *const breeds = sh.breeds, *const gone = sh.gone, *const lds = sh.lds;
     const int s = b.s;
     const int64_t cap = s ? a.cap_w : a.cap_s;
     // blocks at or past the mark hold no live agent: no breeder, every slot
@@ -544,12 +579,12 @@ __global__ __launch_bounds__(kThreads) void k_eat_breeders(StepArgs a) {
     const uint32_t mark = mark_of(a, s);
     if (b.q >= mark) {
         if (mark == 0 && b.q == 0 && threadIdx.x == 0) {
-            *a.d_nb[s] = 0;
-            *a.d_nf[s] = cap;
+            *pick(a.d_nb, s) = 0;
+            *pick(a.d_nf, s) = cap;
         }
         return;
     }
-    const Species sp = species_at(a.sp[s], b.base);
+    const Species sp = species_at(pick(a.sp, s), b.base);
     const uint32_t base = uint32_t(b.base);
     breeds[threadIdx.x] = 0;
     gone[threadIdx.x] = 0;
@@ -618,23 +653,23 @@ __global__ __launch_bounds__(kThreads) void k_eat_breeders(StepArgs a) {
     // once; a thread per bitmask word of the block
     const uint32_t w = threadIdx.x;
     const uint32_t bm = breeds[w];
-    const uint32_t mask = w < b.words ? a.bits[s][b.word0 + w] : 0u;
+    const uint32_t mask = w < b.words ? pick(a.bits, s)[b.word0 + w] : 0u;
     const uint32_t free_m = (~mask & word_in_cap(b, w, cap)) | gone[w];
     uint32_t r0, rf;
     const uint32_t total = rank_block(__popc(bm), &r0, lds);
     const uint32_t total_f = rank_block(__popc(free_m), &rf, lds + kThreadWaves);
     uint32_t excl, free_excl;
-    hier_prefix2(a.status + a.chain_off[s], a.status + a.fchain_off[s], a.status - 1, b.q,
-                 a.blocks[s], epoch, total, total_f, lds, &excl, &free_excl);
+    hier_prefix2(a.status + pick(a.chain_off, s), a.status + pick(a.fchain_off, s), a.err, b.q,
+                 pick(a.blocks, s), epoch, total, total_f, lds, &excl, &free_excl);
     uint32_t r = excl + r0;
     for (uint32_t m = bm; m; m &= m - 1u)
-        a.blist[s][r++] = int32_t(b.base + w * 32u + (__ffs(m) - 1));
+        pick(a.blist, s)[r++] = int32_t(b.base + w * 32u + (__ffs(m) - 1));
     if (threadIdx.x == 0) {
-        a.free_pre[s][b.q] = int32_t(free_excl);
+        pick(a.free_pre, s)[b.q] = int32_t(free_excl);
         if (b.q == mark - 1) {
             const int64_t past = cap - int64_t(first_tile(mark)) * kTile;
-            *a.d_nb[s] = int64_t(excl) + total;
-            *a.d_nf[s] = int64_t(free_excl) + total_f + (past > 0 ? past : 0);
+            *pick(a.d_nb, s) = int64_t(excl) + total;
+            *pick(a.d_nf, s) = int64_t(free_excl) + total_f + (past > 0 ? past : 0);
         }
     }
     if (a.stats && s == 0) {
@@ -643,32 +678,42 @@ __global__ __launch_bounds__(kThreads) void k_eat_breeders(StepArgs a) {
     }
 }
 
+__global__ __launch_bounds__(kThreads) void k_eat_breeders(StepArgs a) {
+    __shared__ EatLds sh;
+    eat_breeders(a, block_of(a, blockIdx.x), read_epoch(a.epoch), sh);
+}
+
 // ------------------------------------------------------------------ K3
-__global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
-    __shared__ uint16_t list[kTile * kTilesPerBlock];
-    __shared__ uint32_t gone[kBlockWords], starves[kBlockWords];
-    __shared__ uint32_t lds[kThreadWaves + 1];
-    const Block b = block_of(a);
+struct BreedLds {
+    uint16_t list[kTile * kTilesPerBlock];
+    uint32_t gone[kBlockWords], starves[kBlockWords];
+    uint32_t lds[kThreadWaves + 1];
+};
+
+// At the end of a tag period each workgroup (b of n) re-arms its slice of the
+// claim tables for the next step (K2, the last reader, has finished): whole
+// lines, streamed.
+__device__ __forceinline__ void rearm_slice(const StepArgs& a, uint32_t b, uint32_t n) {
+    const int64_t words = 3 * a.G, per = (words + n - 1) / n;
+    const int64_t lo = int64_t(b) * per;
+    const int64_t hi = lo + per < words ? lo + per : words;
+    for (int64_t w = lo + threadIdx.x; w < hi; w += kThreads) a.claims[w] = kNoClaim;
+}
+
+__device__ __forceinline__ void breed_die(const StepArgs& a, const Block& b, BreedLds& sh) {
+    uint16_t* const list = sh.list;
+    uint32_t *const gone = sh.gone, *const starves = sh.starves, *const lds = sh.lds;
     const int s = b.s;
     const int64_t cap = s ? a.cap_w : a.cap_s;
-    // at the end of a tag period this workgroup's slice of the claim tables is
-    // re-armed for the next step (K2, the last reader, has finished): whole
-    // lines, streamed
-    if (a.rearm) {
-        const int64_t words = 3 * a.G, per = (words + gridDim.x - 1) / gridDim.x;
-        const int64_t lo = int64_t(blockIdx.x) * per;
-        const int64_t hi = lo + per < words ? lo + per : words;
-        for (int64_t w = lo + threadIdx.x; w < hi; w += kThreads) a.claims[w] = kNoClaim;
-    }
-    const int64_t nb = *a.d_nb[s], nfree = *a.d_nf[s];
-    if (a.stats && b.q == a.blocks[s] - 1 && threadIdx.x == 0)
+    const int64_t nb = *pick(a.d_nb, s), nfree = *pick(a.d_nf, s);
+    if (a.stats && b.q == pick(a.blocks, s) - 1 && threadIdx.x == 0)
         a.stats[s ? kBirthsW : kBirthsS] = nfree < nb ? nfree : nb;
     // the block's free-slot prefix: from K2's scan below the mark; past it every
     // slot of every block is free
     const uint32_t mark = mark_of(a, s);
     int64_t pre;
     if (b.q < mark) {
-        pre = a.free_pre[s][b.q];
+        pre = pick(a.free_pre, s)[b.q];
     } else {
         const int64_t first = int64_t(first_tile(mark)) * kTile;
         pre = nfree - (cap - first > 0 ? cap - first : 0) + (b.base - first);
@@ -676,7 +721,7 @@ __global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
         // breeders) there is nothing to do
         if (pre >= nb) return;
     }
-    const Species sp = a.sp[s], here = species_at(sp, b.base);
+    const Species sp = pick(a.sp, s), here = species_at(sp, b.base);
     gone[threadIdx.x] = 0;
     starves[threadIdx.x] = 0;
     __syncthreads();
@@ -709,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
     }
     __syncthreads();
     const uint32_t w = threadIdx.x;
-    const uint32_t mask = w < b.words ? a.bits[s][b.word0 + w] : 0u;   // live at K1
+    const uint32_t mask = w < b.words ? pick(a.bits, s)[b.word0 + w] : 0u;   // live at K1
     const uint32_t free_m = (~mask & word_in_cap(b, w, cap)) | gone[w];
     // (the same free slots K2 ranked: its chain gave this block's prefix)
     uint32_t r0;
@@ -725,7 +770,7 @@ __global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
         list[r] = uint16_t(w * 32u + (__ffs(m) - 1));
     }
     const uint32_t live_m = (mask & ~gone[w] & ~starves[w]) | born_m;
-    if (w < b.words && live_m != mask) a.bits[s][b.word0 + w] = live_m;
+    if (w < b.words && live_m != mask) pick(a.bits, s)[b.word0 + w] = live_m;
     // the next step's mark: past the last block left with a live agent
     if (__syncthreads_or(live_m != 0u) && threadIdx.x == 0)
         atomicMax(reinterpret_cast<unsigned long long*>(a.mark_wr + s * kMarkLanes +
@@ -733,7 +778,7 @@ __global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
                   (unsigned long long)(b.q + 1));
     // the children, spread over the workgroup
     for (uint32_t j = threadIdx.x; j < births; j += kThreads) {
-        const int64_t ci = b.base + list[j], p = a.blist[s][excl + j];
+        const int64_t ci = b.base + list[j], p = pick(a.blist, s)[excl + j];
         const int32_t px = sp.x[p], py = sp.y[p], pe = sp.e[p];
         const int32_t ec = pe >> 1;
         sp.x[ci] = px;
@@ -745,7 +790,30 @@ __global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
     if (a.stats) block_add(starved, a.acc + a.acc_par, s ? kStarvedW : kStarvedS, lds);
 }
 
+__global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
+    __shared__ BreedLds sh;
+    if (a.rearm) rearm_slice(a, blockIdx.x, gridDim.x);
+    breed_die(a, block_of(a, blockIdx.x), sh);
+}
+
 // ------------------------------------------------------------------ call edges
+// Bitmask word k of the live slots.
+__device__ __forceinline__ uint32_t live_word(const int32_t* alive, int64_t k, int64_t cap) {
+    const int32_t* al = alive + k * 32;
+    uint32_t m = 0;
+    if (k * 32 + 32 <= cap) {
+        int4 v[8];
+        __builtin_memcpy(v, al, sizeof v);      // (4-byte alignment is enough)
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            m |= uint32_t(v[q].x != 0) << (4 * q) | uint32_t(v[q].y != 0) << (4 * q + 1) |
+                 uint32_t(v[q].z != 0) << (4 * q + 2) | uint32_t(v[q].w != 0) << (4 * q + 3);
+    } else {
+        for (int b = 0; b < 32 && k * 32 + b < cap; ++b) m |= uint32_t(al[b] != 0) << b;
+    }
+    return m;
+}
+
 // Start of a call: grass countdowns -> ready steps, live bitmasks from alive,
 // every claim word re-armed.  One thread per bitmask word (and cell).
 __global__ __launch_bounds__(kBlock) void k_call_begin(StepArgs a, int64_t G, int64_t words_s,
@@ -759,26 +827,8 @@ __global__ __launch_bounds__(kBlock) void k_call_begin(StepArgs a, int64_t G, in
         a.claims[3 * k + 1] = kNoClaim;
         a.claims[3 * k + 2] = kNoClaim;
     }
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int64_t words = s ? words_w : words_s;
-        const int64_t cap = s ? a.cap_w : a.cap_s;
-        if (k >= words) continue;
-        const int32_t* al = a.sp[s].alive + k * 32;
-        uint32_t m = 0;
-        if (k * 32 + 32 <= cap && (reinterpret_cast<uintptr_t>(al) & 15) == 0) {
-            int4 v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = reinterpret_cast<const int4*>(al)[q];
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                m |= uint32_t(v[q].x != 0) << (4 * q) | uint32_t(v[q].y != 0) << (4 * q + 1) |
-                     uint32_t(v[q].z != 0) << (4 * q + 2) | uint32_t(v[q].w != 0) << (4 * q + 3);
-        } else {
-            for (int b = 0; b < 32 && k * 32 + b < cap; ++b) m |= uint32_t(al[b] != 0) << b;
-        }
-        a.bits[s][k] = m;
-    }
+    if (k < words_s) a.bits[0][k] = live_word(a.sp[0].alive, k, a.cap_s);
+    if (k < words_w) a.bits[1][k] = live_word(a.sp[1].alive, k, a.cap_w);
 }
 
 // End of a call: ready steps -> countdowns at step `end`.
@@ -793,6 +843,223 @@ __global__ __launch_bounds__(kBlock) void k_call_end(int32_t* grass, int64_t G, 
 // The last step's fold (every other step's is done by the next step's K1).
 __global__ __launch_bounds__(kBlock) void k_fold_stats(int64_t* acc, int64_t* stats) {
     fold_stats(acc, stats);
+}
+
+// Slot bits, first tag and steps of a tag period for slots below max_cap.
+struct Tags {
+    uint32_t sb, top, period;
+};
+
+__host__ __device__ __forceinline__ Tags tags_for(int64_t max_cap) {
+    uint32_t sb = 1;
+    while (sb < 31 && (int64_t(1) << sb) < max_cap) ++sb;
+    const uint32_t tag_bits = 32 - sb < kTagBits ? 32 - sb : kTagBits;
+    const uint32_t t_max = (1u << tag_bits) - 1;
+    return Tags{sb, t_max > 1 ? t_max - 1 : 0u, t_max > 1 ? t_max - 1 : 1u};
+}
+
+// ------------------------------------------------------------------ batches
+// Large models of a batch, all of them side by side: the launches above with
+// the models as the grid's second dimension (`wide` models).  96 models of 32^2
+// to 1024^2 cells x 40 steps take 10.9 ms, bound as the one-model launches are
+// by the atomics and the claim lines of 1.7 M agents (34.5 ms by teams of four
+// workgroups, whose chain of dependent accesses per agent the largest model's
+// team went through alone).  A model's
+// arguments are built on the device, from its descriptor, in its share of the
+// workspace: the breeder lists in one half of it; the arguments, marks, totals,
+// scan words and live bitmasks in the other.
+struct WideLayout {
+    int64_t status, free_pre, bits[2], end;   // byte offsets
+};
+
+struct WideModel {
+    StepArgs a;                           // what does not change (no pointers)
+    WideLayout at;
+    Tags tags;
+    int64_t cell_off, slot_off[2];
+    uint32_t step0;
+    int32_t n;                            // steps of this call
+    unsigned long long updates;
+    uint64_t marks[2][2][kMarkLanes];
+    int64_t nb[2], nf[2];
+};
+
+__host__ __device__ __forceinline__ WideLayout wide_layout(uint32_t tiles_s, uint32_t tiles_w) {
+    const uint32_t b0 = blocks_of(tiles_s), b1 = blocks_of(tiles_w);
+    WideLayout l;
+    l.status = (int64_t(sizeof(WideModel)) + 63) / 64 * 64;
+    l.free_pre = l.status + 16 * (chain_words(b0) + chain_words(b1));
+    l.bits[0] = l.free_pre + 4 * (int64_t(b0) + b1);
+    l.bits[1] = l.bits[0] + 4 * int64_t(tiles_s) * kOwners;
+    l.end = l.bits[1] + 4 * int64_t(tiles_w) * kOwners;
+    return l;
+}
+
+__device__ __forceinline__ WideModel* wide_model(char* shares, int64_t share, uint32_t y) {
+    return reinterpret_cast<WideModel*>(shares + (2 * int64_t(y) + 1) * share);
+}
+
+// One workgroup per model: its arguments, its counters and scan words cleared.
+__global__ __launch_bounds__(kBlock) void k_wide_begin(WideArgs w) {
+    const uint32_t y = blockIdx.x;
+    WideModel* const m = wide_model(w.shares, w.share, y);
+    const abm_model_desc& d = w.models[w.order[y]];
+    const bool links = w.link_s && w.link_w;
+    // as a workgroup's model: refused if it does not fit the lists
+    const bool bad = d.cap_s + d.cap_w > 2 * w.max_cap || (d.multi_prey && !links);
+    const bool taken = int32_t(y) < w.n_team || w.taken[y];
+    const int32_t left = d.steps_target - d.step;
+    const int32_t n = bad || !taken || left <= 0 ? 0 : (left < w.max_steps ? left : w.max_steps);
+    if (n == 0) {
+        if (threadIdx.x == 0) {
+            m->n = 0;
+            if (bad && int32_t(y) < w.n_team) st_agent(w.err, 1ull);
+        }
+        return;
+    }
+    const uint32_t tiles_s = uint32_t((d.cap_s + kTile - 1) / kTile);
+    const uint32_t tiles_w = uint32_t((d.cap_w + kTile - 1) / kTile);
+    const WideLayout l = wide_layout(tiles_s, tiles_w);
+    char* const base = reinterpret_cast<char*>(m);
+    for (int64_t i = threadIdx.x; i < (l.free_pre - l.status) / 8; i += kBlock)
+        reinterpret_cast<uint64_t*>(base + l.status)[i] = 0;   // (no step's epoch)
+    if (threadIdx.x != 0) return;
+    StepArgs a = {};
+    a.W = d.W;
+    a.H = d.H;
+    a.R = d.R;
+    a.gain_s = d.gain_s;
+    a.gain_w = d.gain_w;
+    a.T_s = d.T_s;
+    a.T_w = d.T_w;
+    a.seed = d.seed;
+    a.cap_s = d.cap_s;
+    a.cap_w = d.cap_w;
+    a.G = int64_t(d.W) * d.H;
+    a.multi = d.multi_prey != 0;
+    a.tiles[0] = tiles_s;
+    a.tiles[1] = tiles_w;
+    a.blocks[0] = blocks_of(tiles_s);
+    a.blocks[1] = blocks_of(tiles_w);
+    const int64_t cw0 = chain_words(a.blocks[0]), cw1 = chain_words(a.blocks[1]);
+    a.chain_off[1] = uint32_t(cw0);
+    a.fchain_off[0] = uint32_t(cw0 + cw1);
+    a.fchain_off[1] = uint32_t(2 * cw0 + cw1);
+    for (int s = 0; s < 2; ++s)
+        for (int q = 0; q < kMarkLanes; ++q) m->marks[0][s][q] = a.blocks[s];
+    m->tags = tags_for(d.cap_s > d.cap_w ? d.cap_s : d.cap_w);
+    a.sb = m->tags.sb;
+    a.tag_mask = ~uint64_t(0) << (32 + a.sb);
+    m->a = a;
+    m->at = l;
+    m->cell_off = d.cell_off;
+    m->slot_off[0] = d.sheep_off;
+    m->slot_off[1] = d.wolf_off;
+    m->step0 = uint32_t(d.step);
+    m->n = n;
+    m->updates = 0;
+}
+
+// The model's arguments at step k of the call.
+__device__ __forceinline__ StepArgs wide_step(const WideArgs& w, WideModel* m, int32_t k) {
+    StepArgs a = m->a;
+    // (pointers made of the launch's arguments are known to be global; read
+    // from memory they could point anywhere, and every access would be a flat one)
+    char* const base = reinterpret_cast<char*>(m);
+    a.ready = w.ready + m->cell_off;
+    a.claims = w.claims + 3 * m->cell_off;
+    a.sp[0] = Species{w.sheep.x + m->slot_off[0], w.sheep.y + m->slot_off[0],
+                      w.sheep.e + m->slot_off[0], w.sheep.alive + m->slot_off[0]};
+    a.sp[1] = Species{w.wolves.x + m->slot_off[1], w.wolves.y + m->slot_off[1],
+                      w.wolves.e + m->slot_off[1], w.wolves.alive + m->slot_off[1]};
+    a.bits[0] = reinterpret_cast<uint32_t*>(base + m->at.bits[0]);
+    a.bits[1] = reinterpret_cast<uint32_t*>(base + m->at.bits[1]);
+    a.status = reinterpret_cast<uint64_t*>(base + m->at.status);
+    a.err = w.err;
+    a.updates = &m->updates;
+    a.free_pre[0] = reinterpret_cast<int32_t*>(base + m->at.free_pre);
+    a.free_pre[1] = a.free_pre[0] + a.blocks[0];
+    a.blist[0] = reinterpret_cast<int32_t*>(base - w.share);
+    a.blist[1] = a.blist[0] + a.cap_s;
+    for (int s = 0; s < 2; ++s) {
+        a.d_nb[s] = &m->nb[s];
+        a.d_nf[s] = &m->nf[s];
+    }
+    const uint32_t phase = uint32_t(k) % m->tags.period;
+    a.step = m->step0 + uint32_t(k);
+    a.tag_hi = uint64_t(m->tags.top - phase) << (32 + m->tags.sb);
+    // (the tables are all-ones between runs)
+    a.rearm = phase == m->tags.period - 1 || k + 1 == m->n;
+    a.mark_rd = &m->marks[k & 1][0][0];
+    a.mark_wr = &m->marks[(k + 1) & 1][0][0];
+    return a;
+}
+
+__global__ __launch_bounds__(kBlock) void k_wide_bits(WideArgs w) {
+    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
+    if (m->n == 0) return;
+    const StepArgs a = wide_step(w, m, 0);
+    const int64_t words_s = int64_t(a.tiles[0]) * kOwners, words_w = int64_t(a.tiles[1]) * kOwners;
+    for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < words_s || k < words_w;
+         k += int64_t(gridDim.x) * kBlock) {
+        if (k < words_s) a.bits[0][k] = live_word(a.sp[0].alive, k, a.cap_s);
+        if (k < words_w) a.bits[1][k] = live_word(a.sp[1].alive, k, a.cap_w);
+    }
+}
+
+// Runs body(arguments, block) over this workgroup's blocks of its model.  A
+// model's workgroups are consecutive, so the smallest unfinished block of its
+// scans is always that of a resident one.
+template <class F>
+__device__ __forceinline__ void wide_blocks(const StepArgs& a, F body) {
+    const uint32_t n = a.blocks[0] + a.blocks[1];
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        if (i != blockIdx.x) __syncthreads();
+        body(block_of(a, i));
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_wide_move(WideArgs w, int32_t k) {
+    __shared__ uint32_t lds[kThreadWaves];
+    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
+    if (k >= m->n) return;
+    const StepArgs a = wide_step(w, m, k);
+    if (blockIdx.x == 0 && threadIdx.x < 2 * kMarkLanes) a.mark_wr[threadIdx.x] = 0;
+    wide_blocks(a, [&](const Block& b) { move_claim(a, b, lds); });
+}
+
+__global__ __launch_bounds__(kBlock) void k_wide_match(WideArgs w, int32_t k) {
+    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
+    if (k >= m->n || !m->a.multi) return;
+    const StepArgs a = wide_step(w, m, k);
+    for (int64_t j = int64_t(blockIdx.x) * kBlock + threadIdx.x; j < a.cap_w;
+         j += int64_t(gridDim.x) * kBlock)
+        prey_match(a, j);
+}
+
+__global__ __launch_bounds__(kThreads) void k_wide_eat(WideArgs w, int32_t k) {
+    __shared__ EatLds sh;
+    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
+    if (k >= m->n) return;
+    const StepArgs a = wide_step(w, m, k);
+    wide_blocks(a, [&](const Block& b) { eat_breeders(a, b, uint32_t(k) + 1u, sh); });
+}
+
+__global__ __launch_bounds__(kThreads) void k_wide_breed(WideArgs w, int32_t k) {
+    __shared__ BreedLds sh;
+    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
+    if (k >= m->n) return;
+    const StepArgs a = wide_step(w, m, k);
+    if (a.rearm) rearm_slice(a, blockIdx.x, gridDim.x);
+    wide_blocks(a, [&](const Block& b) { breed_die(a, b, sh); });
+}
+
+__global__ __launch_bounds__(64) void k_wide_end(WideArgs w) {
+    const WideModel* const m = wide_model(w.shares, w.share, blockIdx.x);
+    if (threadIdx.x != 0 || m->n == 0) return;
+    abm_model_desc& d = w.models[w.order[blockIdx.x]];
+    d.step += m->n;
+    d.updates += int64_t(m->updates);
 }
 
 int check_params(const abm_predation_params* p) {
@@ -826,6 +1093,37 @@ int check_state(const abm_predation_state* s) {
 Species species_of(const abm_species& s) { return Species{s.x, s.y, s.e, s.alive}; }
 
 }  // namespace
+}  // namespace abm
+
+namespace abm {
+
+// Workgroups a model gets at most in a launch (96 models of 32^2 to 1024^2 cells
+// x 40 steps: 10.9 ms with 48, 12.4 with 96, 11.1 with 250, one a block).
+constexpr uint32_t kWideBlocks = 48;
+
+bool wide_fits(int64_t max_cap) {
+    // (a descriptor may split the 2 max_cap slots otherwise: a tile more at most)
+    const uint32_t tiles = uint32_t(tiles_for(max_cap, kTile)) + 1;
+    return wide_layout(tiles, tiles).end <= 8 * max_cap;
+}
+
+int launch_wide(const WideArgs& w, hipStream_t st) {
+    const int64_t blocks = 2 * int64_t(blocks_of(uint32_t(tiles_for(w.max_cap, kTile))));
+    const uint32_t x = uint32_t(blocks < kWideBlocks ? blocks : kWideBlocks);
+    const dim3 grid(x, uint32_t(w.n)), block(kThreads);
+    hipLaunchKernelGGL(k_wide_begin, dim3(uint32_t(w.n)), dim3(kBlock), 0, st, w);
+    hipLaunchKernelGGL(k_wide_bits, grid, dim3(kBlock), 0, st, w);
+    for (int32_t k = 0; k < w.max_steps; ++k) {
+        hipLaunchKernelGGL(k_wide_move, grid, block, 0, st, w, k);
+        if (w.link_s && w.link_w)
+            hipLaunchKernelGGL(k_wide_match, grid, dim3(kBlock), 0, st, w, k);
+        hipLaunchKernelGGL(k_wide_eat, grid, block, 0, st, w, k);
+        hipLaunchKernelGGL(k_wide_breed, grid, block, 0, st, w, k);
+    }
+    hipLaunchKernelGGL(k_wide_end, dim3(uint32_t(w.n)), dim3(64), 0, st, w);
+    return launch_status("predation_run_batched");
+}
+
 }  // namespace abm
 
 using namespace abm;
@@ -905,6 +1203,8 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
     a.G = G;
     a.claims = s->claims;
     a.status = w.status;
+    a.err = w.status - 1;
+    a.updates = nullptr;
     a.acc = w.acc;
     a.blist[0] = w.list_a;
     a.blist[1] = w.list_b;
@@ -916,6 +1216,7 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
     a.tiles[1] = static_cast<uint32_t>(tiles_for(p->cap_w, kTile));
     a.blocks[0] = blocks_of(a.tiles[0]);
     a.blocks[1] = blocks_of(a.tiles[1]);
+    a.turn = a.blocks[0] + a.blocks[1] <= 2048 ? 3 : 0;
     // status words: the breeder chains of both species, then their free-slot
     // chains, then the per-block free prefixes (int32) K2 leaves for K3; the
     // area is sized for 512-slot tiles, four times the chains of 2048-slot tiles
@@ -941,14 +1242,9 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
     // 0 every step when only one tag bit is left), and its last step re-arms
     // the table.  Short periods re-arm often enough to cost little (one
     // streamed table per 14 steps) and keep every multi-step call crossing them.
-    const int64_t max_cap = p->cap_s > p->cap_w ? p->cap_s : p->cap_w;
-    uint32_t sb = 1;
-    while (sb < 31 && (int64_t(1) << sb) < max_cap) ++sb;
-    const uint32_t tag_bits = 32 - sb < kTagBits ? 32 - sb : kTagBits;
-    const uint64_t t_max = (uint64_t(1) << tag_bits) - 1;
-    const uint64_t period = t_max > 1 ? t_max - 1 : 1;
-    a.sb = sb;
-    a.tag_mask = ~uint64_t(0) << (32 + sb);
+    const Tags tags = tags_for(p->cap_s > p->cap_w ? p->cap_s : p->cap_w);
+    a.sb = tags.sb;
+    a.tag_mask = ~uint64_t(0) << (32 + tags.sb);
 
     const int64_t words_s = int64_t(a.tiles[0]) * kOwners, words_w = int64_t(a.tiles[1]) * kOwners;
     int64_t edge = G > words_s ? G : words_s;
@@ -970,9 +1266,9 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
         a.mark_rd = w.hdr + kHdrMark + 2 * kMarkLanes * (k & 1);
         a.mark_wr = w.hdr + kHdrMark + 2 * kMarkLanes * ((k + 1) & 1);
         a.fold_row = s->stats && k > 0 ? s->stats + 8 * int64_t(k - 1) : nullptr;
-        const uint64_t phase = uint64_t(k) % period;
-        a.tag_hi = ((t_max > 1 ? t_max - 1 : 0) - phase) << (32 + sb);
-        a.rearm = phase == period - 1;
+        const uint32_t phase = uint32_t(k) % tags.period;
+        a.tag_hi = uint64_t(tags.top - phase) << (32 + tags.sb);
+        a.rearm = phase == tags.period - 1;
         hipLaunchKernelGGL(k_move_claim, grid, block, 0, st, a);
         if (a.multi)
             hipLaunchKernelGGL(k_prey_match, dim3(static_cast<uint32_t>(tiles_for(p->cap_w, kBlock))),

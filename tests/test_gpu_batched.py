@@ -498,3 +498,45 @@ def test_multi_prey_model_without_links_is_left_untouched(abm):
     d = b.descriptors()
     assert abm.workspace_error(b.ws) == 1
     assert (d[0].step, d[1].step) == (0, 5)
+
+
+# models beside teams: by launches over the whole device (up to 256 steps a run; several models
+# of more than one round of workgroups, an uneven one, matched by rank, one not a team's but too
+# wide for one workgroup's LDS, small ones), by teams (longer runs), with and without LDS
+@pytest.mark.parametrize("max_steps", [256, 257])
+@pytest.mark.parametrize("lds", [True, False])
+def test_large_models_side_by_side(abm, orc, max_steps, lds):
+    size = lambda W, H, **kw: dict(dict(W=W, H=H, cap_s=W * H, cap_w=W * H // 4, n_s0=W * H // 5,
+                                        n_w0=W * H // 20, seed=W), **kw)
+    kws = [size(450, 250), size(260, 170, multi_prey=1), size(190, 199, R=3, T_s=2 ** 31),
+           size(257, 100), size(300, 130, cap_w=1, n_w0=1), size(20, 30), size(64, 64)]
+    params = [abm.predation_params(**kw) for kw in kws]
+    b = abm.BatchedPredation(params, [31, 17, 31, 31, 31, 12, 31], team_size=2,
+                             team_min_size=80_000, lds=lds)
+    assert 1 <= b.team_models() <= 3
+    b.init()
+    done = [0] * len(kws)
+    for steps in (1, 15, max_steps):
+        b.run(steps)
+        countdown = b.grass_countdown()
+        for m, kw in enumerate(kws):
+            done[m] = min(done[m] + steps, [31, 17, 31, 31, 31, 12, 31][m])
+            _check_model(abm, orc, b, m, kw, done[m], countdown)
+    assert torch.equal(b.claims.view(torch.int64), torch.full_like(b.claims.view(torch.int64), -1))
+
+
+def test_large_models_replayed_from_a_graph(abm, orc):
+    """Recorded chunks of a batch with large models, eager work between the replays."""
+    kws = [dict(W=300, H=300, cap_s=60_000, cap_w=9_000, n_s0=9000, n_w0=2000, seed=k)
+           for k in range(3)] + [dict(W=40, H=40, cap_s=900, cap_w=200, n_s0=160, n_w0=40)]
+    b = abm.BatchedPredation([abm.predation_params(**kw) for kw in kws], 1000, team_size=4,
+                             team_min_size=100_000)
+    b.init()
+    g = b.capture(7, 2)
+    for replay in range(1, 4):
+        g.replay()
+        torch.zeros(1 << 20, device="cuda").add_(1)
+        torch.cuda.synchronize()
+        countdown = b.grass_countdown()
+        for m, kw in enumerate(kws):
+            _check_model(abm, orc, b, m, kw, 14 * replay, countdown)
