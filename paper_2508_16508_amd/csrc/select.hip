@@ -366,6 +366,54 @@ __device__ __forceinline__ void merge_dense(const SelArgs& a, int32_t* d, const 
     }
 }
 
+// The same for masked records, every array of the tile: the indices of a
+// batch's records are read once and kept for all arrays, not once per array
+// before each record (2^24 slots x 8 attributes, 15 % selected, half of the
+// records used: 315 to 222 us).
+__device__ __forceinline__ void merge_indirect(const SelArgs& a, int64_t tbase, uint32_t tile_excl,
+                                               uint32_t (&dsc)[8], uint32_t (&off)[8], int rows) {
+    const int32_t* const idx_of = a.rec_idx + int64_t(tile_excl);
+#pragma unroll
+    for (int jb = 0; jb < 8; jb += 4) {
+        if (jb >= rows) break;
+        int32_t idx[4][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t ab = (dsc[jb + j] >> 16) & 0xFu, rk = dsc[jb + j] & 0xFFFFu;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                idx[j][k] = (ab >> k) & 1u ? idx_of[rk + __popc(ab & low_bits(uint32_t(k)))] : 0;
+        }
+        for (int at = 0; at < a.n_true; ++at) {
+            const __amdgpu_buffer_rsrc_t rd =
+                __builtin_amdgcn_make_buffer_rsrc(a.dst[at] + tbase, 0, int(kTile * 4), kRsrcWord3);
+            const int32_t* const rec = a.rec[at];
+            v4i v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t dd = dsc[jb + j];
+                const bool need = (dd & kValid) && (dd & kAll) != kAll;
+                v[j] = __builtin_amdgcn_raw_buffer_load_b128(rd, need ? int(off[jb + j]) : kSkip, 0,
+                                                             kStreamPolicy);
+            }
+            int32_t x[4][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    x[j][k] = (dsc[jb + j] >> (16 + k)) & 1u ? rec[idx[j][k]] : 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if ((dsc[jb + j] >> (16 + k)) & 1u) v[j][k] = x[j][k];
+                __builtin_amdgcn_raw_buffer_store_b128(
+                    v[j], rd, (dsc[jb + j] & kValid) ? int(off[jb + j]) : kSkip, 0, kStreamPolicy);
+            }
+        }
+    }
+}
+
 // The listed lines of a tile, every attribute (and, for add_agents,
 // alive = 1 as one more).  A dense tile (more than 96 listed lines) runs the
 // arrays one after another with the whole block on each: thread t takes list
@@ -393,6 +441,10 @@ __device__ __forceinline__ void merge_tile(const SelArgs& a, int64_t tbase, uint
             off[j] = (line * 8u + k) * 16u;
         }
         const int rows = int((n_lines + kLinesPerPass - 1) / kLinesPerPass);
+        if constexpr (MODE == kSelIndirect) {
+            merge_indirect(a, tbase, tile_excl, dsc, off, rows);
+            return;
+        }
         for (int at = 0; at < a.n_true; ++at)
             merge_dense<MODE, false>(a, a.dst[at], a.rec[at], tbase, tile_excl, lim, dsc, off,
                                      rows);
