@@ -1005,15 +1005,15 @@ __global__ __launch_bounds__(kChipThreads) void k_batched_chip(BatchArgs a) {
         const int32_t t = run_on_chip<int16_t, false>(
             v, sh, reinterpret_cast<char*>(chip_lds), a.chip_bytes,
             a.scratch + int64_t(blockIdx.x) * a.scratch_stride, t0, t1, &st);
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == kChipKeeper) {
             d->step = t;
             d->updates += int64_t(st.updates);
             if (t < t1)
                 a.models[atomicAdd(a.queue + kSoloModels, 1u)].live_w = (int64_t(t1 - t) << 32) | m;
         }
-        // (without it the compiler joins this branch of thread 0 to the one the
-        // loop begins with and runs its lane apart from the wave's others, which
-        // then read the last model again, without end)
+        // (without it the compiler may join this branch to the one the loop begins
+        // with and run a lane apart from its wave's others, which then read the
+        // last model again, without end)
         __syncthreads();
     }
 }
@@ -1324,9 +1324,9 @@ namespace abm {
 // A small model advanced by one workgroup on the chip: every slot of both
 // species and every cell fit its LDS, so whatever the populations do the call
 // is one launch.  A step takes the workgroup less than the three dependent
-// launches of the general path: 6.0 us against 17.5 at 64 x 64 cells with 500
-// agents, 7.9 against 20.8 with 5120 (one step alone, from that state, 53 and
-// 53).  With many more slots than cells a first step can find several agents
+// launches of the general path: 5.4 us against 16.1 at 64 x 64 cells with 500
+// agents, 7.5 against 19.3 with 5120 (one step alone, from that state, 53 and
+// 49).  With many more slots than cells a first step can find several agents
 // in every cell, which one workgroup is slow at (20000 agents on 64 x 64 cells:
 // 183 us against 53), so past 1.5 slots a cell only models of up to 1024 slots
 // are taken.
@@ -1496,7 +1496,7 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     a.listed = 0;
     a.chip_bytes = 0;
     // Models of one workgroup go to the chip (4096 models of 32^2 to 256^2 cells
-    // x 50 steps: 50.4 to 8.9 ms), unless there are teams: they run in the time
+    // x 50 steps: 50.4 to 8.5 ms), unless there are teams: they run in the time
     // those take anyway, and a launch before them only delays the teams.
     a.wide = reinterpret_cast<uint8_t*>(a.team_counts);
     a.n_wide = 0;

@@ -27,15 +27,19 @@
 //                masks; contested agents are listed;
 //   B1 post      the listed agents post their keys;
 //   B2 settle    ... and read them back: outcomes, masks;
-//   S  scan      a thread per row: prefix sums of the rows' breeders and free slots;
+//   S  scan      a thread per row: prefix sums of the rows' breeders and free slots
+//                (the other half of the waves: the step's dead);
 //   C  renew     a thread per child: the j-th free slot takes the child of the
-//                j-th breeder; a thread per row: the next alive mask.
-// What bounds a step is the latency of its six barrier-separated parts (about
+//                j-th breeder; a thread per row, of the other half of the waves:
+//                the next alive mask.
+// What bounds a step is the latency of its six barrier-separated parts (under
 // 1 us each for one workgroup, whatever the model's size) and, for large
 // models, the instructions per row: 32 x 32 to 256 x 256 cells x 50 steps, 16
-// models a CU in turn, take 8.9 ms for 4096 models (50.4 ms by passes over
-// global memory); 64 x 64 cells x 200 steps take 1.13 ms (6.36 ms by three
-// launches a step).
+// models a CU in turn, take 8.5 ms for 4096 models (50.4 ms by passes over
+// global memory); 64 x 64 cells x 200 steps take 1.02 ms (6.36 ms by three
+// launches a step).  The busiest wave sets a part's time, so what does not
+// need the same rows goes to the other half of the waves (8.5 ms and 1.02 ms
+// against 8.9 and 1.15 with all of it on the first waves).
 #pragma once
 
 #include "rng.hpp"
@@ -56,6 +60,8 @@ constexpr int32_t kChipHash = 1024;           // entries of the contested table
 constexpr int32_t kChipPosts = 1536;          // a longer list (1 entry or fewer each) may not fit it
 constexpr int32_t kChipList = 1024;           // contested agents listed in LDS (the rest in scratch)
 constexpr uint32_t kChipNoOwner = 0xFFFFFFFFu;
+constexpr int32_t kChipMaxRows = kChipThreads / 2;   // a thread of half the waves per row
+constexpr int kChipKeeper = kChipThreads - 64;       // the thread that keeps the statistics
 
 // Bytes of LDS besides the rows, and per row of 64 slots.
 template <class E>
@@ -145,7 +151,8 @@ struct Chip {
         lane = tid & 63;
         wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         cells = v.W * v.H;
-        R_rows = int32_t((bytes - chip_fixed_bytes<E>(cells)) / chip_row_bytes<E>());
+        R_rows = min(int32_t((bytes - chip_fixed_bytes<E>(cells)) / chip_row_bytes<E>()),
+                     kChipMaxRows);
         char* p = lds;
         hval = reinterpret_cast<uint64_t*>(p);
         p += kChipHash * 8;
@@ -510,27 +517,25 @@ struct Chip {
         }
         if (sizeof(E) == 2 && __ballot(hot) && lane == 0) sh.bad = 1;
         // ---- S: the rows' breeders and free slots, and the step's dead
-        uint64_t a = 0, gone = 0, br = 0, dead = 0, f = 0;
-        int rs_s = 0;
-        int32_t rr = 0, row = 0;
+        // (the second half of the waves counts the dead meanwhile)
+        uint64_t br = 0, f = 0;
         if (tid < rows) {
-            rs_s = tid >= rs;
-            rr = rs_s ? tid - rs : tid;
-            row = row_at(rs_s, rr);
-            a = now[row];
-            gone = eaten[row];
+            const int rs_s = tid >= rs;
+            const int32_t r = rs_s ? tid - rs : tid, row = row_at(rs_s, r);
             br = breed[row];
-            dead = starve[row];
-            f = (~a | gone) & row_in_cap(pick(v.cap, rs_s), rr);
+            f = (~now[row] | eaten[row]) & row_in_cap(pick(v.cap, rs_s), r);
         }
         const uint32_t mine = uint32_t(__popcll(br)) << 16 | uint32_t(__popcll(f));
         const uint32_t incl = uint32_t(wave_incl_sum(int32_t(mine)));
-        if (wave * 64 < rows) {
-            const uint64_t any = __ballot((gone | dead) != 0);
-            if (any) {
+        if (wave >= kChipWaves / 2 && (wave - kChipWaves / 2) * 64 < rows) {
+            const int32_t q = tid - kChipThreads / 2;
+            const int s = q >= rs;
+            const int32_t row = row_at(s, s ? q - rs : q);
+            const uint64_t gone = q < rows ? eaten[row] : 0ull, dead = q < rows ? starve[row] : 0ull;
+            if (__ballot((gone | dead) != 0)) {
                 const int32_t g = wave_incl_sum(int32_t(__popcll(gone)));
-                const int32_t d0 = wave_incl_sum(rs_s ? 0 : int32_t(__popcll(dead)));
-                const int32_t d1 = wave_incl_sum(rs_s ? int32_t(__popcll(dead)) : 0);
+                const int32_t d0 = wave_incl_sum(s ? 0 : int32_t(__popcll(dead)));
+                const int32_t d1 = wave_incl_sum(s ? int32_t(__popcll(dead)) : 0);
                 if (lane == 63) {
                     if (g) atomicAdd(&sh.eaten, g);
                     if (d0) atomicAdd(&sh.starved[0], d0);
@@ -614,8 +619,10 @@ struct Chip {
                 }
             }
         }
-        // the next alive masks, and the rows they use
-        for (int32_t q = tid; q < end[0] + end[1]; q += kChipThreads) {
+        // the next alive masks, and the rows they use, by the second half of the
+        // waves (few steps have so many births that those bear children too)
+        if (wave >= kChipWaves / 2 && tid - kChipThreads / 2 < end[0] + end[1]) {
+            const int32_t q = tid - kChipThreads / 2;
             const int s = q >= end[0];
             const int32_t r = s ? q - end[0] : q, at = row_at(s, r);
             const int32_t first = s ? rs : 0, n = s ? rw : rs;
@@ -681,7 +688,7 @@ struct Chip {
 };
 
 // What the caller of run_on_chip keeps per step: live agents at its start and
-// its events (thread 0).
+// its events (thread kChipKeeper, whose wave has the fewest rows).
 struct ChipStats {
     int64_t* row;        // next statistics row, or null
     uint64_t updates;    // live agents summed over the steps' starts
@@ -713,7 +720,7 @@ __device__ __forceinline__ int32_t run_on_chip(const V& v, ChipShared& sh, char*
             __syncthreads();
         }
         go = c.step(uint32_t(t), base, par, count);
-        if (c.tid == 0) {
+        if (c.tid == kChipKeeper) {
             const int32_t ne = sh.eaten - eaten, n0 = sh.starved[0] - starved[0],
                           n1 = sh.starved[1] - starved[1];
             st->updates += uint64_t(live[0] + live[1]);
