@@ -61,9 +61,13 @@ constexpr uint32_t kDxPacked = 0x9224u;  // see predation.hip: dir -> dx + 1, 2 
 constexpr uint32_t kDyPacked = 0xA940u;
 
 // Words of the workspace header: the queues of the team models, of the models
-// of one workgroup and of those run on the chip, and the lengths of the lists
-// k_classify makes of the latter two.
-enum QueueWord : int { kQueueTeam = 0, kQueueSolo, kQueueChip, kChipModels, kSoloModels, kQueueWords };
+// of one workgroup and of those run on the chip (by size class), and the
+// lengths of the lists k_classify makes of the latter two.
+constexpr int kChipClasses = 3;
+enum QueueWord : int {
+    kQueueTeam = 0, kQueueSolo, kSoloModels, kQueueChip, kChipModels = kQueueChip + kChipClasses,
+    kQueueWords = kChipModels + kChipClasses
+};
 
 // Cells plus slots from which a model of one workgroup that does not fit the
 // chip joins the large ones (see launch_wide): one workgroup takes some 0.06 ms
@@ -86,7 +90,8 @@ struct BatchArgs {
     int32_t *wx, *wy, *we, *wa;
     uint32_t* queue;           // model queue counters (see QueueWord; reset before the launch)
     int32_t listed;            // the models of one workgroup come from the lists of k_classify
-    int32_t chip_bytes;        // LDS of a workgroup of k_batched_chip
+    int32_t chip_bytes[kChipClasses];   // LDS of a workgroup of k_batched_chip (0: class not used)
+    int64_t* chip_list[kChipClasses];   // models | steps << 32 (the last class: in the descriptors)
     uint8_t* wide;             // order[n_team, n_wide): taken by launch_wide (written by k_classify)
     int32_t n_wide;            // 0: none
     int32_t* scratch;          // per-workgroup breeder list
@@ -927,89 +932,125 @@ __global__ __launch_bounds__(1024) void k_batched_run(BatchArgs a) {
     }
 }
 
-// The models of one workgroup with steps to do, in launch order, as two lists:
-// those that may run on the chip (entry k in models[k].live_s) and the others
-// (models[k].live_w, with the steps it may run above bit 32).  The descriptors'
-// live counts are written when the run ends and serve as the lists' memory
-// until then.  One workgroup.
+// Whether a model of n0 agents at the start is tried on the chip by workgroups
+// of T threads.  Classes but the last (spare: half as many agents again) are
+// left by the models that outgrow them for the next one.
+template <int T>
+__device__ __forceinline__ bool chip_room(int64_t bytes, int64_t cells, int64_t n0, bool spare) {
+    int64_t rows = (bytes - chip_fixed_bytes<T>(cells)) / chip_row_bytes<int16_t>();
+    rows = rows < ChipSize<T>::kMaxRows ? rows : ChipSize<T>::kMaxRows;
+    return rows >= 2 && rows * 64 >= (spare ? n0 * 3 / 2 + 128 : n0 * 9 / 8);
+}
+
+// Entry k of a chip class's list, or of the list of the others.  (The
+// descriptors' live counts are written when the run ends; until then they hold
+// the lists of the last class, live_s, and of the others, live_w.)
+__device__ __forceinline__ int64_t& chip_entry(const BatchArgs& a, int c, uint32_t k) {
+    return c == kChipClasses - 1 ? a.models[k].live_s : a.chip_list[c][k];
+}
+
+// The models of one workgroup with steps to do, in launch order, as lists of
+// model | steps << 32: one per chip class, and the others.  One workgroup.
 __global__ __launch_bounds__(1024) void k_classify(BatchArgs a) {
-    __shared__ uint32_t s_cnt[2][16];
+    constexpr int kLists = kChipClasses + 1;
+    __shared__ uint32_t s_cnt[kLists][16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t n[2] = {0, 0};
+    uint32_t n[kLists] = {};
     for (int32_t i0 = a.n_team; i0 < a.n_models; i0 += 1024) {
         const int32_t i = i0 + int32_t(threadIdx.x);
-        int32_t m = 0;
-        bool chip = false, solo = false;
+        int32_t m = 0, list = -1;
         if (i < a.n_models) {
             m = a.order[i];
             const abm_model_desc& d = a.models[m];
-            const bool pending = d.steps_target > d.step;
-            const int64_t cells = int64_t(d.W) * d.H;
-            chip = pending && !d.multi_prey && d.W >= 1 && d.H >= 1 && d.W <= kChipSide &&
-                   d.H <= kChipSide && d.R >= 1 && d.R <= kChipMaxR && d.gain_s >= 0 &&
-                   d.gain_w >= 0 && d.gain_s <= kChipMaxGain && d.gain_w <= kChipMaxGain &&
-                   d.cap_s + d.cap_w <= a.scratch_stride;
-            // room for the rows of the initial agents and an eighth more
-            const int64_t rows = chip ? (int64_t(a.chip_bytes) - chip_fixed_bytes<int16_t>(cells)) /
-                                            chip_row_bytes<int16_t>() : 0;
-            chip = chip && rows >= 2 && rows * 64 >= (d.n_s0 + d.n_w0) * 9 / 8;
-            solo = pending && !chip;
+            const int64_t cells = int64_t(d.W) * d.H, n0 = d.n_s0 + d.n_w0;
+            const bool held = !d.multi_prey && d.W >= 1 && d.H >= 1 && d.W <= kChipSide &&
+                              d.H <= kChipSide && d.R >= 1 && d.R <= kChipMaxR && d.gain_s >= 0 &&
+                              d.gain_w >= 0 && d.gain_s <= kChipMaxGain &&
+                              d.gain_w <= kChipMaxGain && d.cap_s + d.cap_w <= a.scratch_stride;
+            list = kChipClasses;
+            if (held && chip_room<256>(a.chip_bytes[0], cells, n0, true))
+                list = 0;
+            else if (held && chip_room<512>(a.chip_bytes[1], cells, n0, true))
+                list = 1;
+            else if (held && chip_room<1024>(a.chip_bytes[2], cells, n0, false))
+                list = 2;
+            if (d.steps_target <= d.step) list = -1;
             if (i < a.n_wide) {
                 const int64_t size = cells + d.cap_s + d.cap_w;
-                const bool wide = solo && size >= kWideSize && d.cap_s + d.cap_w <= a.scratch_stride &&
+                const bool wide = list == kChipClasses && size >= kWideSize &&
+                                  d.cap_s + d.cap_w <= a.scratch_stride &&
                                   (!d.multi_prey || (a.link_s && a.link_w));
                 a.wide[i] = wide;
-                solo = solo && !wide;
+                if (wide) list = -1;
             }
         }
-        const uint64_t b[2] = {__ballot(chip), __ballot(solo)};
+        uint64_t b[kLists];
+#pragma unroll
+        for (int k = 0; k < kLists; ++k) b[k] = __ballot(list == k);
         __syncthreads();
         if (lane == 0)
-            for (int k = 0; k < 2; ++k) s_cnt[k][wave] = uint32_t(__popcll(b[k]));
+#pragma unroll
+            for (int k = 0; k < kLists; ++k) s_cnt[k][wave] = uint32_t(__popcll(b[k]));
         __syncthreads();
-        for (int k = 0; k < 2; ++k) {
+        const int64_t entry = (int64_t(a.max_steps) << 32) | m;
+#pragma unroll
+        for (int k = 0; k < kLists; ++k) {
             uint32_t at = n[k];
             for (int w = 0; w < wave; ++w) at += s_cnt[k][w];
             for (int w = 0; w < 16; ++w) n[k] += s_cnt[k][w];
             at += lane_rank(b[k]);
-            if (k == 0 && chip) a.models[at].live_s = m;
-            if (k == 1 && solo) a.models[at].live_w = (int64_t(a.max_steps) << 32) | m;
+            if (list == k) {
+                if (k < kChipClasses)
+                    chip_entry(a, k, at) = entry;
+                else
+                    a.models[at].live_w = entry;
+            }
         }
     }
     if (threadIdx.x == 0) {
-        a.queue[kChipModels] = n[0];
-        a.queue[kSoloModels] = n[1];
+#pragma unroll
+        for (int k = 0; k < kChipClasses; ++k) a.queue[kChipModels + k] = n[k];
+        a.queue[kSoloModels] = n[kChipClasses];
     }
 }
 
-// Models on the chip: one workgroup, and so one CU, per model.  A model that
-// does not fit, or outgrows the chip, goes (on) to the list of the others.
-__global__ __launch_bounds__(kChipThreads) void k_batched_chip(BatchArgs a) {
+// Models on the chip: one workgroup of T threads per model, class C.  A model
+// that does not fit, or outgrows its class, goes (on) to the list of the next,
+// and from the last one to that of the others.
+template <int T, int C>
+__global__ __launch_bounds__(T) void k_batched_chip(BatchArgs a) {
     extern __shared__ uint4 chip_lds[];
     __shared__ ChipShared sh;
-    __shared__ int32_t s_model;
+    __shared__ int32_t s_model, s_steps;
     for (;;) {
         if (threadIdx.x == 0) {
-            const uint32_t q = atomicAdd(a.queue + kQueueChip, 1u);
-            s_model = q < a.queue[kChipModels] ? int32_t(a.models[q].live_s) : -1;
+            const uint32_t q = atomicAdd(a.queue + kQueueChip + C, 1u);
+            const int64_t entry = q < a.queue[kChipModels + C] ? chip_entry(a, C, q) : -1;
+            s_model = int32_t(entry);
+            s_steps = int32_t(entry >> 32);
         }
         __syncthreads();
-        const int32_t m = s_model;
+        const int32_t m = s_model, steps = s_steps;
         __syncthreads();
         if (m < 0) return;
         abm_model_desc* d = a.models + m;
         const ModelView v = view_of(a, d);
         const int32_t t0 = d->step;
-        const int32_t t1 = d->steps_target - t0 > a.max_steps ? t0 + a.max_steps : d->steps_target;
+        const int32_t t1 = d->steps_target - t0 > steps ? t0 + steps : d->steps_target;
         ChipStats st = {nullptr, 0};
-        const int32_t t = run_on_chip<int16_t, false>(
-            v, sh, reinterpret_cast<char*>(chip_lds), a.chip_bytes,
+        const int32_t t = run_on_chip<T, int16_t, false>(
+            v, sh, reinterpret_cast<char*>(chip_lds), a.chip_bytes[C],
             a.scratch + int64_t(blockIdx.x) * a.scratch_stride, t0, t1, &st);
-        if (threadIdx.x == kChipKeeper) {
+        if (threadIdx.x == ChipSize<T>::kKeeper) {
             d->step = t;
             d->updates += int64_t(st.updates);
-            if (t < t1)
-                a.models[atomicAdd(a.queue + kSoloModels, 1u)].live_w = (int64_t(t1 - t) << 32) | m;
+            if (t < t1) {
+                const int64_t entry = (int64_t(t1 - t) << 32) | m;
+                if constexpr (C + 1 < kChipClasses)
+                    chip_entry(a, C + 1, atomicAdd(a.queue + kChipModels + C + 1, 1u)) = entry;
+                else
+                    a.models[atomicAdd(a.queue + kSoloModels, 1u)].live_w = entry;
+            }
         }
         // (without it the compiler may join this branch to the one the loop begins
         // with and run a lane apart from its wave's others, which then read the
@@ -1063,7 +1104,7 @@ __global__ __launch_bounds__(kChipThreads) void k_predation_small(SmallArgs a) {
     set_tags(v, a.cap[0] > a.cap[1] ? a.cap[0] : a.cap[1]);
     const int32_t t1 = a.t0 + a.n_steps;
     ChipStats st = {a.stats, 0};
-    const int32_t t = run_on_chip<int32_t, true>(v, sh, reinterpret_cast<char*>(chip_lds),
+    const int32_t t = run_on_chip<kChipThreads, int32_t, true>(v, sh, reinterpret_cast<char*>(chip_lds),
                                                  a.chip_bytes, a.scratch, a.t0, t1, &st);
     if (t == t1) return;
     const int64_t cells = int64_t(a.W) * a.H;
@@ -1223,7 +1264,12 @@ using namespace abm;
 // byte 248), the team area (barrier counter and model mailbox per team, member
 // counts per workgroup) and one breeder list (2 * max_cap ints) per workgroup.
 constexpr int64_t kTeamAreaWords = int64_t(kMaxWorkgroups) * (2 + kCountWords);
-constexpr int kMaxWideModels = kMaxWorkgroups;   // (a byte each in the team area's count words)
+// The count words of the team area hold a byte per wide model and two lists of
+// models on the chip when no team runs.
+constexpr int kMaxWideModels = kMaxWorkgroups;
+constexpr int64_t kChipListed = 9000;
+static_assert(2 * kMaxWideModels + 64 + 16 * kChipListed <=
+                  4 * int64_t(kMaxWorkgroups) * kCountWords, "the lists fit the count words");
 
 extern "C" size_t abm_batched_workspace_bytes(int64_t max_cap, int32_t n_workgroups) {
     if (max_cap < 1 || max_cap > (int64_t(1) << 30) || n_workgroups < 1 ||
@@ -1291,7 +1337,7 @@ bool run_shape(int items, int block, int* n_cu, int* per_cu, int64_t* lds_bytes)
     return true;
 }
 
-// Dynamic LDS a workgroup of the on-chip kernels can take on the current
+// Dynamic LDS a workgroup of the largest on-chip class can take on the current
 // device (the per-workgroup limit less their static LDS), looked up once per
 // device; 0 if a query fails.
 constexpr int kChipDevices = 64;
@@ -1306,7 +1352,8 @@ int chip_lds_bytes() {
         hipFuncAttributes fb, fs;
         if (hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
                 hipSuccess ||
-            hipFuncGetAttributes(&fb, reinterpret_cast<const void*>(k_batched_chip)) != hipSuccess ||
+            hipFuncGetAttributes(&fb, reinterpret_cast<const void*>(k_batched_chip<1024, 2>)) !=
+                hipSuccess ||
             hipFuncGetAttributes(&fs, reinterpret_cast<const void*>(k_predation_small)) != hipSuccess)
             return 0;
         const size_t fixed = fb.sharedSizeBytes > fs.sharedSizeBytes ? fb.sharedSizeBytes : fs.sharedSizeBytes;
@@ -1315,6 +1362,13 @@ int chip_lds_bytes() {
         g_chip_bytes[dev].store(n, std::memory_order_relaxed);
     }
     return n;
+}
+
+// ... and of a class of which `per_cu` workgroups are to share a CU: its part,
+// less the static LDS and an allocation unit.
+int chip_lds_part(int whole, int per_cu) {
+    const int n = (whole / per_cu - 2048) / 1024 * 1024;
+    return n > 0 ? n : 0;
 }
 
 }  // namespace
@@ -1338,7 +1392,7 @@ int launch_small_predation(const abm_predation_params* p, const abm_predation_st
         return ABM_OK;
     const int64_t cells = int64_t(p->W) * p->H;
     const int64_t rows = tiles_for(p->cap_s, 64) + tiles_for(p->cap_w, 64);
-    const int64_t need = chip_fixed_bytes<int32_t>(cells) + rows * chip_row_bytes<int32_t>();
+    const int64_t need = chip_fixed_bytes<kChipThreads>(cells) + rows * chip_row_bytes<int32_t>();
     const int bytes = chip_lds_bytes();
     const int64_t slots = p->cap_s + p->cap_w;
     if (need > bytes || (slots > 1024 && 2 * slots > 3 * cells)) return ABM_OK;
@@ -1494,9 +1548,12 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     hipLaunchKernelGGL(k_reset_queue, dim3((n_teams + 255) / 256 + 1), dim3(256), 0, st, a.queue,
                        a.team_ctr, n_teams);
     a.listed = 0;
-    a.chip_bytes = 0;
+    for (int c = 0; c < kChipClasses; ++c) {
+        a.chip_bytes[c] = 0;
+        a.chip_list[c] = nullptr;
+    }
     // Models of one workgroup go to the chip (4096 models of 32^2 to 256^2 cells
-    // x 50 steps: 50.4 to 8.5 ms), unless there are teams: they run in the time
+    // x 50 steps: 50.4 to 7.7 ms), unless there are teams: they run in the time
     // those take anyway, and a launch before them only delays the teams.
     a.wide = reinterpret_cast<uint8_t*>(a.team_counts);
     a.n_wide = 0;
@@ -1505,8 +1562,21 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
         const int chip = chip_lds_bytes();
         if (chip > 0) {
             a.listed = 1;
-            a.chip_bytes = chip;
             a.n_wide = n_wide;
+            a.chip_bytes[2] = chip;
+            // The smaller classes put two or four models on a CU, which pays when
+            // there are more models than CUs: a workgroup waits for the latency of
+            // its parts, and another one's fill the gaps (x 50 steps, in ms: 4096
+            // models of 32^2 to 64^2 cells 3.7 to 1.4, of 100^2 to 150^2 6.2 to 4.3,
+            // of 32^2 to 256^2 8.5 to 7.7; 300 of 100^2 to 150^2 0.73 to 0.60).
+            // Their lists lie behind the bytes of `wide`
+            const int64_t solo = b->n_models - n_team;
+            if (solo <= kChipListed && solo > n_cu) {
+                a.chip_list[1] = reinterpret_cast<int64_t*>(a.wide + 2 * kMaxWideModels + 64);
+                a.chip_list[0] = a.chip_list[1] + kChipListed;
+                a.chip_bytes[1] = chip_lds_part(chip, 2);
+                if (solo > 2 * n_cu) a.chip_bytes[0] = chip_lds_part(chip, 4);
+            }
             hipLaunchKernelGGL(k_classify, dim3(1), dim3(1024), 0, st, a);
         }
     }
@@ -1532,10 +1602,17 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
         if (rc != ABM_OK) return rc;
     }
     if (a.listed) {
-        const int solo = b->n_models - n_team;
-        const int wgs = n_cu < grid ? n_cu : grid;
-        hipLaunchKernelGGL(k_batched_chip, dim3(wgs < solo ? wgs : solo), dim3(kChipThreads),
-                           size_t(a.chip_bytes), st, a);
+        // (a share of the workspace each)
+        const int solo = b->n_models - n_team, most = solo < shares ? solo : int(shares);
+        const auto wgs = [&](int per_cu) { return dim3(per_cu * n_cu < most ? per_cu * n_cu : most); };
+        if (a.chip_bytes[0] > 0)
+            hipLaunchKernelGGL((k_batched_chip<256, 0>), wgs(4), dim3(256),
+                               size_t(a.chip_bytes[0]), st, a);
+        if (a.chip_bytes[1] > 0)
+            hipLaunchKernelGGL((k_batched_chip<512, 1>), wgs(2), dim3(512),
+                               size_t(a.chip_bytes[1]), st, a);
+        hipLaunchKernelGGL((k_batched_chip<1024, 2>), wgs(1), dim3(1024), size_t(a.chip_bytes[2]),
+                           st, a);
     }
     const size_t dyn = size_t(lds_bytes);
     if (grid > 0) switch (items) {

@@ -34,12 +34,12 @@
 //                the next alive mask.
 // What bounds a step is the latency of its six barrier-separated parts (under
 // 1 us each for one workgroup, whatever the model's size) and, for large
-// models, the instructions per row: 32 x 32 to 256 x 256 cells x 50 steps, 16
-// models a CU in turn, take 8.5 ms for 4096 models (50.4 ms by passes over
-// global memory); 64 x 64 cells x 200 steps take 1.02 ms (6.36 ms by three
+// models, the instructions per row: 4096 models of 32 x 32 to 256 x 256 cells x
+// 50 steps take 7.7 ms, the smaller ones two or four to a CU (50.4 ms by passes
+// over global memory); 64 x 64 cells x 200 steps take 1.02 ms (6.36 ms by three
 // launches a step).  The busiest wave sets a part's time, so what does not
-// need the same rows goes to the other half of the waves (8.5 ms and 1.02 ms
-// against 8.9 and 1.15 with all of it on the first waves).
+// need the same rows goes to the other half of the waves (1.02 ms against 1.15
+// with all of it on the first ones).
 #pragma once
 
 #include "rng.hpp"
@@ -49,25 +49,32 @@
 namespace abm {
 namespace {
 
-constexpr int kChipThreads = 1024;
-constexpr int kChipWaves = kChipThreads / 64;
+constexpr int kChipThreads = 1024;            // of the largest workgroup
 constexpr int32_t kChipSide = 256;            // positions are 8 + 8 bits
 constexpr int32_t kChipReadyMax = 254;        // a regrowth byte above it does not fit
 constexpr int32_t kChipMaxR = 200;            // leaves 55 steps at least between two rebasings
 constexpr int32_t kChipMaxGain = 8192;
 constexpr int32_t kChipEnergyMax = 16384;     // a 16-bit energy above it ends the on-chip run
-constexpr int32_t kChipHash = 1024;           // entries of the contested table
-constexpr int32_t kChipPosts = 1536;          // a longer list (1 entry or fewer each) may not fit it
-constexpr int32_t kChipList = 1024;           // contested agents listed in LDS (the rest in scratch)
 constexpr uint32_t kChipNoOwner = 0xFFFFFFFFu;
-constexpr int32_t kChipMaxRows = kChipThreads / 2;   // a thread of half the waves per row
-constexpr int kChipKeeper = kChipThreads - 64;       // the thread that keeps the statistics
+
+// What a workgroup of T threads works with.
+template <int T>
+struct ChipSize {
+    static constexpr int32_t kWaves = T / 64;
+    static constexpr int32_t kHash = T;              // entries of the contested table
+    static constexpr int32_t kHashBits = T == 1024 ? 10 : (T == 512 ? 9 : 8);
+    static constexpr int32_t kPosts = T + T / 2;     // a longer list (1 entry or fewer each) may not fit it
+    static constexpr int32_t kList = T;              // contested agents listed in LDS (the rest in scratch)
+    static constexpr int32_t kMaxRows = T / 2;       // a thread of half the waves per row
+    static constexpr int kKeeper = T - 64;           // the thread that keeps the statistics
+    static_assert(kHash == 1 << kHashBits, "the hash yields kHashBits bits");
+};
 
 // Bytes of LDS besides the rows, and per row of 64 slots.
-template <class E>
+template <int T>
 __host__ __device__ __forceinline__ int64_t chip_fixed_bytes(int64_t cells) {
     const int64_t occ = (cells + 31) / 32 * 16, rdy = (cells + 15) / 16 * 16;
-    return occ + rdy + int64_t(kChipHash) * 12 + int64_t(kChipList) * 4 + 8;
+    return occ + rdy + int64_t(ChipSize<T>::kHash) * 12 + int64_t(ChipSize<T>::kList) * 4 + 8;
 }
 template <class E>
 __host__ __device__ __forceinline__ int64_t chip_row_bytes() {
@@ -77,7 +84,7 @@ __host__ __device__ __forceinline__ int64_t chip_row_bytes() {
 // What a launch keeps of a model in the workgroup's static LDS.
 struct ChipShared {
     int32_t rows[2][2];          // rows in use per species, by step parity
-    uint32_t wsum[kChipWaves];
+    uint32_t wsum[kChipThreads / 64];
     int32_t n_list, over, bad, armed;
     int32_t live[2];             // live agents per species
     int32_t eaten, starved[2], grass;
@@ -124,12 +131,13 @@ __device__ __forceinline__ T pick(const T (&a)[2], int s) {
     return s ? a[1] : a[0];
 }
 
-// A model on the chip.  V: its view (parameters and global arrays); E: the
+// A model on the chip, T threads.  V: its view (parameters and global arrays); E: the
 // type of an energy in LDS (int16_t, with a bound that ends the run, or
 // int32_t).  COUNTDOWN: the grass array holds countdowns instead of the steps
 // at which cells are grown.
-template <class V, class E, bool COUNTDOWN>
-struct Chip {
+template <int T, class V, class E, bool COUNTDOWN>
+struct Chip : ChipSize<T> {
+    using Z = ChipSize<T>;
     const V& v;
     ChipShared& sh;
     int32_t cells, R_rows;       // rows that fit
@@ -151,11 +159,11 @@ struct Chip {
         lane = tid & 63;
         wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         cells = v.W * v.H;
-        R_rows = min(int32_t((bytes - chip_fixed_bytes<E>(cells)) / chip_row_bytes<E>()),
-                     kChipMaxRows);
+        R_rows = min(int32_t((bytes - chip_fixed_bytes<T>(cells)) / chip_row_bytes<E>()),
+                     Z::kMaxRows);
         char* p = lds;
         hval = reinterpret_cast<uint64_t*>(p);
-        p += kChipHash * 8;
+        p += Z::kHash * 8;
         alive = reinterpret_cast<uint64_t*>(p);
         p += 2 * 8 * int64_t(R_rows);
         eaten = reinterpret_cast<uint64_t*>(p);
@@ -173,9 +181,9 @@ struct Chip {
         rdy = reinterpret_cast<uint8_t*>(p);
         p += (int64_t(cells) + 15) / 16 * 16;
         hown = reinterpret_cast<uint32_t*>(p);
-        p += kChipHash * 4;
+        p += Z::kHash * 4;
         list = reinterpret_cast<uint32_t*>(p);
-        p += kChipList * 4;
+        p += Z::kList * 4;
         en = reinterpret_cast<E*>(p);
         p += 64 * int64_t(sizeof(E)) * R_rows;
         pos = reinterpret_cast<uint16_t*>(p);
@@ -191,10 +199,10 @@ struct Chip {
 
     __device__ __forceinline__ void clear_cells() {
         uint4* o = reinterpret_cast<uint4*>(occ);
-        for (int32_t i = tid; i < (cells + 31) / 32; i += kChipThreads) o[i] = uint4{0, 0, 0, 0};
+        for (int32_t i = tid; i < (cells + 31) / 32; i += T) o[i] = uint4{0, 0, 0, 0};
     }
     __device__ __forceinline__ void clear_table() {
-        for (int32_t i = tid; i < kChipHash; i += kChipThreads) {
+        for (int32_t i = tid; i < Z::kHash; i += T) {
             hval[i] = ~0ull;
             hown[i] = kChipNoOwner;
         }
@@ -215,7 +223,7 @@ struct Chip {
         }
         __syncthreads();
         bool bad = false;
-        for (int32_t i = tid; i < (cells + 3) / 4; i += kChipThreads) {
+        for (int32_t i = tid; i < (cells + 3) / 4; i += T) {
             uint32_t w = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -237,23 +245,23 @@ struct Chip {
             const int32_t n = (pick(v.cap, s) + 63) / 64;
             int32_t top = 0;
             constexpr int kAhead = 8;
-            for (int32_t r0 = wave; r0 < n; r0 += kChipWaves * kAhead) {
+            for (int32_t r0 = wave; r0 < n; r0 += Z::kWaves * kAhead) {
                 int32_t a[kAhead];
 #pragma unroll
                 for (int q = 0; q < kAhead; ++q) {
-                    const int32_t r = r0 + q * kChipWaves, i = r * 64 + lane;
+                    const int32_t r = r0 + q * Z::kWaves, i = r * 64 + lane;
                     a[q] = r < n && i < pick(v.cap, s) ? pick(v.al, s)[i] : 0;
                 }
 #pragma unroll
                 for (int q = 0; q < kAhead; ++q)
-                    if (__ballot(a[q] != 0)) top = r0 + q * kChipWaves + 1;
+                    if (__ballot(a[q] != 0)) top = r0 + q * Z::kWaves + 1;
             }
             if (lane == 0) atomicMax(&sh.mark[s], top);
         }
         __syncthreads();
         const int32_t rs = sh.mark[0], rw = sh.mark[1];
         if (rs + rw > R_rows) return false;            // (uniform: read from LDS)
-        for (int32_t i = tid; i < R_rows; i += kChipThreads) {
+        for (int32_t i = tid; i < R_rows; i += T) {
             alive[i] = 0;
             alive[R_rows + i] = 0;
             born[i] = 0;
@@ -261,7 +269,7 @@ struct Chip {
         clear_cells();
         clear_table();
         __syncthreads();
-        for (int32_t q = wave; q < rs + rw; q += kChipWaves) {
+        for (int32_t q = wave; q < rs + rw; q += Z::kWaves) {
             const int s = q >= rs;
             const int32_t r = s ? q - rs : q, i = r * 64 + lane, at = row_at(s, r);
             const bool in = i < pick(v.cap, s);
@@ -291,7 +299,7 @@ struct Chip {
     // hold R or more and go to the global array (COUNTDOWN: the array is only
     // written at the end).
     __device__ __forceinline__ void rebase(int32_t from, int32_t to) {
-        for (int32_t i = tid; i < (cells + 3) / 4; i += kChipThreads) {
+        for (int32_t i = tid; i < (cells + 3) / 4; i += T) {
             uint32_t w = reinterpret_cast<uint32_t*>(rdy)[i], out = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -307,7 +315,7 @@ struct Chip {
     // Writes the state back after the last step (rows[] of its parity), at
     // step t with base `base`.
     __device__ __forceinline__ void store(int32_t base, int32_t t, int par, const int32_t (&rows0)[2]) {
-        for (int32_t i = tid; i < (cells + 3) / 4; i += kChipThreads) {
+        for (int32_t i = tid; i < (cells + 3) / 4; i += T) {
             const uint32_t w = reinterpret_cast<uint32_t*>(rdy)[i];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -322,7 +330,7 @@ struct Chip {
             }
         }
         const int32_t ms = sh.max_rows[0], mw = sh.max_rows[1];
-        for (int32_t q = wave; q < ms + mw; q += kChipWaves) {
+        for (int32_t q = wave; q < ms + mw; q += Z::kWaves) {
             const int s = q >= ms;
             const int32_t r = s ? q - ms : q, i = r * 64 + lane, at = row_at(s, r);
             const bool open = r < sh.rows[par][s];     // (rows past it hold no live agent)
@@ -345,10 +353,9 @@ struct Chip {
         return (uint64_t(draw(skey, uint32_t(slot), purpose)) << 32) | uint32_t(slot);
     }
     __device__ __forceinline__ uint32_t hash(uint32_t id) const {
-        return (id * 2654435761u) >> (32 - 10);
+        return (id * 2654435761u) >> (32 - Z::kHashBits);
     }
     __device__ __forceinline__ void post(uint32_t id, uint64_t k) {
-        static_assert(kChipHash == 1024, "hash() yields 10 bits");
         uint32_t h = hash(id);
         for (int probe = 0; probe < 64; ++probe) {
             const uint32_t o = atomicCAS(&hown[h], kChipNoOwner, id);
@@ -356,7 +363,7 @@ struct Chip {
                 claim_min_lds(&hval[h], k);
                 return;
             }
-            h = (h + 1) & (kChipHash - 1);
+            h = (h + 1) & (Z::kHash - 1);
         }
         sh.over = 1;
     }
@@ -364,13 +371,13 @@ struct Chip {
         uint32_t h = hash(id);
         for (int probe = 0; probe < 64; ++probe) {
             if (hown[h] == id) return hval[h];
-            h = (h + 1) & (kChipHash - 1);
+            h = (h + 1) & (Z::kHash - 1);
         }
         return ~0ull;
     }
     __device__ __forceinline__ uint32_t listed(int32_t q) const {
-        uint32_t w = list[q < kChipList ? q : 0];
-        if (q >= kChipList) w = uint32_t(spill[q - kChipList]);
+        uint32_t w = list[q < Z::kList ? q : 0];
+        if (q >= Z::kList) w = uint32_t(spill[q - Z::kList]);
         return w;
     }
 
@@ -385,7 +392,7 @@ struct Chip {
         uint64_t* const now = alive + par * R_rows;
         uint64_t* const next = alive + (par ^ 1) * R_rows;
         // ---- A: move
-        for (int32_t q = wave; q < rows; q += kChipWaves) {
+        for (int32_t q = wave; q < rows; q += Z::kWaves) {
             const int s = q >= rs;
             const int32_t r = s ? q - rs : q, at = row_at(s, r);
             if (!((now[at] >> lane) & 1)) continue;
@@ -404,7 +411,7 @@ struct Chip {
         const int32_t now_rel = int32_t(t) - base;
         uint32_t ate = 0;
         bool hot = false;                              // an energy near the end of its type
-        for (int32_t q = wave; q < rows; q += kChipWaves) {
+        for (int32_t q = wave; q < rows; q += Z::kWaves) {
             const int s = q >= rs;
             const int32_t r = s ? q - rs : q, at = row_at(s, r), i = r * 64 + lane;
             const bool on = (now[at] >> lane) & 1;
@@ -444,7 +451,7 @@ struct Chip {
                 if (contested) {
                     const uint32_t w = uint32_t(at * 64 + lane) | (s ? 1u << 20 : 0u) |
                                        (grown ? 1u << 21 : 0u) | (nib & 4u ? 1u << 22 : 0u);
-                    if (n0 < kChipList) list[n0] = w; else spill[n0 - kChipList] = int32_t(w);
+                    if (n0 < Z::kList) list[n0] = w; else spill[n0 - Z::kList] = int32_t(w);
                 }
             }
         }
@@ -453,7 +460,7 @@ struct Chip {
         bool global = false;
         if (n_list > 0) {
             // ---- B1: post
-            for (int32_t q = tid; q < n_list && n_list <= kChipPosts; q += kChipThreads) {
+            for (int32_t q = tid; q < n_list && n_list <= Z::kPosts; q += T) {
                 const uint32_t w = listed(q);
                 const int32_t at = int32_t(w & 0xFFFFFu);
                 const bool wolf = w & (1u << 20);
@@ -467,10 +474,10 @@ struct Chip {
                 }
             }
             __syncthreads();
-            global = n_list > kChipPosts || __builtin_amdgcn_readfirstlane(sh.over) != 0;
+            global = n_list > Z::kPosts || __builtin_amdgcn_readfirstlane(sh.over) != 0;
             if (global) post_global(skey, n_list);
             // ---- B2: settle
-            for (int32_t q = tid; q < n_list; q += kChipThreads) {
+            for (int32_t q = tid; q < n_list; q += T) {
                 const uint32_t w = listed(q);
                 const int32_t at = int32_t(w & 0xFFFFFu);
                 const bool wolf = w & (1u << 20);
@@ -505,7 +512,7 @@ struct Chip {
             __syncthreads();
         }
         if (global)                                    // (every read is behind the barrier)
-            for (int32_t q = tid; q < n_list; q += kChipThreads) {
+            for (int32_t q = tid; q < n_list; q += T) {
                 uint64_t* cw = v.claims + 3 * int64_t(cell_of(pos[listed(q) & 0xFFFFFu]));
                 rearm(cw);
                 rearm(cw + 1);
@@ -527,8 +534,8 @@ struct Chip {
         }
         const uint32_t mine = uint32_t(__popcll(br)) << 16 | uint32_t(__popcll(f));
         const uint32_t incl = uint32_t(wave_incl_sum(int32_t(mine)));
-        if (wave >= kChipWaves / 2 && (wave - kChipWaves / 2) * 64 < rows) {
-            const int32_t q = tid - kChipThreads / 2;
+        if (wave >= Z::kWaves / 2 && (wave - Z::kWaves / 2) * 64 < rows) {
+            const int32_t q = tid - T / 2;
             const int s = q >= rs;
             const int32_t row = row_at(s, s ? q - rs : q);
             const uint64_t gone = q < rows ? eaten[row] : 0ull, dead = q < rows ? starve[row] : 0ull;
@@ -547,7 +554,7 @@ struct Chip {
         if (tid < 2) sh.rows[par ^ 1][tid] = 0;
         __syncthreads();
         {
-            const uint32_t w = lane < kChipWaves ? sh.wsum[lane] : 0u;
+            const uint32_t w = lane < Z::kWaves ? sh.wsum[lane] : 0u;
             const int32_t wi = wave_incl_sum(int32_t(w));
             const uint32_t before = wave ? uint32_t(__builtin_amdgcn_readlane(wi, wave - 1)) : 0u;
             if (tid < rows) pre[tid] = before + incl - mine;
@@ -578,7 +585,7 @@ struct Chip {
             end[0] = min(end[0], had[0]);
             end[1] = min(end[1], had[1]);
         }
-        for (int32_t j = tid; j < births[0] + births[1]; j += kChipThreads) {
+        for (int32_t j = tid; j < births[0] + births[1]; j += T) {
             const int s = j >= births[0];
             const int32_t jj = s ? j - births[0] : j;
             const int32_t first = s ? rs : 0, n = s ? rw : rs;
@@ -621,8 +628,8 @@ struct Chip {
         }
         // the next alive masks, and the rows they use, by the second half of the
         // waves (few steps have so many births that those bear children too)
-        if (wave >= kChipWaves / 2 && tid - kChipThreads / 2 < end[0] + end[1]) {
-            const int32_t q = tid - kChipThreads / 2;
+        if (wave >= Z::kWaves / 2 && tid - T / 2 < end[0] + end[1]) {
+            const int32_t q = tid - T / 2;
             const int s = q >= end[0];
             const int32_t r = s ? q - end[0] : q, at = row_at(s, r);
             const int32_t first = s ? rs : 0, n = s ? rw : rs;
@@ -664,12 +671,12 @@ struct Chip {
     // are performed before the barrier that ends each part.
     __device__ __forceinline__ void post_global(uint64_t skey, int32_t n_list) {
         if (COUNTDOWN && sh.armed == 0) {
-            for (int64_t w = tid; w < 3 * int64_t(cells); w += kChipThreads) rearm(v.claims + w);
+            for (int64_t w = tid; w < 3 * int64_t(cells); w += T) rearm(v.claims + w);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         if (tid == 0) sh.armed = 1;
-        for (int32_t q = tid; q < n_list; q += kChipThreads) {
+        for (int32_t q = tid; q < n_list; q += T) {
             const uint32_t w = listed(q);
             const int32_t at = int32_t(w & 0xFFFFFu);
             const bool wolf = w & (1u << 20);
@@ -688,7 +695,7 @@ struct Chip {
 };
 
 // What the caller of run_on_chip keeps per step: live agents at its start and
-// its events (thread kChipKeeper, whose wave has the fewest rows).
+// its events (thread ChipSize<T>::kKeeper, whose wave has the fewest rows).
 struct ChipStats {
     int64_t* row;        // next statistics row, or null
     uint64_t updates;    // live agents summed over the steps' starts
@@ -697,11 +704,11 @@ struct ChipStats {
 // Advances model v from step t0 towards t1 on the chip; returns the step
 // reached (t0 if the model does not fit; less than t1 if its rows or energies
 // outgrew the chip).  The global state is current when it returns.
-template <class E, bool COUNTDOWN, class V>
+template <int T, class E, bool COUNTDOWN, class V>
 __device__ __forceinline__ int32_t run_on_chip(const V& v, ChipShared& sh, char* lds, int64_t bytes,
                                                int32_t* scratch, int32_t t0, int32_t t1,
                                                ChipStats* st) {
-    Chip<V, E, COUNTDOWN> c(v, sh, lds, bytes, scratch);
+    Chip<T, V, E, COUNTDOWN> c(v, sh, lds, bytes, scratch);
     if (c.R_rows < 2 || !c.load(t0)) {
         __syncthreads();
         return t0;
@@ -720,7 +727,7 @@ __device__ __forceinline__ int32_t run_on_chip(const V& v, ChipShared& sh, char*
             __syncthreads();
         }
         go = c.step(uint32_t(t), base, par, count);
-        if (c.tid == kChipKeeper) {
+        if (c.tid == ChipSize<T>::kKeeper) {
             const int32_t ne = sh.eaten - eaten, n0 = sh.starved[0] - starved[0],
                           n1 = sh.starved[1] - starved[1];
             st->updates += uint64_t(live[0] + live[1]);

@@ -201,3 +201,35 @@ def test_one_model_replayed_from_a_graph(abm, orc):
         g.replay()
         torch.cuda.synchronize()
         _check(dict(grass=m.grass, sheep=m.sheep, wolves=m.wolves), S, 5)
+
+
+# more models than CUs (two share one), and than twice as many (four do); some of every size
+# class, some that outgrow the smaller ones during a run, runs of 1, 6 and 30 steps
+@pytest.mark.parametrize("n", [300, 700])
+def test_size_classes(abm, orc, n):
+    g = np.random.default_rng(n)
+    kws = []
+    for k in range(n):
+        side = int(g.choice([8, 20, 60, 100, 140])) if k % 40 else 220
+        cells = side * side
+        grows = k % 5 == 0
+        kws.append(dict(W=side, H=side + k % 3, seed=k, cap_s=4 * cells, cap_w=cells,
+                        n_s0=cells // 8, n_w0=cells // 40, R=2 if grows else 30,
+                        T_s=2 ** 31 if grows else 171798691))
+    b = abm.BatchedPredation([abm.predation_params(**kw) for kw in kws], 100)
+    b.init()
+    states = [(orc.pred_params(**kw),) for kw in kws]
+    states = [(p, orc.predation_init(p)) for (p,) in states]
+    updates = np.zeros(n, np.int64)
+    for steps in (1, 6, 30):
+        b.run(steps)
+        countdown, desc = b.grass_countdown(), b.descriptors()
+        check = range(n) if steps < 30 else range(0, n, 7)
+        for m, (p, s) in enumerate(states):
+            if m not in check:
+                continue
+            updates[m] += sum(r["live_s"] + r["live_w"] for r in orc.predation_run(p, s, steps))
+            grass, sheep, wolves = b.model_state(m, countdown)
+            _check(dict(grass=grass.reshape(s.grass.shape), sheep=sheep, wolves=wolves), s,
+                   (m, steps))
+            assert desc[m].step == s.step and desc[m].updates == updates[m]
