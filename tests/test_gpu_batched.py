@@ -540,3 +540,24 @@ def test_large_models_replayed_from_a_graph(abm, orc):
         countdown = b.grass_countdown()
         for m, kw in enumerate(kws):
             _check_model(abm, orc, b, m, kw, 14 * replay, countdown)
+
+
+@pytest.mark.parametrize("n_models", [1, 65, 4097])
+def test_initial_states_at_every_offset(abm, orc, n_models):
+    """The state is streamed from line starts by a share of workgroups that
+    depends on the number of models: every word of every model is written, at
+    whatever offset in a line its arrays begin, over poisoned arrays."""
+    kws = _mixed_models(n_models, n_models)
+    kws[0].update(W=211, H=307, cap_s=20011, cap_w=4999, n_s0=7001, n_w0=1777)
+    batch = abm.BatchedPredation([abm.predation_params(**kw) for kw in kws], 1)
+    for t in (batch.ready, *batch.sheep.values(), *batch.wolves.values()):
+        t.fill_(-7)
+    batch.claims.view(torch.int64).fill_(5)
+    batch.init()
+    states = [orc.predation_init(orc.pred_params(**kw)) for kw in kws]
+    assert np.array_equal(_host(batch.grass_countdown()), np.concatenate([s.grass for s in states]))
+    assert bool((batch.claims.view(torch.int64) == -1).all())
+    for name in ("sheep", "wolves"):
+        for f in FIELDS:
+            want = np.concatenate([getattr(s, name)[f] for s in states])
+            assert np.array_equal(_host(getattr(batch, name)[f]), want), (name, f)
