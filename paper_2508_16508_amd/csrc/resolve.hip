@@ -137,11 +137,8 @@ __global__ __launch_bounds__(kMoveThreads) void k_range_count(RangeArgs a) {
     hist[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kMoveItems; ++k) {
-        const int64_t c = int64_t(t) * kMoveTile + k * kMoveThreads + threadIdx.x;
+    for (int k = 0; k < kMoveItems; ++k)
         if ((live >> k) & 1u) atomicAdd(&hist[uint32_t(tg[k]) >> a.shift], 1u);
-        if (c < a.n_claims) a.won[c] = 0;
-    }
     for (int64_t i = int64_t(t) * kMoveThreads + threadIdx.x; i < a.n_targets;
          i += int64_t(gridDim.x) * kMoveThreads)
         a.best[i] = ~0ull;
@@ -178,6 +175,9 @@ __global__ __launch_bounds__(kMoveThreads) void k_range_move(RangeArgs a) {
     for (int k = 0; k < kMoveItems; ++k) {
         const int64_t c = c0 + k * kMoveThreads;
         pr[k] = a.prio[c < a.n_claims ? c : a.n_claims - 1];
+        // (here and not in the count: won may be the array that active is, and
+        // every claim counted has to be moved)
+        if (c < a.n_claims) a.won[c] = 0;
     }
     const uint32_t before_tile = a.counts[int64_t(threadIdx.x) * a.n_tiles + t];
     const uint32_t total = a.totals[threadIdx.x];

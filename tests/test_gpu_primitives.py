@@ -270,6 +270,24 @@ def test_resolve_conflicts_partitioned(abm, orc, n_targets, crowded):
     assert np.array_equal(host(won), ewon)
 
 
+# posted by atomics, and partitioned by target
+@pytest.mark.parametrize("n", [5000, (1 << 20) + 777])
+def test_resolve_conflicts_won_over_active(abm, orc, n):
+    """The claims' own flags receive the outcome: every claim reads its flag
+    before its outcome replaces it."""
+    nt = n // 3
+    g = np.random.default_rng(n)
+    target = g.integers(0, nt, size=n).astype(np.int32)
+    prio = g.integers(0, 99, size=n).astype(np.uint32)
+    active = (g.random(n) < 0.7).astype(np.uint8)
+    eb, ew, ewon = orc.resolve_conflicts(target, prio, nt, active=active)
+    flags = dev(active)
+    best, winner, won = abm.resolve_conflicts(dev(target), dev(prio.view(np.int32)).view(torch.uint32),
+                                              nt, active=flags, won=flags)
+    assert won is flags and np.array_equal(host(flags), ewon)
+    assert np.array_equal(host(best), eb) and np.array_equal(host(winner), ew)
+
+
 def test_resolve_conflicts_partitioned_on_a_side_stream(abm, orc):
     n, nt = 1 << 20, 50_000
     g = np.random.default_rng(8)
