@@ -903,6 +903,7 @@ __global__ __launch_bounds__(1024) void k_batched_run(BatchArgs a) {
             __syncthreads();
             if (m < 0) break;
             if (!run_model<ITEMS>(a, m, a.max_steps, tm, lds)) return;
+            __syncthreads();   // (thread 0 rejoins its wave: see k_batched_chip)
         }
     }
     tm.K = 1;
