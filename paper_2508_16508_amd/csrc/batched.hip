@@ -254,7 +254,8 @@ struct ModelView {
     uint64_t tag_mask;           // the tag field and the bits above it
     int32_t cap[2];
     int32_t* link[2];            // list links (multi), per species
-    int32_t* ready;
+    int32_t* ready;              // per cell the step, less `base`, at which it is grown
+    int32_t base;
     uint64_t* claims;
     int32_t *x[2], *y[2], *e[2], *al[2];
 };
@@ -470,7 +471,7 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
                 const int64_t c = int64_t(y) * v.W + x;
                 uint64_t* cw = claims + 3 * c;
                 if (s == 0) {
-                    if (v.ready[c] <= int32_t(t))
+                    if (v.ready[c] <= int32_t(t) - v.base)
                         post(cw + 0, tagged_key(tag_hi, sb, skey, i, kSheepGrassKey));
                     if (v.multi)
                         push(cw + 1, i, v.link[0]);
@@ -532,7 +533,7 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
                         if (rd(cw + 0) == tagged_key(tag_hi, sb, skey, i, kSheepGrassKey)) {
                             e += v.gain[0];
                             v.e[0][i] = e;
-                            v.ready[c] = int32_t(t) + v.R;
+                            v.ready[c] = int32_t(t) - v.base + v.R;
                             if (counts) atomicAdd(&counts->grass, 1);
                         }
                         if (v.multi) {
@@ -725,6 +726,7 @@ __device__ ModelView view_of(const BatchArgs& a, const abm_model_desc* d) {
     v.cap[0] = int32_t(d->cap_s);
     v.cap[1] = int32_t(d->cap_w);
     v.ready = a.ready + d->cell_off;
+    v.base = 0;
     v.claims = a.claims + 3 * d->cell_off;
     v.x[0] = a.sx + d->sheep_off;
     v.y[0] = a.sy + d->sheep_off;
@@ -1109,9 +1111,8 @@ __global__ __launch_bounds__(kChipThreads) void k_predation_small(SmallArgs a) {
                                                  a.chip_bytes, a.scratch, a.t0, t1, &st);
     if (t == t1) return;
     const int64_t cells = int64_t(a.W) * a.H;
-    for (int64_t c = threadIdx.x; c < cells; c += blockDim.x)
-        v.ready[c] = int32_t(uint32_t(t) + uint32_t(v.ready[c]));
     for (int64_t w = threadIdx.x; w < 3 * cells; w += blockDim.x) rearm(v.claims + w);
+    v.base = t;               // the countdowns as they are: no sum that could overflow
     Team tm = {};
     tm.K = 1;
     tm.scratch = a.scratch;
@@ -1139,8 +1140,8 @@ __global__ __launch_bounds__(kChipThreads) void k_predation_small(SmallArgs a) {
         __syncthreads();
     }
     for (int64_t c = threadIdx.x; c < cells; c += blockDim.x) {
-        const int32_t d = int32_t(uint32_t(v.ready[c]) - uint32_t(t1));
-        v.ready[c] = d > 0 ? d : 0;
+        const int64_t d = int64_t(v.ready[c]) - (t1 - t);
+        v.ready[c] = d > 0 ? int32_t(d) : 0;
     }
 }
 

@@ -179,6 +179,38 @@ def test_agents_off_the_grid(abm, orc):
             assert torch.equal(wolves[f], out[0][2][f])
 
 
+# agents off the grid send the model to global memory
+@pytest.mark.parametrize("off_grid", [False, True])
+def test_cells_that_never_grow(abm, orc, off_grid):
+    """Countdowns of 2^31 - 1 set in the middle of a run: no cell of them is eaten,
+    whichever path runs the model."""
+    P, S = _state(orc, {}, None)
+    orc.predation_run(P, S, 3)
+    S.grass.reshape(-1)[::3] = 2 ** 31 - 1
+    if off_grid:
+        _off_grid(S)
+    got = []
+    for cap in (P.cap_s, 40000):
+        m = abm.predation_init(abm.predation_params(seed=31, cap_s=cap))
+        m.run(3)
+        m.grass.copy_(torch.from_numpy(S.grass))
+        for sp in ("sheep", "wolves"):
+            for f in FIELDS:
+                a = getattr(S, sp)[f]
+                getattr(m, sp)[f][:a.size].copy_(torch.from_numpy(a))
+        stats = torch.zeros((80, 8), dtype=torch.int64, device="cuda")
+        m.run(80, stats)
+        got.append([m.grass, stats] + [getattr(m, sp)[f][:getattr(S, sp)[f].size]
+                                       for sp in ("sheep", "wolves") for f in FIELDS])
+    assert int((got[0][0] == 2 ** 31 - 81).sum()) == (P.W * P.H + 2) // 3
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    if not off_grid:
+        orc.predation_run(P, S, 80)
+        _check(dict(grass=got[0][0], sheep=dict(zip(FIELDS, got[0][2:6])),
+                    wolves=dict(zip(FIELDS, got[0][6:]))), S, 80)
+
+
 def test_one_model_replayed_from_a_graph(abm, orc):
     """Captured calls replayed with other work between them."""
     P, S = _state(orc, {}, None)
