@@ -228,7 +228,8 @@ typedef struct abm_species {
     int32_t* x;            /* device int32[cap] */
     int32_t* y;
     int32_t* e;            /* energy */
-    int32_t* alive;
+    int32_t* alive;        /* non-zero = live; a newborn's is 1, an agent's that the caller
+                              made stays as it is, but for 2, which a run turns into 1 */
 } abm_species;
 
 typedef struct abm_predation_state {

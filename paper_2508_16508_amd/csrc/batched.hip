@@ -457,6 +457,7 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
             for (int k = 0; k < ITEMS; ++k) {
                 if (al[k] == 0) continue;
                 const int32_t i = c0 + lbase + k * 64;
+                if (al[k] == 2) v.al[s][i] = 1;   // (the caller's: not the mark of pass B)
                 ++live;
                 if (counts) atomicAdd(&counts->live[s], 1);
                 const uint32_t d = draw(skey, uint32_t(i), move_p[s]) >> 29;
@@ -514,15 +515,17 @@ __device__ bool model_step(const ModelView& v, uint32_t t, uint32_t t0, bool las
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 const int32_t i = c0 + lbase + k * 64;
-                al[k] = i < eff[s] ? v.al[s][i] : -1;
+                al[k] = i < eff[s] ? v.al[s][i] : 0;
             }
             bool br[ITEMS];
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 br[k] = false;
-                if (al[k] == 0) ++nfree;
-                if (al[k] <= 0) continue;
                 const int32_t i = c0 + lbase + k * 64;
+                if (al[k] == 0) {
+                    nfree += i < eff[s] ? 1u : 0u;
+                    continue;
+                }
                 const int32_t x = v.x[s][i], y = v.y[s][i];
                 int32_t e = v.e[s][i];
                 bool eaten = false;

@@ -341,10 +341,11 @@ struct Chip : ChipSize<T> {
             pick(v.x, s)[i] = int32_t(p & 255u);
             pick(v.y, s)[i] = int32_t(p >> 8);
             pick(v.e, s)[i] = int32_t(en[at * 64 + lane]);
+            int32_t* const al = pick(v.al, s) + i;
             if (!on)
-                pick(v.al, s)[i] = 0;
-            else if (child)
-                pick(v.al, s)[i] = 1;
+                *al = 0;
+            else if (child || *al == 2)                // (2 marks an eaten sheep in the other paths)
+                *al = 1;
         }
     }
 

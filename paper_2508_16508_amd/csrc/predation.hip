@@ -797,20 +797,28 @@ __global__ __launch_bounds__(kThreads) void k_breed_die(StepArgs a) {
 }
 
 // ------------------------------------------------------------------ call edges
-// Bitmask word k of the live slots.
-__device__ __forceinline__ uint32_t live_word(const int32_t* alive, int64_t k, int64_t cap) {
-    const int32_t* al = alive + k * 32;
-    uint32_t m = 0;
+// Bitmask word k of the live slots.  A caller's 2, the mark of an eaten sheep
+// within a step, becomes 1.
+__device__ __forceinline__ uint32_t live_word(int32_t* alive, int64_t k, int64_t cap) {
+    int32_t* al = alive + k * 32;
+    uint32_t m = 0, twos = 0;
     if (k * 32 + 32 <= cap) {
         int4 v[8];
         __builtin_memcpy(v, al, sizeof v);      // (4-byte alignment is enough)
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
+        for (int q = 0; q < 8; ++q) {
             m |= uint32_t(v[q].x != 0) << (4 * q) | uint32_t(v[q].y != 0) << (4 * q + 1) |
                  uint32_t(v[q].z != 0) << (4 * q + 2) | uint32_t(v[q].w != 0) << (4 * q + 3);
+            twos |= uint32_t(v[q].x == 2) << (4 * q) | uint32_t(v[q].y == 2) << (4 * q + 1) |
+                    uint32_t(v[q].z == 2) << (4 * q + 2) | uint32_t(v[q].w == 2) << (4 * q + 3);
+        }
     } else {
-        for (int b = 0; b < 32 && k * 32 + b < cap; ++b) m |= uint32_t(al[b] != 0) << b;
+        for (int b = 0; b < 32 && k * 32 + b < cap; ++b) {
+            m |= uint32_t(al[b] != 0) << b;
+            twos |= uint32_t(al[b] == 2) << b;
+        }
     }
+    for (; twos; twos &= twos - 1u) al[__ffs(twos) - 1] = 1;
     return m;
 }
 

@@ -211,6 +211,55 @@ def test_cells_that_never_grow(abm, orc, off_grid):
                     wolves=dict(zip(FIELDS, got[0][6:]))), S, 80)
 
 
+# path: (grid, one model or how the batch is run); 257 cells do not fit the chip
+LIVE_PATHS = {
+    "chip": (dict(), None),
+    "general": (dict(W=257, H=16), None),
+    "batch on the chip": (dict(), dict(max_steps=7)),
+    "batch": (dict(W=257, H=16), dict(max_steps=7)),
+    "batch, claims in global memory": (dict(), dict(max_steps=7, lds=False)),
+    "launches": (dict(W=257, H=16), dict(max_steps=7, team_size=2)),
+    "teams": (dict(W=257, H=16), dict(max_steps=1 << 20, team_size=2)),
+}
+
+
+@pytest.mark.parametrize("multi_prey", [0, 1])
+@pytest.mark.parametrize("path", LIVE_PATHS)
+def test_any_nonzero_value_is_live(abm, orc, path, multi_prey):
+    """Live agents' values are kept (2 becomes 1), whichever path runs the model."""
+    grid, how = LIVE_PATHS[path]
+    kw = dict(grid, multi_prey=multi_prey)
+    P, S = _state(orc, kw, None)
+    for sp in (S.sheep, S.wolves):
+        live = np.flatnonzero(sp["alive"])
+        sp["alive"][live] = np.resize([-1, 7, 2, -2 ** 31, 2 ** 31 - 1, 1], live.size)
+    params = abm.predation_params(seed=31, **kw)
+    if how is None:
+        m = abm.predation_init(params)
+        flat = (m.sheep, m.wolves)
+    else:
+        how = dict(how)
+        b = abm.BatchedPredation([params], 14, team_min_size=1, lds=how.pop("lds", True),
+                                 team_size=how.pop("team_size", 1))
+        b.init()
+        flat = (b.sheep, b.wolves)
+    for d, sp in zip(flat, (S.sheep, S.wolves)):
+        for f in FIELDS:
+            d[f].copy_(torch.from_numpy(sp[f]))
+    for part in range(1 if how and how["max_steps"] > 14 else 2):
+        if how is None:
+            m.run(7)
+            got = dict(grass=m.grass, sheep=m.sheep, wolves=m.wolves)
+        else:
+            b.run(**how)
+            grass, sheep, wolves = b.model_state(0, b.grass_countdown())
+            got = dict(grass=grass.reshape(S.grass.shape), sheep=sheep, wolves=wolves)
+        orc.predation_run(P, S, 14 if how and how["max_steps"] > 14 else 7)
+        for sp in (S.sheep, S.wolves):
+            sp["alive"][sp["alive"] == 2] = 1
+        _check(got, S, part)
+
+
 def test_one_model_replayed_from_a_graph(abm, orc):
     """Captured calls replayed with other work between them."""
     P, S = _state(orc, {}, None)
