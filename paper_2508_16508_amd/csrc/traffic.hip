@@ -142,6 +142,103 @@ __device__ __forceinline__ void write_row(const TrafficArgs& a, int32_t k,
 __host__ __device__ __forceinline__ int32_t grid_words(int32_t L) { return 5 * (L + 2); }
 __host__ __device__ __forceinline__ int32_t free_words(int32_t L) { return (3 * L + 63) / 64 * 2; }
 
+// A road on which cars share cells, as a caller may have placed them (no step
+// puts a car on an occupied cell): such cars draw, claim and leave each for
+// itself.  A thread per car slot, the slots in global memory; the LDS (6 bytes a
+// slot) holds the lowest key that claims a cell, (direction priority << 24 |
+// slot), whether a cell is occupied, and each car's target lane.
+__device__ __forceinline__ void run_shared_cells(const TrafficArgs& a, int32_t* lds) {
+    __shared__ uint32_t cnt[kCols], s_entry;
+    const int32_t L = a.L, n = 3 * L, block = int32_t(blockDim.x);
+    uint32_t* const claim = reinterpret_cast<uint32_t*>(lds);
+    uint8_t* const occ = reinterpret_cast<uint8_t*>(claim + n);
+    int8_t* const to = reinterpret_cast<int8_t*>(occ + n);
+    const int64_t base = int64_t(blockIdx.x) * n;
+    int32_t *const lane = a.lane + base, *const pos = a.pos + base, *const alive = a.alive + base;
+    const int tid = threadIdx.x;
+    const auto cell_of = [&](int32_t i) {     // -1: no car, or none of the road's
+        const int32_t l = lane[i], x = pos[i];
+        return alive[i] && l >= 0 && l < 3 && x >= 0 && x < L ? l * L + x : -1;
+    };
+    const auto key_of = [](int32_t from, int32_t lane_to, int32_t i) {
+        return (lane_to == from ? 0u : (from < lane_to ? 1u : 2u)) << 24 | uint32_t(i);
+    };
+    for (int32_t k = 0; k < a.n_steps; ++k) {
+        const uint64_t skey = stream_key(a.seed + blockIdx.x, a.step0 + uint32_t(k));
+        __syncthreads();
+        for (int32_t i = tid; i < n; i += block) {
+            claim[i] = ~0u;
+            occ[i] = 0;
+        }
+        if (tid < kCols) cnt[tid] = 0;
+        if (tid == 0) s_entry = 0;
+        __syncthreads();
+        for (int32_t i = tid; i < n; i += block) {
+            const int32_t c = cell_of(i);
+            if (c >= 0) occ[c] = 1;
+        }
+        __syncthreads();
+        for (int32_t i = tid; i < n; i += block) {
+            const int32_t c = cell_of(i);
+            if (c < 0) continue;
+            atomicAdd(&cnt[kCars], 1u);
+            const int32_t l = lane[i];
+            to[i] = kNone;
+            if (c - l * L == L - 1) continue;
+            const int32_t nl = l + int32_t(scale(draw(skey, uint32_t(i), kTrafficLane), 3u)) - 1;
+            const int32_t t = uint32_t(nl) > 2u ? l : nl, ahead = t * L + (c - l * L) + 1;
+            if (occ[ahead]) {
+                atomicAdd(&cnt[kBlocked], 1u);
+            } else {
+                to[i] = int8_t(t);
+                atomicMin(&claim[ahead], key_of(l, t, i));
+            }
+        }
+        __syncthreads();
+        for (int32_t i = tid; i < n; i += block) {
+            const int32_t c = cell_of(i);
+            if (c < 0) continue;
+            const int32_t l = lane[i], x = c - l * L, t = to[i];
+            if (x == L - 1) {
+                const bool green = draw(skey, uint32_t(l), kTrafficLight) < a.T_green;
+                atomicAdd(&cnt[green ? kExited : kWaitingRed], 1u);
+                if (green) alive[i] = 0;
+                continue;
+            }
+            const bool moves = t != kNone && claim[t * L + x + 1] == key_of(l, t, i);
+            if (moves) {
+                atomicAdd(&cnt[kMoved], 1u);
+                if (t != l) atomicAdd(&cnt[kLaneChanges], 1u);
+                lane[i] = t;
+                pos[i] = x + 1;
+            } else {
+                if (t != kNone) atomicAdd(&cnt[kLost], 1u);
+                if (x == 0) atomicOr(&s_entry, 1u << l);
+            }
+        }
+        __syncthreads();
+        if (tid < 64) {
+            const bool want = tid < 3 && !((s_entry >> tid) & 1u) &&
+                              draw(skey, uint32_t(tid), kTrafficSpawn) < a.T_spawn;
+            uint64_t left = __ballot(want);   // lanes still without a slot
+            for (int32_t i0 = 0; i0 < n && left; i0 += 64) {
+                uint64_t f = __ballot(i0 + tid < n && alive[i0 + tid] == 0);
+                for (; f && left; f &= f - 1, left &= left - 1) {
+                    const int32_t i = i0 + __ffsll((unsigned long long)f) - 1;
+                    if (tid != 0) continue;
+                    lane[i] = __ffsll((unsigned long long)left) - 1;
+                    pos[i] = 0;
+                    alive[i] = 1;
+                    ++cnt[kSpawned];
+                }
+            }
+        }
+        __syncthreads();
+        if (a.stats && tid < kCols)
+            a.stats[(int64_t(k) * a.n_roads + blockIdx.x) * kCols + tid] = cnt[tid];
+    }
+}
+
 // Wave 0 holds the entry and the exit column (lane l and lane 3 + l: lane l of
 // the road) and spawns; the last wave holds no cell, draws what depends on no
 // car for the steps to come and writes the statistics; the waves between them
@@ -161,6 +258,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_traffic_run(TrafficArgs a) {
     extern __shared__ int32_t grid[];
     __shared__ uint32_t s_cnt[2][2][kMaxWaves];   // packed counts of each wave
     __shared__ uint32_t s_ex[2];                  // left | waiting at red << 8 | spawned << 16
+    __shared__ int32_t s_unplaced;                // cars without a cell of their own
     __shared__ uint4 s_pre[2];                    // a step's stream key (x, y), its lights and entry draws (z)
     const int32_t L = a.L, n = 3 * L, stride = L + 2, words = grid_words(L);
     uint32_t* const free_bits = reinterpret_cast<uint32_t*>(grid + 2 * words);
@@ -190,11 +288,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_traffic_run(TrafficArgs a) {
         prepare_step(0);
         prepare_step(1);
     }
+    if (tid == 0) s_unplaced = 0;
     __syncthreads();
+    int32_t cars = 0;
     for (int32_t i = tid; i < n; i += int32_t(blockDim.x)) {
         const int32_t l = a.lane[base + i], x = a.pos[base + i];
-        if (a.alive[base + i] && l >= 0 && l < 3 && x >= 0 && x < L)
+        if (a.alive[base + i] && l >= 0 && l < 3 && x >= 0 && x < L) {
             grid[(l + 1) * stride + x + 1] = ((i + 1) << 2) | kNone;
+            ++cars;
+        }
     }
     // the free slots' bits; wave 0 keeps their number and the lowest of them
     int32_t n_free = 0;
@@ -221,8 +323,15 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_traffic_run(TrafficArgs a) {
         col[r] = !ok ? -1 : (wave ? i % len + 1 : (i < 3 ? 0 : L - 1));
         cell[r] = ok ? (row[r] + 1) * stride + col[r] + 1 : 0;   // (word 0: never a car's)
         sl[r] = word_slot(grid[cell[r]]);
+        cars -= sl[r] >= 0 ? 1 : 0;
     }
+    cars = wave_incl_sum(cars);
+    if (lane == 63 && cars) atomicAdd(&s_unplaced, cars);
     __syncthreads();
+    if (s_unplaced != 0) {
+        run_shared_cells(a, grid);
+        return;
+    }
 
     if (wave == 0) __builtin_amdgcn_s_setprio(3);   // every step waits for this wave
     for (int32_t k = 0; k < a.n_steps; ++k) {

@@ -90,3 +90,39 @@ def test_a_crowded_road_spawns_into_the_last_free_slots(abm, orc):
     roads, stats = _run(abm, 12, 20, (200,), T_green=2 ** 28, T_spawn=2 ** 32 - 1, seed=77)
     assert int(stats[..., 0].max()) == 36
     _check_roads(abm, orc, roads, stats, 200)
+
+
+# one, two and four cells a thread; cars that share the entry, the exit and other cells, some
+# of every road or of one road only
+@pytest.mark.parametrize("length,n_roads", [(2, 5), (40, 4), (301, 3), (1024, 2)])
+def test_cars_that_share_cells(abm, orc, length, n_roads):
+    n = 3 * length
+    g = np.random.default_rng(length)
+    roads = abm.TrafficRoads(abm.traffic_params(length, T_green=2 ** 30, seed=7), n_roads)
+    roads.init()
+    roads.run(3)
+    lane = roads.lane.cpu().numpy()
+    pos, alive = roads.pos.cpu().numpy(), roads.alive.cpu().numpy()
+    for r in range(1, n_roads):                  # (road 0 stays as it is)
+        k = max(2, n // 3) if r > 1 else 2
+        at = g.choice(n, size=k, replace=False)
+        alive[r, at] = 1
+        lane[r, at], pos[r, at] = g.integers(0, 3, k), g.integers(0, length, k)
+        lane[r, at[1]], pos[r, at[1]] = lane[r, at[0]], pos[r, at[0]]
+    for d, h in ((roads.lane, lane), (roads.pos, pos), (roads.alive, alive)):
+        d.copy_(torch.from_numpy(h))
+    states = []
+    for r in range(n_roads):
+        OP = orc.traffic_params(length, 2 ** 30, 2 ** 31, 7 + r)
+        S = orc.traffic_init(OP)
+        S.lane[:], S.pos[:], S.alive[:], S.step = lane[r], pos[r], alive[r], 3
+        states.append((OP, S))
+    for steps in (1, 9, 70):
+        stats = torch.full((steps, n_roads, 8), -1, dtype=torch.int64, device="cuda")
+        roads.run(steps, stats)
+        st = stats.cpu().numpy()
+        for r, (OP, S) in enumerate(states):
+            exp = orc.traffic_run(OP, S, steps)
+            assert np.array_equal(st[:, r], [[d[k] for k in orc.TRAFFIC_STATS] for d in exp]), r
+            for d, h in ((roads.lane, S.lane), (roads.pos, S.pos), (roads.alive, S.alive)):
+                assert np.array_equal(d[r].cpu().numpy(), h), (r, steps)
