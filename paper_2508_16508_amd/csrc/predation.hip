@@ -137,6 +137,7 @@ struct StepArgs {
     uint32_t chain_off[2];  // start of each species' breeder scan chain in the status words
     uint32_t fchain_off[2]; // ... and of its free-slot scan chain
     int32_t multi;          // prey by rank within a cell (K1 builds lists, K1b matches)
+    int32_t batch;          // a model of a batch
     uint64_t* mark_rd;      // [2][kMarkLanes] per species: no live agent in a block past the largest
     uint64_t* mark_wr;      // the same for the next step, raised by K3 (cleared by K1)
 };
@@ -363,8 +364,10 @@ __device__ __forceinline__ uint32_t word_in_cap(const Block& b, uint32_t w, int6
     return left <= 0 ? 0u : low_bits(left < 32 ? uint32_t(left) : 32u);
 }
 
-__device__ __forceinline__ bool grown(int32_t ready, uint32_t step) {
-    return int32_t(uint32_t(ready) - step) <= 0;
+// In a one-model call ready is step + countdown and may wrap; in a batch it is a
+// step, or anything that the caller set it to.
+__device__ __forceinline__ bool grown(const StepArgs& a, int32_t ready) {
+    return a.batch ? ready <= int32_t(a.step) : int32_t(uint32_t(ready) - a.step) <= 0;
 }
 
 // Tile-local part of a rank: this thread's exclusive rank of its count c
@@ -482,7 +485,7 @@ __device__ __forceinline__ void move_claim(const StepArgs& a, const Block& b, ui
         bool grows[kPerThread];
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k)
-            grows[k] = s == 0 && c[k] >= 0 && grown(a.ready[c[k]], a.step);
+            grows[k] = s == 0 && c[k] >= 0 && grown(a, a.ready[c[k]]);
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
             if (c[k] < 0) continue;
@@ -945,6 +948,7 @@ __global__ __launch_bounds__(kBlock) void k_wide_begin(WideArgs w) {
     a.cap_w = d.cap_w;
     a.G = int64_t(d.W) * d.H;
     a.multi = d.multi_prey != 0;
+    a.batch = 1;
     a.tiles[0] = tiles_s;
     a.tiles[1] = tiles_w;
     a.blocks[0] = blocks_of(tiles_s);
@@ -1239,6 +1243,7 @@ extern "C" int abm_predation_step(const abm_predation_params* p, abm_predation_s
     a.free_pre[0] = reinterpret_cast<int32_t*>(w.status + 2 * (cw0 + cw1));
     a.free_pre[1] = a.free_pre[0] + a.blocks[0];
     a.multi = p->multi_prey;
+    a.batch = 0;
     a.step = s->step;
     a.stats = nullptr;
     a.acc_par = 0;

@@ -260,6 +260,31 @@ def test_any_nonzero_value_is_live(abm, orc, path, multi_prey):
         _check(got, S, part)
 
 
+@pytest.mark.parametrize("path", [p for p, (_, how) in LIVE_PATHS.items() if how])
+def test_cells_grown_since_ever(abm, orc, path):
+    """A batch's cells whose step is -2^31 are grown at every step."""
+    grid, how = LIVE_PATHS[path]
+    how = dict(how)
+    P, S = _state(orc, grid, None)
+    b = abm.BatchedPredation([abm.predation_params(seed=31, **grid)], 10, team_min_size=1,
+                             lds=how.pop("lds", True), team_size=how.pop("team_size", 1))
+    b.init()
+    b.run(3)
+    orc.predation_run(P, S, 3)
+    b.ready[::2] = -2 ** 31
+    S.grass.reshape(-1)[::2] = 0
+    b.run(**how)
+    orc.predation_run(P, S, 7)
+    # (the countdown of a cell grown at -2^31 is not asked for: it is not a step)
+    ready = torch.where(b.ready == -2 ** 31, 0, b.ready)
+    grass = (ready - 10).clamp(min=0).cpu().numpy().reshape(S.grass.shape)
+    assert np.array_equal(grass, S.grass)
+    _, sheep, wolves = b.model_state(0, b.ready)
+    for d, sp in ((sheep, S.sheep), (wolves, S.wolves)):
+        for f in FIELDS:
+            assert np.array_equal(d[f].cpu().numpy(), sp[f]), f
+
+
 def test_one_model_replayed_from_a_graph(abm, orc):
     """Captured calls replayed with other work between them."""
     P, S = _state(orc, {}, None)
