@@ -267,8 +267,9 @@ def _counts(device, *given):
 
 
 def _segment_counts(n_seg, device):
-    """One count per segment, each written by the call (none: a single 0)."""
-    if n_seg == 0:
+    """One count per segment, each written by the call (none: a single 0; fewer than
+    none, an empty offset array, is for the call to refuse)."""
+    if n_seg <= 0:
         return torch.zeros(1, dtype=torch.int64, device=device)
     return torch.empty(n_seg, dtype=torch.int64, device=device)
 

@@ -181,3 +181,16 @@ def test_records_far_from_the_first(abm):
     assert ap.tolist() == [10, 10, 40]
     assert a[:10].tolist() == [0, 1, 2, 3, 4, 5, 6, 7, 0, 0] and a[10:20].tolist() == [0] * 10
     assert a[20:60].tolist() == list(range(1000, 1040)) and a[60:].tolist() == [-1] * 30
+
+
+def test_empty_offsets_are_refused(abm):
+    """No offset at all is not a number of segments: the call's own error."""
+    none = torch.zeros(0, dtype=torch.int64, device="cuda")
+    rows = torch.zeros((1, 8), dtype=torch.int32, device="cuda")
+    alive = torch.zeros(8, dtype=torch.int32, device="cuda")
+    mask = torch.zeros(8, dtype=torch.uint8, device="cuda")
+    for call in (lambda: abm.select_update_batched(rows, none, mask, rows, none),
+                 lambda: abm.add_agents_batched(rows, alive, none, rows, none),
+                 lambda: abm.remove_agents_batched(alive, none, mask)):
+        with pytest.raises(abm.AbmError):
+            call()
