@@ -397,7 +397,9 @@ def remove_agents(alive, kill_mask, ws=None, removed=None, stream=None):
 
 def resolve_conflicts(target, prio, n_targets, active=None, best=None, winner=None, won=None,
                       stream=None):
-    """Lowest (prio, claim) wins each target.  Returns (best, winner, won)."""
+    """Lowest (prio, claim) wins each target.  Returns (best, winner, won).  Many claims
+    (abm_resolve_workspace_bytes) take a workspace of 12 bytes each for the call; where
+    there is no room for it, they are resolved without."""
     _require(target, torch.int32, "target")
     _require(prio, torch.int32 if prio.dtype == torch.int32 else torch.uint32, "prio")
     _require(active, torch.uint8, "active")
@@ -411,8 +413,13 @@ def resolve_conflicts(target, prio, n_targets, active=None, best=None, winner=No
         won = torch.empty(max(1, n), dtype=torch.uint8, device=dev)
     ws, need = None, int(lib().abm_resolve_workspace_bytes(n, n_targets))
     if need:
-        with torch.cuda.stream(stream):   # (freed in the order of the stream that uses it)
-            raw = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+        try:
+            with torch.cuda.stream(stream):   # (freed in the order of the stream that uses it)
+                raw = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:        # the form without a workspace needs none
+            _check(lib().abm_resolve_conflicts(n, _p(target), _p(prio), _p(active), n_targets,
+                                               _p(best), _p(winner), _p(won), _stream(stream)))
+            return best, winner, won
         off = (-raw.data_ptr()) % 256
         ws = raw[off: off + need]
     _check(lib().abm_resolve_conflicts_ws(n, _p(target), _p(prio), _p(active), n_targets, _p(best),

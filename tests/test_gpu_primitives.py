@@ -304,6 +304,31 @@ def test_resolve_conflicts_partitioned_on_a_side_stream(abm, orc):
         assert np.array_equal(host(a), e)
 
 
+def test_resolve_conflicts_without_room_for_a_workspace(abm, orc):
+    n, nt = 1 << 22, 1000
+    g = np.random.default_rng(9)
+    target = g.integers(0, nt, size=n).astype(np.int32)
+    prio = g.integers(0, 2 ** 32, size=n, dtype=np.uint64).astype(np.uint32)
+    exp = orc.resolve_conflicts(target, prio, nt)
+    d_target, d_prio = dev(target), dev(prio.view(np.int32)).view(torch.uint32)
+    out = dict(best=torch.empty(nt, dtype=torch.uint64, device="cuda"),
+               winner=torch.empty(nt, dtype=torch.int32, device="cuda"),
+               won=torch.empty(n, dtype=torch.uint8, device="cuda"))
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:     # what is held now and a little: less than the workspace
+        torch.cuda.set_per_process_memory_fraction(
+            (torch.cuda.memory_reserved() + (8 << 20)) / total)
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(abm.lib().abm_resolve_workspace_bytes(n, nt), dtype=torch.uint8,
+                        device="cuda")
+        got = abm.resolve_conflicts(d_target, d_prio, nt, **out)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    for a, e in zip(got, exp):
+        assert np.array_equal(host(a), e)
+
+
 def test_graph_replay_select_add_remove(abm, orc):
     """select_update, add_agents and remove_agents recorded once into a graph and
     replayed with fresh inputs copied in between: the device-side epoch keeps
