@@ -51,8 +51,9 @@ namespace {
 
 constexpr int kChipThreads = 1024;            // of the largest workgroup
 constexpr int32_t kChipSide = 256;            // positions are 8 + 8 bits
-constexpr int32_t kChipReadyMax = 254;        // a regrowth byte above it does not fit
-constexpr int32_t kChipMaxR = 200;            // leaves 55 steps at least between two rebasings
+constexpr int32_t kChipReadyMax = 254;        // the last step, past the base, that a regrowth byte holds
+constexpr int32_t kChipFar = 255;             // ... of a cell grown later: the global array has the step
+constexpr int32_t kChipMaxR = 200;            // leaves 54 steps at least between two rebasings
 constexpr int32_t kChipMaxGain = 8192;
 constexpr int32_t kChipEnergyMax = 16384;     // a 16-bit energy above it ends the on-chip run
 constexpr uint32_t kChipNoOwner = 0xFFFFFFFFu;
@@ -150,6 +151,7 @@ struct Chip : ChipSize<T> {
     uint64_t* hval;
     uint32_t *hown, *list;
     int32_t* spill;              // global: contested agents past the list
+    int32_t first;               // step at which the run began
     int tid, lane, wave;
 
     __device__ __forceinline__ Chip(const V& view, ChipShared& shared, char* lds, int64_t bytes,
@@ -208,9 +210,20 @@ struct Chip : ChipSize<T> {
         }
     }
 
+    // Steps from `base` on until a cell is grown, by the global value g (a cell
+    // that has not been eaten since the run began).
+    __device__ __forceinline__ int32_t far_from(int32_t g, int32_t base) const {
+        return max(g, 0) - (COUNTDOWN ? base - first : base);
+    }
+    // ... as a regrowth byte.
+    __device__ __forceinline__ uint32_t ready_byte(int32_t rel) const {
+        return uint32_t(min(max(rel, 0), kChipFar));
+    }
+
     // Reads the model's state at step t0.  False if it does not fit the chip
     // form (then nothing has changed).
     __device__ __forceinline__ bool load(int32_t t0) {
+        first = t0;
         if (tid == 0) {
             sh.bad = 0;
             sh.armed = 0;
@@ -228,14 +241,7 @@ struct Chip : ChipSize<T> {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int32_t c = 4 * i + q;
-                int32_t rel = 0;
-                if (c < cells) {
-                    const int32_t g = v.ready[c];
-                    rel = COUNTDOWN ? g : int32_t(uint32_t(g) - uint32_t(t0));
-                    bad |= rel > kChipReadyMax;
-                    rel = rel < 0 ? 0 : rel;
-                }
-                w |= uint32_t(rel & 255) << (8 * q);
+                w |= (c < cells ? ready_byte(far_from(v.ready[c], t0)) : 0u) << (8 * q);
             }
             reinterpret_cast<uint32_t*>(rdy)[i] = w;
         }
@@ -275,9 +281,10 @@ struct Chip : ChipSize<T> {
             const bool in = i < pick(v.cap, s);
             const int32_t x = in ? pick(v.x, s)[i] : 0, y = in ? pick(v.y, s)[i] : 0, e = in ? pick(v.e, s)[i] : 0;
             const bool on = in && pick(v.al, s)[i] != 0;
-            // live agents on the grid, stale positions in 8 bits, energies in range
-            bad |= uint32_t(x) > 255u || uint32_t(y) > 255u || (on && (x >= v.W || y >= v.H));
-            if (sizeof(E) == 2) bad |= e > kChipEnergyMax || e < -kChipEnergyMax;
+            // live agents on the grid, their energies in range (what a dead slot
+            // holds is not read before a child is put there)
+            bad |= on && (uint32_t(x) >= uint32_t(v.W) || uint32_t(y) >= uint32_t(v.H));
+            if (sizeof(E) == 2) bad |= on && (e > kChipEnergyMax || e < -kChipEnergyMax);
             pos[at * 64 + lane] = uint16_t(uint32_t(y) << 8 | (uint32_t(x) & 255u));
             en[at * 64 + lane] = E(e);
             const uint64_t m = __ballot(on);
@@ -303,10 +310,13 @@ struct Chip : ChipSize<T> {
             uint32_t w = reinterpret_cast<uint32_t*>(rdy)[i], out = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int32_t rel = int32_t((w >> (8 * q)) & 255u);
-                if (!COUNTDOWN && rel >= v.R && 4 * i + q < cells) v.ready[4 * i + q] = from + rel;
-                const int32_t left = rel - (to - from);
-                out |= uint32_t(left > 0 ? left : 0) << (8 * q);
+                const int32_t rel = int32_t((w >> (8 * q)) & 255u), c = 4 * i + q;
+                if (rel == kChipFar) {
+                    out |= ready_byte(far_from(v.ready[c], to)) << (8 * q);
+                    continue;
+                }
+                if (!COUNTDOWN && rel >= v.R && c < cells) v.ready[c] = from + rel;
+                out |= ready_byte(rel - (to - from)) << (8 * q);
             }
             reinterpret_cast<uint32_t*>(rdy)[i] = out;
         }
@@ -322,9 +332,9 @@ struct Chip : ChipSize<T> {
                 const int32_t rel = int32_t((w >> (8 * q)) & 255u), c = 4 * i + q;
                 if (c >= cells) continue;
                 if (COUNTDOWN) {
-                    const int32_t left = rel - (t - base);
+                    const int32_t left = rel == kChipFar ? far_from(v.ready[c], t) : rel - (t - base);
                     v.ready[c] = left > 0 ? left : 0;
-                } else if (rel >= v.R) {
+                } else if (rel >= v.R && rel != kChipFar) {
                     v.ready[c] = base + rel;
                 }
             }
@@ -336,15 +346,17 @@ struct Chip : ChipSize<T> {
             const bool open = r < sh.rows[par][s];     // (rows past it hold no live agent)
             const bool on = open && ((alive[par * R_rows + at] >> lane) & 1);
             const bool child = (born[at] >> lane) & 1;
-            if (i >= pick(v.cap, s) || (r >= pick(rows0, s) && !child)) continue;
+            // (a slot that held no agent in this run keeps its fields)
+            int32_t* const al = pick(v.al, s) + i;
+            const int32_t was = i < pick(v.cap, s) && r < pick(rows0, s) ? *al : 0;
+            if (i >= pick(v.cap, s) || (was == 0 && !child)) continue;
             const uint32_t p = pos[at * 64 + lane];
             pick(v.x, s)[i] = int32_t(p & 255u);
             pick(v.y, s)[i] = int32_t(p >> 8);
             pick(v.e, s)[i] = int32_t(en[at * 64 + lane]);
-            int32_t* const al = pick(v.al, s) + i;
             if (!on)
                 *al = 0;
-            else if (child || *al == 2)                // (2 marks an eaten sheep in the other paths)
+            else if (child || was == 2)                // (2 marks an eaten sheep in the other paths)
                 *al = 1;
         }
     }
@@ -722,7 +734,7 @@ __device__ __forceinline__ int32_t run_on_chip(const V& v, ChipShared& sh, char*
     int par = 0;
     bool go = true;
     for (; t < t1 && go; ++t, par ^= 1) {
-        if (t - base + v.R > 255) {
+        if (t - base + v.R > kChipReadyMax) {
             c.rebase(base, t);
             base = t;
             __syncthreads();

@@ -285,6 +285,49 @@ def test_cells_grown_since_ever(abm, orc, path):
             assert np.array_equal(d[f].cpu().numpy(), sp[f]), f
 
 
+# the regrowth bytes are rebased several times in 600 steps; dead slots between live ones hold
+# what no agent could, and keep it until a child is put there
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("R", [1, 30, 200])
+def test_far_countdowns_and_odd_dead_slots(abm, orc, R, batched):
+    kw = dict(R=R, T_s=10 ** 8, n_s0=300)
+    P, S = _state(orc, kw, None)
+    S.grass.reshape(-1)[::5] = np.resize([254, 255, 256, 300, 454, 455, 479, 480, 510, 700,
+                                          10 ** 9, 2 ** 31 - 1], S.grass.reshape(-1)[::5].size)
+    g = np.random.default_rng(R)
+    for sp in (S.sheep, S.wolves):
+        sp["alive"][g.random(sp["alive"].size) < 0.4] = 0
+        dead = np.flatnonzero(sp["alive"] == 0)
+        for f in ("x", "y", "e"):
+            sp[f][dead] = g.integers(-2 ** 31, 2 ** 31, dead.size)
+    params = abm.predation_params(seed=31, **kw)
+    if batched:
+        b = abm.BatchedPredation([params], 600)
+        b.init()
+        b.ready.copy_(torch.from_numpy(S.grass.reshape(-1)))
+        flat = (b.sheep, b.wolves)
+    else:
+        m = abm.predation_init(params)
+        m.grass.copy_(torch.from_numpy(S.grass))
+        flat = (m.sheep, m.wolves)
+    for d, sp in zip(flat, (S.sheep, S.wolves)):
+        for f in FIELDS:
+            d[f].copy_(torch.from_numpy(sp[f]))
+    for steps in (3, 597):
+        if batched:
+            b.run(steps)
+            grass, sheep, wolves = b.model_state(0, b.grass_countdown())
+            got = dict(grass=grass.reshape(S.grass.shape), sheep=sheep, wolves=wolves)
+        else:
+            stats = torch.zeros((steps, 8), dtype=torch.int64, device="cuda")
+            m.run(steps, stats)
+            got = dict(grass=m.grass, sheep=m.sheep, wolves=m.wolves)
+        rows = orc.predation_run(P, S, steps)
+        if not batched:
+            assert np.array_equal(stats.cpu().numpy(), [[r[k] for k in abm.STAT_NAMES] for r in rows])
+        _check(got, S, steps)
+
+
 def test_one_model_replayed_from_a_graph(abm, orc):
     """Captured calls replayed with other work between them."""
     P, S = _state(orc, {}, None)
