@@ -1414,13 +1414,20 @@ namespace abm {
 
 // A small model advanced by one workgroup on the chip: every slot of both
 // species and every cell fit its LDS, so whatever the populations do the call
-// is one launch.  A step takes the workgroup less than the three dependent
-// launches of the general path: 5.4 us against 16.1 at 64 x 64 cells with 500
-// agents, 7.5 against 19.3 with 5120 (one step alone, from that state, 53 and
-// 49).  With many more slots than cells a first step can find several agents
-// in every cell, which one workgroup is slow at (20000 agents on 64 x 64 cells:
-// 183 us against 53), so past 1.5 slots a cell only models of up to 1024 slots
-// are taken.
+// is one launch.  20 steps from the initial state, in us, against the general
+// path's launches: 64 x 64 cells with 511 agents 128 and 303, with 5120 248 and
+// 480; 170 x 170 cells with 3612 agents 233 and 550, with 15104 557 and 567.
+//   With many more slots than cells a first step can find several agents in
+// every cell, which one workgroup is slow at (20000 agents on 64 x 64 cells: 183
+// us against 53), so past 1.5 slots a cell only models of up to 1024 slots are
+// taken.
+//   A call of one step loads and stores the whole state for it: 28 against 37 us
+// at 64 x 64 cells with 511 agents, 53 and 48 with 5120; 50 and 50 at 170 x 170
+// with 3612, 107 and 52 with 15104.  The call does not know the number of
+// agents, so a single step of more than kOneStepSlots slots is left to the
+// launches, whose time hardly depends on it.
+constexpr int64_t kOneStepSlots = 8192;
+
 int launch_small_predation(const abm_predation_params* p, const abm_predation_state* s,
                            int32_t n_steps, const Workspace& w, hipStream_t st, bool* taken) {
     *taken = false;
@@ -1432,7 +1439,9 @@ int launch_small_predation(const abm_predation_params* p, const abm_predation_st
     const int64_t need = chip_fixed_bytes<kChipThreads>(cells) + rows * chip_row_bytes<int32_t>();
     const int bytes = chip_lds_bytes();
     const int64_t slots = p->cap_s + p->cap_w;
-    if (need > bytes || (slots > 1024 && 2 * slots > 3 * cells)) return ABM_OK;
+    if (need > bytes || (slots > 1024 && 2 * slots > 3 * cells) ||
+        (n_steps == 1 && slots > kOneStepSlots))
+        return ABM_OK;
     SmallArgs a;
     a.W = p->W;
     a.H = p->H;
