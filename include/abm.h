@@ -337,8 +337,12 @@ typedef struct abm_batch {        /* host struct of device pointers */
 
 typedef struct abm_tuning {
     int32_t block_threads;         /* threads per model workgroup (multiple of 64 in [256, 1024]); 0 = 512 */
-    int32_t workgroups;            /* persistent workgroups; 0 = as many as are resident at once */
-    int32_t items;                 /* slots per thread per chunk: 1, 2 or 4; 0 = 4 */
+    int32_t workgroups;            /* persistent workgroups; 0 = as many as are resident at once.  Fewer
+                                      than that bound every launch of the run that advances models */
+    int32_t items;                 /* slots per thread per chunk: 1, 2 or 4; 0 = 4.  (This and
+                                      block_threads shape the models that a workgroup advances in
+                                      global memory; those that fit a workgroup's LDS, and large ones
+                                      advanced by launches over the device, have shapes of their own) */
     int32_t team_size;             /* workgroups per team (1..16); 0 or 1 = no teams */
     int32_t team_models;           /* the first team_models entries of order run in teams */
     int32_t team_workgroups;       /* workgroups formed into teams, a multiple of 8 * team_size;

@@ -1506,7 +1506,10 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     if (!run_shape(items, block, &n_cu, &per_cu, &lds_bytes)) return ABM_E_HIP;
     if (tune && tune->global_claims) lds_bytes = 0;
     int resident = n_cu * per_cu;
-    if (tune && tune->workgroups > 0 && tune->workgroups < resident) resident = tune->workgroups;
+    // a caller that asks for fewer workgroups than would be resident leaves the
+    // rest of the device to others, whichever kernels advance its models
+    const bool bounded = tune && tune->workgroups > 0 && tune->workgroups < resident;
+    if (bounded) resident = tune->workgroups;
     if (resident > kMaxWorkgroups) resident = kMaxWorkgroups;
     // teams: order[0, n_team) is run by teams of K workgroups, formed from the
     // first team_wgs workgroups (a multiple of 8 K)
@@ -1578,7 +1581,7 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     if (n_team > 0 && hipStreamIsCapturing(st, &capture) != hipSuccess)
         return fail(ABM_E_HIP, "hipStreamIsCapturing failed");
     const int32_t most = capture == hipStreamCaptureStatusNone ? kWideSteps : kWideStepsRecorded;
-    if (n_team > 0 && max_steps <= most && 2 * int64_t(n_team) <= shares &&
+    if (n_team > 0 && !bounded && max_steps <= most && 2 * int64_t(n_team) <= shares &&
         n_team < kMaxWideModels && wide_fits(b->max_cap)) {
         // (the order is largest first where it balances the load)
         const int with = n_team + (n_team + 8 < 64 ? 64 : n_team + 8);
@@ -1603,6 +1606,7 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     // those take anyway, and a launch before them only delays the teams.
     a.wide = reinterpret_cast<uint8_t*>(a.team_counts);
     a.n_wide = 0;
+    const int bound = bounded ? resident : 4 * n_cu;   // workgroups of a chip launch
     const bool chips = !(tune && tune->global_claims) && team_wgs == 0 && n_team < b->n_models;
     if (chips) {
         const int chip = chip_lds_bytes();
@@ -1617,11 +1621,12 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
             // of 32^2 to 256^2 8.5 to 7.7; 300 of 100^2 to 150^2 0.73 to 0.60).
             // Their lists lie behind the bytes of `wide`
             const int64_t solo = b->n_models - n_team;
-            if (solo <= kChipListed && solo > n_cu) {
+            if (solo <= kChipListed && solo > n_cu && bound >= 2 * n_cu) {
                 a.chip_list[1] = reinterpret_cast<int64_t*>(a.wide + 2 * kMaxWideModels + 64);
                 a.chip_list[0] = a.chip_list[1] + kChipListed;
                 a.chip_bytes[1] = chip_lds_part(chip, 2);
-                if (solo > 2 * n_cu) a.chip_bytes[0] = chip_lds_part(chip, 4);
+                if (solo > 2 * n_cu && bound >= 4 * n_cu)
+                    a.chip_bytes[0] = chip_lds_part(chip, 4);
             }
             hipLaunchKernelGGL(k_classify, dim3(1), dim3(1024), 0, st, a);
         }
@@ -1649,7 +1654,8 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     }
     if (a.listed) {
         // (a share of the workspace each)
-        const int solo = b->n_models - n_team, most = solo < shares ? solo : int(shares);
+        const int solo = b->n_models - n_team, room = solo < shares ? solo : int(shares);
+        const int most = room < bound ? room : bound;
         const auto wgs = [&](int per_cu) { return dim3(per_cu * n_cu < most ? per_cu * n_cu : most); };
         if (a.chip_bytes[0] > 0)
             hipLaunchKernelGGL((k_batched_chip<256, 0>), wgs(4), dim3(256),

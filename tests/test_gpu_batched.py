@@ -561,3 +561,23 @@ def test_initial_states_at_every_offset(abm, orc, n_models):
         for f in FIELDS:
             want = np.concatenate([getattr(s, name)[f] for s in states])
             assert np.array_equal(_host(getattr(batch, name)[f]), want), (name, f)
+
+
+def test_workgroups_bound_the_models_on_the_chip(abm):
+    """A run of few workgroups leaves the rest of the device free, also where the
+    models are advanced inside LDS: 64 equal models by one workgroup take it 64
+    turns (at least eight times as long as side by side, with a margin of eight)."""
+    params = [abm.predation_params(seed=m) for m in range(64)]
+    b = abm.BatchedPredation(params, 1000)
+    b.init()
+
+    def ms(**how):
+        b.run(20, **how)
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        e0.record()
+        b.run(20, **how)
+        e1.record()
+        torch.cuda.synchronize()
+        return e0.elapsed_time(e1)
+
+    assert ms(workgroups=1) > 8 * ms()
