@@ -61,18 +61,22 @@ constexpr uint32_t kDxPacked = 0x9224u;  // see predation.hip: dir -> dx + 1, 2 
 constexpr uint32_t kDyPacked = 0xA940u;
 
 // Words of the workspace header: the queues of the team models, of the models
-// of one workgroup and of those run on the chip (by size class), and the
-// lengths of the lists k_classify makes of the latter two.
+// of one workgroup and of those run on the chip (by size class), the lengths of
+// the lists k_classify makes of the latter two, and the number of wide models.
 constexpr int kChipClasses = 3;
 enum QueueWord : int {
     kQueueTeam = 0, kQueueSolo, kSoloModels, kQueueChip, kChipModels = kQueueChip + kChipClasses,
-    kQueueWords = kChipModels + kChipClasses
+    kWideModels = kChipModels + kChipClasses, kQueueWords
 };
 
 // Cells plus slots from which a model of one workgroup that does not fit the
 // chip joins the large ones (see launch_wide): one workgroup takes some 0.06 ms
 // a step for it and more as it grows, which the launches' total no longer hides.
 constexpr int64_t kWideSize = 1 << 15;
+// Leading models of the order that may join them beside the teams' (200 models of
+// 300^2 to 430^2 cells, 15 of them a team's, x 20 steps: 11.3 ms with 64, the others
+// one workgroup each afterwards, 10.0 with all of them).
+constexpr int32_t kWideAtLeast = 256;
 // Steps of a run up to which it is done by launches: three or four are queued
 // for each of the max_steps steps, whether or not the models have that many
 // left (about 2.5 us a launch that finds nothing to do).  A recorded run keeps
@@ -1584,7 +1588,7 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     if (n_team > 0 && !bounded && max_steps <= most && 2 * int64_t(n_team) <= shares &&
         n_team < kMaxWideModels && wide_fits(b->max_cap)) {
         // (the order is largest first where it balances the load)
-        const int with = n_team + (n_team + 8 < 64 ? 64 : n_team + 8);
+        const int with = n_team + 8 < kWideAtLeast ? kWideAtLeast : n_team + 8;
         n_wide = b->n_models < with ? b->n_models : with;
         if (n_wide > shares / 2) n_wide = int(shares / 2);
         team_wgs = 0;
@@ -1643,6 +1647,7 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
         w.link_w = b->link_w;
         w.err = a.err;
         w.taken = a.wide;
+        w.count = a.queue + kWideModels;
         w.shares = reinterpret_cast<char*>(a.scratch);
         w.share = 8 * b->max_cap;
         w.max_cap = b->max_cap;

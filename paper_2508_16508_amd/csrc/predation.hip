@@ -870,8 +870,8 @@ __host__ __device__ __forceinline__ Tags tags_for(int64_t max_cap) {
 }
 
 // ------------------------------------------------------------------ batches
-// Large models of a batch, all of them side by side: the launches above with
-// the models as the grid's second dimension (`wide` models).  96 models of 32^2
+// Large models of a batch (`wide` models), all of them side by side: the launches
+// above with the workgroups shared out among the models.  96 models of 32^2
 // to 1024^2 cells x 40 steps take 10.9 ms, bound as the one-model launches are
 // by the atomics and the claim lines of 1.7 M agents (34.5 ms by teams of four
 // workgroups, whose chain of dependent accesses per agent the largest model's
@@ -889,6 +889,7 @@ struct WideModel {
     Tags tags;
     int64_t cell_off, slot_off[2];
     uint32_t step0;
+    int32_t index;                        // of the model
     int32_t n;                            // steps of this call
     unsigned long long updates;
     uint64_t marks[2][2][kMarkLanes];
@@ -906,25 +907,34 @@ __host__ __device__ __forceinline__ WideLayout wide_layout(uint32_t tiles_s, uin
     return l;
 }
 
-__device__ __forceinline__ WideModel* wide_model(char* shares, int64_t share, uint32_t y) {
-    return reinterpret_cast<WideModel*>(shares + (2 * int64_t(y) + 1) * share);
+__device__ __forceinline__ WideModel* wide_model(const WideArgs& w, uint32_t k) {
+    return reinterpret_cast<WideModel*>(w.shares + (2 * int64_t(k) + 1) * w.share);
 }
 
-// One workgroup per model: its arguments, its counters and scan words cleared.
+// One workgroup per model that may be taken: the k-th taken one gets the k-th
+// pair of shares, its arguments, its counters and scan words cleared there.
 __global__ __launch_bounds__(kBlock) void k_wide_begin(WideArgs w) {
-    const uint32_t y = blockIdx.x;
-    WideModel* const m = wide_model(w.shares, w.share, y);
-    const abm_model_desc& d = w.models[w.order[y]];
+    const int32_t y = int32_t(blockIdx.x);
+    const auto taken = [&](int32_t i) { return i < w.n_team || w.taken[i] != 0; };
+    int32_t k = 0;
+    for (int32_t i0 = 0; i0 < y; i0 += kBlock) {
+        const int32_t i = i0 + int32_t(threadIdx.x);
+        k += __syncthreads_count(i < y && taken(i));
+    }
+    if (y == w.n - 1 && threadIdx.x == 0) *w.count = uint32_t(k + (taken(y) ? 1 : 0));
+    if (!taken(y)) return;
+    WideModel* const m = wide_model(w, uint32_t(k));
+    const int32_t index = w.order[y];
+    const abm_model_desc& d = w.models[index];
     const bool links = w.link_s && w.link_w;
     // as a workgroup's model: refused if it does not fit the lists
     const bool bad = d.cap_s + d.cap_w > 2 * w.max_cap || (d.multi_prey && !links);
-    const bool taken = int32_t(y) < w.n_team || w.taken[y];
     const int32_t left = d.steps_target - d.step;
-    const int32_t n = bad || !taken || left <= 0 ? 0 : (left < w.max_steps ? left : w.max_steps);
+    const int32_t n = bad || left <= 0 ? 0 : (left < w.max_steps ? left : w.max_steps);
     if (n == 0) {
         if (threadIdx.x == 0) {
             m->n = 0;
-            if (bad && int32_t(y) < w.n_team) st_agent(w.err, 1ull);
+            if (bad) st_agent(w.err, 1ull);
         }
         return;
     }
@@ -968,6 +978,7 @@ __global__ __launch_bounds__(kBlock) void k_wide_begin(WideArgs w) {
     m->slot_off[0] = d.sheep_off;
     m->slot_off[1] = d.wolf_off;
     m->step0 = uint32_t(d.step);
+    m->index = index;
     m->n = n;
     m->updates = 0;
 }
@@ -1007,13 +1018,43 @@ __device__ __forceinline__ StepArgs wide_step(const WideArgs& w, WideModel* m, i
     return a;
 }
 
+// The model of this workgroup (null: none), and the workgroup's number among the
+// `per` of the model.
+struct WideGroup {
+    WideModel* m;
+    uint32_t x, per;
+};
+
+// The workgroups of the launch are divided among the models taken, whose number
+// only the device knows: a model has 8 times an odd number of consecutive ones.
+// Consecutive workgroups go to the eight XCDs in turn, and on an XCD to its 32
+// CUs in turn; with an even share of each XCD the low blocks of the models,
+// where the live agents are, would meet on the same CUs (200 models of 64^2 to
+// 500^2 cells x 20 steps: 3.1 ms with 24 workgroups a model, 4.0 with 32, 3.4 with 48;
+// 96 of 32^2 to 1024^2: 6.0, 6.6, 6.1).  Many models take few each (200 of 300^2
+// to 430^2: 10.0 ms with 8, 11.6 with 48).  No model takes more than kWideShare,
+// though one alone would gain (1000^2: 1.69 ms with 48, 0.81 with 256): a
+// workgroup with several blocks waits for the later ones of its model, so an XCD
+// has to hold a model's seven workgroups at once, beside what the launches of
+// other streams hold.
+constexpr uint32_t kWideShare = 56;
+
+__device__ __forceinline__ WideGroup wide_group(const WideArgs& w) {
+    const uint32_t n = *w.count;
+    if (n == 0) return WideGroup{nullptr, 0, 1};
+    uint32_t per = gridDim.x / n < kWideShare ? gridDim.x / n : kWideShare;
+    per = 8 * (((per / 8 > 1 ? per / 8 : 1) - 1) | 1);
+    const uint32_t k = blockIdx.x / per;
+    return WideGroup{k < n ? wide_model(w, k) : nullptr, blockIdx.x - k * per, per};
+}
+
 __global__ __launch_bounds__(kBlock) void k_wide_bits(WideArgs w) {
-    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
-    if (m->n == 0) return;
-    const StepArgs a = wide_step(w, m, 0);
+    const WideGroup g = wide_group(w);
+    if (!g.m || g.m->n == 0) return;
+    const StepArgs a = wide_step(w, g.m, 0);
     const int64_t words_s = int64_t(a.tiles[0]) * kOwners, words_w = int64_t(a.tiles[1]) * kOwners;
-    for (int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x; k < words_s || k < words_w;
-         k += int64_t(gridDim.x) * kBlock) {
+    for (int64_t k = int64_t(g.x) * kBlock + threadIdx.x; k < words_s || k < words_w;
+         k += int64_t(g.per) * kBlock) {
         if (k < words_s) a.bits[0][k] = live_word(a.sp[0].alive, k, a.cap_s);
         if (k < words_w) a.bits[1][k] = live_word(a.sp[1].alive, k, a.cap_w);
     }
@@ -1023,53 +1064,53 @@ __global__ __launch_bounds__(kBlock) void k_wide_bits(WideArgs w) {
 // model's workgroups are consecutive, so the smallest unfinished block of its
 // scans is always that of a resident one.
 template <class F>
-__device__ __forceinline__ void wide_blocks(const StepArgs& a, F body) {
+__device__ __forceinline__ void wide_blocks(const WideGroup& g, const StepArgs& a, F body) {
     const uint32_t n = a.blocks[0] + a.blocks[1];
-    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
-        if (i != blockIdx.x) __syncthreads();
+    for (uint32_t i = g.x; i < n; i += g.per) {
+        if (i != g.x) __syncthreads();
         body(block_of(a, i));
     }
 }
 
 __global__ __launch_bounds__(kThreads) void k_wide_move(WideArgs w, int32_t k) {
     __shared__ uint32_t lds[kThreadWaves];
-    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
-    if (k >= m->n) return;
-    const StepArgs a = wide_step(w, m, k);
-    if (blockIdx.x == 0 && threadIdx.x < 2 * kMarkLanes) a.mark_wr[threadIdx.x] = 0;
-    wide_blocks(a, [&](const Block& b) { move_claim(a, b, lds); });
+    const WideGroup g = wide_group(w);
+    if (!g.m || k >= g.m->n) return;
+    const StepArgs a = wide_step(w, g.m, k);
+    if (g.x == 0 && threadIdx.x < 2 * kMarkLanes) a.mark_wr[threadIdx.x] = 0;
+    wide_blocks(g, a, [&](const Block& b) { move_claim(a, b, lds); });
 }
 
 __global__ __launch_bounds__(kBlock) void k_wide_match(WideArgs w, int32_t k) {
-    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
-    if (k >= m->n || !m->a.multi) return;
-    const StepArgs a = wide_step(w, m, k);
-    for (int64_t j = int64_t(blockIdx.x) * kBlock + threadIdx.x; j < a.cap_w;
-         j += int64_t(gridDim.x) * kBlock)
+    const WideGroup g = wide_group(w);
+    if (!g.m || k >= g.m->n || !g.m->a.multi) return;
+    const StepArgs a = wide_step(w, g.m, k);
+    for (int64_t j = int64_t(g.x) * kBlock + threadIdx.x; j < a.cap_w; j += int64_t(g.per) * kBlock)
         prey_match(a, j);
 }
 
 __global__ __launch_bounds__(kThreads) void k_wide_eat(WideArgs w, int32_t k) {
     __shared__ EatLds sh;
-    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
-    if (k >= m->n) return;
-    const StepArgs a = wide_step(w, m, k);
-    wide_blocks(a, [&](const Block& b) { eat_breeders(a, b, uint32_t(k) + 1u, sh); });
+    const WideGroup g = wide_group(w);
+    if (!g.m || k >= g.m->n) return;
+    const StepArgs a = wide_step(w, g.m, k);
+    wide_blocks(g, a, [&](const Block& b) { eat_breeders(a, b, uint32_t(k) + 1u, sh); });
 }
 
 __global__ __launch_bounds__(kThreads) void k_wide_breed(WideArgs w, int32_t k) {
     __shared__ BreedLds sh;
-    WideModel* const m = wide_model(w.shares, w.share, blockIdx.y);
-    if (k >= m->n) return;
-    const StepArgs a = wide_step(w, m, k);
-    if (a.rearm) rearm_slice(a, blockIdx.x, gridDim.x);
-    wide_blocks(a, [&](const Block& b) { breed_die(a, b, sh); });
+    const WideGroup g = wide_group(w);
+    if (!g.m || k >= g.m->n) return;
+    const StepArgs a = wide_step(w, g.m, k);
+    if (a.rearm) rearm_slice(a, g.x, g.per);
+    wide_blocks(g, a, [&](const Block& b) { breed_die(a, b, sh); });
 }
 
 __global__ __launch_bounds__(64) void k_wide_end(WideArgs w) {
-    const WideModel* const m = wide_model(w.shares, w.share, blockIdx.x);
-    if (threadIdx.x != 0 || m->n == 0) return;
-    abm_model_desc& d = w.models[w.order[blockIdx.x]];
+    if (blockIdx.x >= *w.count || threadIdx.x != 0) return;
+    const WideModel* const m = wide_model(w, blockIdx.x);
+    if (m->n == 0) return;
+    abm_model_desc& d = w.models[m->index];
     d.step += m->n;
     d.updates += int64_t(m->updates);
 }
@@ -1109,9 +1150,8 @@ Species species_of(const abm_species& s) { return Species{s.x, s.y, s.e, s.alive
 
 namespace abm {
 
-// Workgroups a model gets at most in a launch (96 models of 32^2 to 1024^2 cells
-// x 40 steps: 10.9 ms with 48, 12.4 with 96, 11.1 with 250, one a block).
-constexpr uint32_t kWideBlocks = 48;
+// Workgroups of a launch: 12 a CU, eight a model at least.
+constexpr int64_t kWideGroups = 3072;
 
 bool wide_fits(int64_t max_cap) {
     // (a descriptor may split the 2 max_cap slots otherwise: a tile more at most)
@@ -1120,9 +1160,9 @@ bool wide_fits(int64_t max_cap) {
 }
 
 int launch_wide(const WideArgs& w, hipStream_t st) {
-    const int64_t blocks = 2 * int64_t(blocks_of(uint32_t(tiles_for(w.max_cap, kTile))));
-    const uint32_t x = uint32_t(blocks < kWideBlocks ? blocks : kWideBlocks);
-    const dim3 grid(x, uint32_t(w.n)), block(kThreads);
+    int64_t groups = int64_t(w.n) * kWideShare;
+    if (groups > kWideGroups) groups = kWideGroups > 8 * int64_t(w.n) ? kWideGroups : 8 * int64_t(w.n);
+    const dim3 grid{uint32_t(groups)}, block(kThreads);
     hipLaunchKernelGGL(k_wide_begin, dim3(uint32_t(w.n)), dim3(kBlock), 0, st, w);
     hipLaunchKernelGGL(k_wide_bits, grid, dim3(kBlock), 0, st, w);
     for (int32_t k = 0; k < w.max_steps; ++k) {

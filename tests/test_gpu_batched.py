@@ -581,3 +581,26 @@ def test_workgroups_bound_the_models_on_the_chip(abm):
         return e0.elapsed_time(e1)
 
     assert ms(workgroups=1) > 8 * ms()
+
+
+# large models that share one launch's workgroups: 56 each at most, 8 each at least; every
+# third of them has no step left.  (4500 slots: three tiles of 2048 and a small remainder)
+@pytest.mark.parametrize("n_models", [1, 2, 57, 200, 400])
+def test_large_models_share_the_workgroups(abm, orc, n_models):
+    kws = [dict(W=40 + m % 5, H=30, cap_s=4500, cap_w=600, n_s0=250 + m, n_w0=60, seed=m)
+           for m in range(n_models)]
+    targets = [0 if m % 3 == 1 else 9 for m in range(n_models)]
+    b = abm.BatchedPredation([abm.predation_params(**kw) for kw in kws], targets, team_size=2,
+                             team_min_size=1)
+    assert b.team_models() == n_models
+    b.init()
+    done = 0
+    for steps in (4, 5):
+        b.run(steps)
+        done += steps
+        countdown = b.grass_countdown()
+        desc = b.descriptors()
+        assert [d.step for d in desc] == [min(t, done) for t in targets]
+        for m in range(0, n_models, 1 if n_models < 100 else 7):
+            _check_model(abm, orc, b, m, kws[m], min(targets[m], done), countdown)
+    assert abm.workspace_error(b.ws) == 0
