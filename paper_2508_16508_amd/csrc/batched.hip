@@ -959,41 +959,114 @@ __device__ __forceinline__ int64_t& chip_entry(const BatchArgs& a, int c, uint32
     return c == kChipClasses - 1 ? a.models[k].live_s : a.chip_list[c][k];
 }
 
+// Sums of the sizes (cells plus slots) of the models on the chip and of the
+// others, and the largest of each.
+struct Sizes {
+    uint64_t sum[2] = {0, 0}, most[2] = {0, 0};   // on the chip, others
+
+    __device__ __forceinline__ void add(bool other, uint64_t size) {
+        sum[other] += size;
+        most[other] = size > most[other] ? size : most[other];
+    }
+
+    // ... over the workgroup of 1024 threads.
+    __device__ __forceinline__ void reduce() {
+        __shared__ uint64_t s_sum[2][16], s_most[2][16];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                sum[k] += __shfl_xor((unsigned long long)sum[k], o, 64);
+                const uint64_t x = __shfl_xor((unsigned long long)most[k], o, 64);
+                most[k] = x > most[k] ? x : most[k];
+            }
+            if ((threadIdx.x & 63) == 0) {
+                s_sum[k][threadIdx.x >> 6] = sum[k];
+                s_most[k][threadIdx.x >> 6] = most[k];
+            }
+        }
+        __syncthreads();
+        *this = Sizes();
+        for (int w = 0; w < 16; ++w)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                sum[k] += s_sum[k][w];
+                most[k] = s_most[k][w] > most[k] ? s_most[k][w] : most[k];
+            }
+    }
+
+    // The chip launches run before the launch of the models that do not fit
+    // them, so a batch with such models takes the sum of the two.  One launch of
+    // all, a workgroup each, takes the time of its largest model, or that of all
+    // sizes at the rate of some 56 models side by side; the chip takes a sixth
+    // of it for its models.  Whichever is less, x 20 steps, in ms, one launch
+    // against two: 40 models of 32^2 to 260^2 cells 1.94 and 2.23, 20 of 250^2 and
+    // one of 270^2 2.07 and 2.31, 300 of 32^2 to 300^2, logarithmic, 3.0 and 3.2;
+    // 200 of 250^2 and one of 400^2 6.5 and 4.6, 1000 of 32^2 to 260^2 6.4 and 3.6.
+    __device__ __forceinline__ bool one_launch() const {
+        constexpr uint64_t kSideBySide = 56, kChipGain = 6;
+        const uint64_t others = sum[1] > kSideBySide * most[1] ? sum[1] : kSideBySide * most[1];
+        return kChipGain * (sum[0] + sum[1]) < kChipGain * others + sum[0] + kSideBySide * most[0];
+    }
+};
+
 // The models of one workgroup with steps to do, in launch order, as lists of
 // model | steps << 32: one per chip class, and the others.  One workgroup.
 __global__ __launch_bounds__(1024) void k_classify(BatchArgs a) {
     constexpr int kLists = kChipClasses + 1;
     __shared__ uint32_t s_cnt[kLists][16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // list of the model at position i of the order (-1: none), its index and size
+    const auto list_of = [&](int32_t i, int32_t* m, uint64_t* size) {
+        *m = a.order[i];
+        const abm_model_desc& d = a.models[*m];
+        const int64_t cells = int64_t(d.W) * d.H, n0 = d.n_s0 + d.n_w0;
+        const bool held = !d.multi_prey && d.W >= 1 && d.H >= 1 && d.W <= kChipSide &&
+                          d.H <= kChipSide && d.R >= 1 && d.R <= kChipMaxR && d.gain_s >= 0 &&
+                          d.gain_w >= 0 && d.gain_s <= kChipMaxGain &&
+                          d.gain_w <= kChipMaxGain && d.cap_s + d.cap_w <= a.scratch_stride;
+        int32_t list = kChipClasses;
+        if (held && chip_room<256>(a.chip_bytes[0], cells, n0, true))
+            list = 0;
+        else if (held && chip_room<512>(a.chip_bytes[1], cells, n0, true))
+            list = 1;
+        else if (held && chip_room<1024>(a.chip_bytes[2], cells, n0, false))
+            list = 2;
+        if (d.steps_target <= d.step) list = -1;
+        *size = uint64_t(cells + d.cap_s + d.cap_w);
+        if (i < a.n_wide) {
+            const bool wide = list == kChipClasses && int64_t(*size) >= kWideSize &&
+                              d.cap_s + d.cap_w <= a.scratch_stride &&
+                              (!d.multi_prey || (a.link_s && a.link_w));
+            a.wide[i] = wide;
+            if (wide) list = -1;
+        }
+        return list;
+    };
+    // (a batch of one round is looked at once)
+    const bool once = a.n_models - a.n_team <= 1024;
+    Sizes sizes;
+    for (int32_t i = a.n_team + int32_t(threadIdx.x); i < a.n_models && !once; i += 1024) {
+        int32_t m;
+        uint64_t size;
+        const int32_t list = list_of(i, &m, &size);
+        if (list >= 0) sizes.add(list == kChipClasses, size);
+    }
+    bool one_launch = false;
     uint32_t n[kLists] = {};
     for (int32_t i0 = a.n_team; i0 < a.n_models; i0 += 1024) {
         const int32_t i = i0 + int32_t(threadIdx.x);
         int32_t m = 0, list = -1;
-        if (i < a.n_models) {
-            m = a.order[i];
-            const abm_model_desc& d = a.models[m];
-            const int64_t cells = int64_t(d.W) * d.H, n0 = d.n_s0 + d.n_w0;
-            const bool held = !d.multi_prey && d.W >= 1 && d.H >= 1 && d.W <= kChipSide &&
-                              d.H <= kChipSide && d.R >= 1 && d.R <= kChipMaxR && d.gain_s >= 0 &&
-                              d.gain_w >= 0 && d.gain_s <= kChipMaxGain &&
-                              d.gain_w <= kChipMaxGain && d.cap_s + d.cap_w <= a.scratch_stride;
-            list = kChipClasses;
-            if (held && chip_room<256>(a.chip_bytes[0], cells, n0, true))
-                list = 0;
-            else if (held && chip_room<512>(a.chip_bytes[1], cells, n0, true))
-                list = 1;
-            else if (held && chip_room<1024>(a.chip_bytes[2], cells, n0, false))
-                list = 2;
-            if (d.steps_target <= d.step) list = -1;
-            if (i < a.n_wide) {
-                const int64_t size = cells + d.cap_s + d.cap_w;
-                const bool wide = list == kChipClasses && size >= kWideSize &&
-                                  d.cap_s + d.cap_w <= a.scratch_stride &&
-                                  (!d.multi_prey || (a.link_s && a.link_w));
-                a.wide[i] = wide;
-                if (wide) list = -1;
+        uint64_t size = 0;
+        if (i < a.n_models) list = list_of(i, &m, &size);
+        if (i0 == a.n_team) {
+            if (once && list >= 0) sizes.add(list == kChipClasses, size);
+            if (__syncthreads_or(sizes.most[1] != 0)) {
+                sizes.reduce();
+                one_launch = sizes.one_launch();
             }
         }
+        if (one_launch && list >= 0) list = kChipClasses;
         uint64_t b[kLists];
 #pragma unroll
         for (int k = 0; k < kLists; ++k) b[k] = __ballot(list == k);
@@ -1606,12 +1679,17 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
         a.chip_list[c] = nullptr;
     }
     // Models of one workgroup go to the chip (4096 models of 32^2 to 256^2 cells
-    // x 50 steps: 50.4 to 7.7 ms), unless there are teams: they run in the time
-    // those take anyway, and a launch before them only delays the teams.
+    // x 50 steps: 50.4 to 7.5 ms), unless there are teams: they run in the time
+    // those take anyway, and a launch before them only delays the teams.  A batch
+    // with links holds models matched by rank, which do not go there; all of its
+    // models run as one launch, since looking for others costs more than it may
+    // find (1000 models of 32^2 to 64^2, all by rank, x 10 steps: 489 and 600 us).
     a.wide = reinterpret_cast<uint8_t*>(a.team_counts);
     a.n_wide = 0;
     const int bound = bounded ? resident : 4 * n_cu;   // workgroups of a chip launch
-    const bool chips = !(tune && tune->global_claims) && team_wgs == 0 && n_team < b->n_models;
+    const bool links = b->link_s && b->link_w;
+    const bool chips = !(tune && tune->global_claims) && team_wgs == 0 && n_team < b->n_models &&
+                       (!links || n_wide > 0);
     if (chips) {
         const int chip = chip_lds_bytes();
         if (chip > 0) {

@@ -604,3 +604,25 @@ def test_large_models_share_the_workgroups(abm, orc, n_models):
         for m in range(0, n_models, 1 if n_models < 100 else 7):
             _check_model(abm, orc, b, m, kws[m], min(targets[m], done), countdown)
     assert abm.workspace_error(b.ws) == 0
+
+
+# models that fit a workgroup's LDS beside one that is too wide for it: run with it in one launch
+# (few of them), or before it (many; more than 1024 are looked at in two rounds); with one matched by
+# rank among them all run in one launch
+@pytest.mark.parametrize("multi_prey", [0, 1])
+@pytest.mark.parametrize("n_small", [3, 300, 1023, 1024, 1300])
+def test_one_model_past_the_chip(abm, orc, n_small, multi_prey):
+    kws = [dict(W=9 + m % 4, H=12, cap_s=200, cap_w=60, n_s0=40, n_w0=12, seed=m)
+           for m in range(n_small)]
+    kws[1]["multi_prey"] = multi_prey
+    kws.insert(n_small // 2, dict(W=257, H=3, cap_s=300, cap_w=90, n_s0=150, n_w0=30, seed=7))
+    b = abm.BatchedPredation([abm.predation_params(**kw) for kw in kws], 12)
+    b.init()
+    for steps in (5, 7):
+        b.run(steps)
+    countdown = b.grass_countdown()
+    desc = b.descriptors()
+    assert all(d.step == 12 for d in desc)
+    for m in {0, 1, n_small // 2, n_small, *range(0, n_small, 61)}:
+        _check_model(abm, orc, b, m, kws[m], 12, countdown)
+    assert torch.equal(b.claims.view(torch.int64), torch.full_like(b.claims.view(torch.int64), -1))
