@@ -6,6 +6,13 @@ on the model sizes in the batch (a small model wastes a wide workgroup; a large
 one needs many slots in flight).  The tuner times every candidate on a fresh
 sample of the actual batch and caches the winner in a JSON file keyed by the
 GPU architecture and a caller-chosen workload key.
+
+The shape is that of the models a workgroup advances in global memory.  Models
+that fit a workgroup's LDS have shapes of their own, whatever these parameters
+say; timed as they run, all candidates would do the same work and noise would
+pick the one that the models past the LDS then get.  So the candidates are timed
+with every model in global memory (a batch matched by rank, which never goes to
+the LDS, as it runs).
 """
 from __future__ import annotations
 
@@ -46,6 +53,8 @@ def autotune_batched(make_batch, key: str, steps: int = 8, candidates=CANDIDATES
     timings = {}
     for block, items in candidates:
         b = make_batch(block, items)
+        if b.links is None:
+            b.lds = False
         b.run(1, block_threads=block, items=items)       # warm-up
         torch.cuda.synchronize()
         e0 = torch.cuda.Event(enable_timing=True)

@@ -626,3 +626,25 @@ def test_one_model_past_the_chip(abm, orc, n_small, multi_prey):
     for m in {0, 1, n_small // 2, n_small, *range(0, n_small, 61)}:
         _check_model(abm, orc, b, m, kws[m], 12, countdown)
     assert torch.equal(b.claims.view(torch.int64), torch.full_like(b.claims.view(torch.int64), -1))
+
+
+@pytest.mark.parametrize("multi_prey", [0, 1])
+def test_autotuner_times_what_the_shape_applies_to(abm, multi_prey):
+    """Models that would run inside LDS, where the shape does not matter, are timed
+    in global memory; models matched by rank as they run."""
+    from paper_2508_16508_amd.tune import autotune_batched
+    seen = []
+
+    class Spy(abm.BatchedPredation):
+        def run(self, *args, **kw):
+            seen.append(self.lds)
+            super().run(*args, **kw)
+
+    def make(block, items):
+        b = Spy([abm.predation_params(seed=m, multi_prey=multi_prey) for m in range(3)], 100,
+                block_threads=block, items=items)
+        b.init()
+        return b
+
+    autotune_batched(make, "test", steps=2, candidates=((256, 1), (512, 2)), use_cache=False)
+    assert seen == [bool(multi_prey)] * 4
