@@ -35,7 +35,7 @@
 // What bounds a step is the latency of its six barrier-separated parts (under
 // 1 us each for one workgroup, whatever the model's size) and, for large
 // models, the instructions per row: 4096 models of 32 x 32 to 256 x 256 cells x
-// 50 steps take 7.7 ms, the smaller ones two or four to a CU (50.4 ms by passes
+// 50 steps take 7.5 ms, the smaller ones two or four to a CU (50.4 ms by passes
 // over global memory); 64 x 64 cells x 200 steps take 1.02 ms (6.36 ms by three
 // launches a step).  The busiest wave sets a part's time, so what does not
 // need the same rows goes to the other half of the waves (1.02 ms against 1.15

@@ -872,7 +872,7 @@ __host__ __device__ __forceinline__ Tags tags_for(int64_t max_cap) {
 // ------------------------------------------------------------------ batches
 // Large models of a batch (`wide` models), all of them side by side: the launches
 // above with the workgroups shared out among the models.  96 models of 32^2
-// to 1024^2 cells x 40 steps take 10.9 ms, bound as the one-model launches are
+// to 1024^2 cells x 40 steps take 10.5 ms, bound as the one-model launches are
 // by the atomics and the claim lines of 1.7 M agents (34.5 ms by teams of four
 // workgroups, whose chain of dependent accesses per agent the largest model's
 // team went through alone).  A model's

@@ -477,9 +477,11 @@ __device__ __forceinline__ void merge_tile(const SelArgs& a, int64_t tbase, uint
 // pointer is 16-byte aligned (checked on the host); the last tile, when
 // partial, merges its whole chunks and writes the slots behind them one by one
 // (10,000 slots x 4 attributes, of which 500 are written: 20 to 10 us with
-// every slot of that tile written by its lane before).  The kernel stays within 64 VGPRs, so all
-// 2048 tiles of a 2^24-slot launch are resident at once and the look-back
-// waits one round.
+// every slot of that tile written by its lane before).  With dense records the
+// kernel stays within 64 VGPRs, so all 2048 tiles of a 2^24-slot launch are
+// resident at once and the look-back waits one round; with masked ones
+// (kSelIndirect: 86, five waves a SIMD, 1280 tiles at once) it waits two, which
+// the indices kept for all attributes outweigh (see merge_indirect).
 template <int MODE>
 __global__ __launch_bounds__(kBlock) void k_merge(SelArgs a) {
     __shared__ uint32_t lds[kWaves + 1];
