@@ -1583,10 +1583,14 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     if (!run_shape(items, block, &n_cu, &per_cu, &lds_bytes)) return ABM_E_HIP;
     if (tune && tune->global_claims) lds_bytes = 0;
     int resident = n_cu * per_cu;
-    // a caller that asks for fewer workgroups than would be resident leaves the
-    // rest of the device to others, whichever kernels advance its models
-    const bool bounded = tune && tune->workgroups > 0 && tune->workgroups < resident;
-    if (bounded) resident = tune->workgroups;
+    const size_t fixed = size_t(abm_batched_workspace_bytes(b->max_cap, 1)) - size_t(8 * b->max_cap);
+    const int64_t shares = ws_bytes > fixed ? int64_t((ws_bytes - fixed) / size_t(8 * b->max_cap)) : 0;
+    // a caller that asks for fewer workgroups than would be resident and its
+    // workspace has shares for leaves the rest of the device to others, whichever
+    // kernels advance its models
+    const bool bounded =
+        tune && tune->workgroups > 0 && tune->workgroups < resident && tune->workgroups < shares;
+    if (tune && tune->workgroups > 0 && tune->workgroups < resident) resident = tune->workgroups;
     if (resident > kMaxWorkgroups) resident = kMaxWorkgroups;
     // teams: order[0, n_team) is run by teams of K workgroups, formed from the
     // first team_wgs workgroups (a multiple of 8 K)
@@ -1651,8 +1655,6 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     // The models that would run in teams, and the largest of the others, by
     // launches over the whole device instead, all of them side by side, where
     // the workspace has two shares for each
-    const int64_t shares = int64_t((ws_bytes - kHeaderBytes - 4 * kTeamAreaWords) /
-                                   size_t(8 * b->max_cap));
     int n_wide = 0;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (n_team > 0 && hipStreamIsCapturing(st, &capture) != hipSuccess)
