@@ -1373,6 +1373,10 @@ constexpr int64_t kTeamAreaWords = int64_t(kMaxWorkgroups) * (2 + kCountWords);
 // models on the chip when no team runs.
 constexpr int kMaxWideModels = kMaxWorkgroups;
 constexpr int64_t kChipListed = 9000;
+// Steps of a run from which four small models share a CU, and the capacity up to
+// which one step of many models is left to one launch (see abm_predation_run_batched).
+constexpr int32_t kFourSteps = 16;
+constexpr int64_t kTinyCap = 4096;
 static_assert(2 * kMaxWideModels + 64 + 16 * kChipListed <=
                   4 * int64_t(kMaxWorkgroups) * kCountWords, "the lists fit the count words");
 
@@ -1690,8 +1694,13 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     a.n_wide = 0;
     const int bound = bounded ? resident : 4 * n_cu;   // workgroups of a chip launch
     const bool links = b->link_s && b->link_w;
-    const bool chips = !(tune && tune->global_claims) && team_wgs == 0 && n_team < b->n_models &&
-                       (!links || n_wide > 0);
+    const int64_t solo = b->n_models - n_team;
+    // One step of many tiny models does not repay the list and the launches (1000
+    // of 32^2 to 64^2 cells, up to 1636 slots a species: 107 us in one launch, 125
+    // with the chip; of 32^2 to 200^2, up to 16000: 342 and 144)
+    const bool tiny = max_steps == 1 && solo > n_cu && b->max_cap <= kTinyCap;
+    const bool chips = !(tune && tune->global_claims) && team_wgs == 0 && solo > 0 &&
+                       (n_wide > 0 || (!links && !tiny));
     if (chips) {
         const int chip = chip_lds_bytes();
         if (chip > 0) {
@@ -1703,13 +1712,15 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
             // its parts, and another one's fill the gaps (x 50 steps, in ms: 4096
             // models of 32^2 to 64^2 cells 3.7 to 1.4, of 100^2 to 150^2 6.2 to 4.3,
             // of 32^2 to 256^2 8.5 to 7.7; 300 of 100^2 to 150^2 0.73 to 0.60).
+            // Each is a launch of its own, so they need steps: 1000 models of 32^2 to
+            // 64^2 x 1 step take 125, 138 and 205 us with one, two and three classes,
+            // x 3 142, 140 and 199, x 10 295, 226 and 254, x 40 790, 498 and 403.
             // Their lists lie behind the bytes of `wide`
-            const int64_t solo = b->n_models - n_team;
-            if (solo <= kChipListed && solo > n_cu && bound >= 2 * n_cu) {
+            if (solo <= kChipListed && solo > n_cu && bound >= 2 * n_cu && max_steps > 1) {
                 a.chip_list[1] = reinterpret_cast<int64_t*>(a.wide + 2 * kMaxWideModels + 64);
                 a.chip_list[0] = a.chip_list[1] + kChipListed;
                 a.chip_bytes[1] = chip_lds_part(chip, 2);
-                if (solo > 2 * n_cu && bound >= 4 * n_cu)
+                if (solo > 2 * n_cu && bound >= 4 * n_cu && max_steps >= kFourSteps)
                     a.chip_bytes[0] = chip_lds_part(chip, 4);
             }
             hipLaunchKernelGGL(k_classify, dim3(1), dim3(1024), 0, st, a);
@@ -1739,7 +1750,7 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     }
     if (a.listed) {
         // (a share of the workspace each)
-        const int solo = b->n_models - n_team, room = solo < shares ? solo : int(shares);
+        const int room = solo < shares ? int(solo) : int(shares);
         const int most = room < bound ? room : bound;
         const auto wgs = [&](int per_cu) { return dim3(per_cu * n_cu < most ? per_cu * n_cu : most); };
         if (a.chip_bytes[0] > 0)
