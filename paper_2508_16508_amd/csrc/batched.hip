@@ -1307,31 +1307,36 @@ __global__ __launch_bounds__(256) void k_batched_grass(const abm_model_desc* mod
 
 // Live counts per model (stored into the descriptors): eight loads of a thread
 // in flight (96 models of up to 1002^2 cells: 700 us one at a time, by 256
-// threads each; 57 so).
-constexpr int kCountThreads = 1024, kCountAhead = 8;
+// threads each; 57 so with 1024, 114 with 256).  Models of up to kCountFew slots
+// a species have 256 threads, as many small workgroups are dispatched sooner
+// (4096 models of 32^2 to 64^2 cells 28.6 to 9.3 us, of 32^2 to 200^2 39.6 to 24.6;
+// eight of 256^2, past it, 4.8 with 1024 and 8.6 with 256).
+constexpr int kCountAhead = 8;
+constexpr int64_t kCountFew = 1 << 14;
 
+template <int T>
 __device__ __forceinline__ uint32_t count_live(const int32_t* alive, int64_t cap) {
     uint32_t n = 0;
-    for (int64_t i0 = threadIdx.x; i0 < cap; i0 += kCountThreads * kCountAhead) {
+    for (int64_t i0 = threadIdx.x; i0 < cap; i0 += T * kCountAhead) {
         int32_t v[kCountAhead];
 #pragma unroll
         for (int k = 0; k < kCountAhead; ++k) {
-            const int64_t i = i0 + k * kCountThreads;
+            const int64_t i = i0 + k * T;
             v[k] = alive[i < cap ? i : i0];
         }
 #pragma unroll
-        for (int k = 0; k < kCountAhead; ++k) n += v[k] != 0 && i0 + k * kCountThreads < cap;
+        for (int k = 0; k < kCountAhead; ++k) n += v[k] != 0 && i0 + k * T < cap;
     }
     return n;
 }
 
-__global__ __launch_bounds__(kCountThreads) void k_batched_count(abm_model_desc* models,
-                                                                const int32_t* sa,
-                                                                const int32_t* wa) {
-    __shared__ uint32_t lds[kCountThreads / 64];
+template <int T>
+__global__ __launch_bounds__(T) void k_batched_count(abm_model_desc* models, const int32_t* sa,
+                                                     const int32_t* wa) {
+    __shared__ uint32_t lds[T / 64];
     abm_model_desc& d = models[blockIdx.x];
-    const uint32_t ls = block_sum32(count_live(sa + d.sheep_off, d.cap_s), lds);
-    const uint32_t lw = block_sum32(count_live(wa + d.wolf_off, d.cap_w), lds);
+    const uint32_t ls = block_sum32(count_live<T>(sa + d.sheep_off, d.cap_s), lds);
+    const uint32_t lw = block_sum32(count_live<T>(wa + d.wolf_off, d.cap_w), lds);
     if (threadIdx.x == 0) {
         d.live_s = ls;
         d.live_w = lw;
@@ -1768,8 +1773,12 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
         case 2: hipLaunchKernelGGL(k_batched_run<2>, dim3(grid), dim3(block), dyn, st, a); break;
         default: hipLaunchKernelGGL(k_batched_run<4>, dim3(grid), dim3(block), dyn, st, a); break;
     }
-    hipLaunchKernelGGL(k_batched_count, dim3(b->n_models), dim3(kCountThreads), 0, st, b->models,
-                       b->sheep.alive, b->wolves.alive);
+    if (b->max_cap <= kCountFew)
+        hipLaunchKernelGGL(k_batched_count<256>, dim3(b->n_models), dim3(256), 0, st, b->models,
+                           b->sheep.alive, b->wolves.alive);
+    else
+        hipLaunchKernelGGL(k_batched_count<1024>, dim3(b->n_models), dim3(1024), 0, st, b->models,
+                           b->sheep.alive, b->wolves.alive);
     return launch_status("predation_run_batched");
 }
 
