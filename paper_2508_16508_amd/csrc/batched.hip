@@ -1378,9 +1378,10 @@ constexpr int64_t kTeamAreaWords = int64_t(kMaxWorkgroups) * (2 + kCountWords);
 // models on the chip when no team runs.
 constexpr int kMaxWideModels = kMaxWorkgroups;
 constexpr int64_t kChipListed = 9000;
-// Steps of a run from which four small models share a CU, and the capacity up to
-// which one step of many models is left to one launch (see abm_predation_run_batched).
-constexpr int32_t kFourSteps = 16;
+// Models times steps of a run from which four small models share a CU, and the
+// capacity up to which a step or two of many models are left to one launch (see
+// abm_predation_run_batched).
+constexpr int64_t kFourWork = 24000;
 constexpr int64_t kTinyCap = 4096;
 static_assert(2 * kMaxWideModels + 64 + 16 * kChipListed <=
                   4 * int64_t(kMaxWorkgroups) * kCountWords, "the lists fit the count words");
@@ -1702,8 +1703,11 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
     const int64_t solo = b->n_models - n_team;
     // One step of many tiny models does not repay the list and the launches (1000
     // of 32^2 to 64^2 cells, up to 1636 slots a species: 107 us in one launch, 125
-    // with the chip; of 32^2 to 200^2, up to 16000: 342 and 144)
-    const bool tiny = max_steps == 1 && solo > n_cu && b->max_cap <= kTinyCap;
+    // with the chip; of 32^2 to 200^2, up to 16000: 342 and 144), and neither do two
+    // of models that a round or two of workgroups hold (1000 of 24^2 to 40^2: 108 and
+    // 118; 300 of 24^2 to 64^2 81 and 70, 2000 222 and 199)
+    const bool tiny = solo > n_cu && b->max_cap <= kTinyCap &&
+                      (max_steps == 1 || (max_steps == 2 && solo <= 4 * n_cu));
     const bool chips = !(tune && tune->global_claims) && team_wgs == 0 && solo > 0 &&
                        (n_wide > 0 || (!links && !tiny));
     if (chips) {
@@ -1719,13 +1723,14 @@ extern "C" int abm_predation_run_batched(const abm_batch* b, const int32_t* orde
             // of 32^2 to 256^2 8.5 to 7.7; 300 of 100^2 to 150^2 0.73 to 0.60).
             // Each is a launch of its own, so they need steps: 1000 models of 32^2 to
             // 64^2 x 1 step take 125, 138 and 205 us with one, two and three classes,
-            // x 3 142, 140 and 199, x 10 295, 226 and 254, x 40 790, 498 and 403.
+            // x 3 142, 140 and 199, x 10 295, 226 and 254, x 40 790, 498 and 403; 4096
+            // of 24^2 to 64^2 x 8 two 496 and three 509, x 15 736 and 625.
             // Their lists lie behind the bytes of `wide`
             if (solo <= kChipListed && solo > n_cu && bound >= 2 * n_cu && max_steps > 1) {
                 a.chip_list[1] = reinterpret_cast<int64_t*>(a.wide + 2 * kMaxWideModels + 64);
                 a.chip_list[0] = a.chip_list[1] + kChipListed;
                 a.chip_bytes[1] = chip_lds_part(chip, 2);
-                if (solo > 2 * n_cu && bound >= 4 * n_cu && max_steps >= kFourSteps)
+                if (solo > 2 * n_cu && bound >= 4 * n_cu && solo * max_steps >= kFourWork)
                     a.chip_bytes[0] = chip_lds_part(chip, 4);
             }
             hipLaunchKernelGGL(k_classify, dim3(1), dim3(1024), 0, st, a);
