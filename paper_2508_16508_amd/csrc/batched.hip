@@ -62,11 +62,12 @@ constexpr uint32_t kDyPacked = 0xA940u;
 
 // Words of the workspace header: the queues of the team models, of the models
 // of one workgroup and of those run on the chip (by size class), the lengths of
-// the lists k_classify makes of the latter two, and the number of wide models.
+// the lists k_classify makes of the latter two, the number of wide models and the
+// most steps that one of them has.
 constexpr int kChipClasses = 3;
 enum QueueWord : int {
     kQueueTeam = 0, kQueueSolo, kSoloModels, kQueueChip, kChipModels = kQueueChip + kChipClasses,
-    kWideModels = kChipModels + kChipClasses, kQueueWords
+    kWideModels = kChipModels + kChipClasses, kWideMostSteps, kQueueWords
 };
 
 // Cells plus slots from which a model of one workgroup that does not fit the

@@ -146,7 +146,8 @@ struct WideArgs {
     int32_t *link_s, *link_w;
     uint64_t* err;
     const uint8_t* taken;
-    uint32_t* count;           // models taken (written by the first launch)
+    uint32_t* count;           // models taken and the most steps of one (zero before the first
+                               // launch, which writes them)
     char* shares;              // 2 n shares of workspace
     int64_t share;             // bytes of one (8 max_cap)
     int64_t max_cap;

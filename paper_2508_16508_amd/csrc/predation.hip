@@ -872,7 +872,7 @@ __host__ __device__ __forceinline__ Tags tags_for(int64_t max_cap) {
 // ------------------------------------------------------------------ batches
 // Large models of a batch (`wide` models), all of them side by side: the launches
 // above with the workgroups shared out among the models.  96 models of 32^2
-// to 1024^2 cells x 40 steps take 10.5 ms, bound as the one-model launches are
+// to 1024^2 cells x 40 steps take 10.4 ms, bound as the one-model launches are
 // by the atomics and the claim lines of 1.7 M agents (34.5 ms by teams of four
 // workgroups, whose chain of dependent accesses per agent the largest model's
 // team went through alone).  A model's
@@ -980,6 +980,7 @@ __global__ __launch_bounds__(kBlock) void k_wide_begin(WideArgs w) {
     m->step0 = uint32_t(d.step);
     m->index = index;
     m->n = n;
+    atomicMax(w.count + 1, uint32_t(n));
     m->updates = 0;
 }
 
@@ -1039,9 +1040,10 @@ struct WideGroup {
 // other streams hold.
 constexpr uint32_t kWideShare = 56;
 
-__device__ __forceinline__ WideGroup wide_group(const WideArgs& w) {
-    const uint32_t n = *w.count;
-    if (n == 0) return WideGroup{nullptr, 0, 1};
+__device__ __forceinline__ WideGroup wide_group(const WideArgs& w, int32_t step) {
+    const uint32_t n = w.count[0];
+    // (a launch past every model's last step costs one load of each workgroup)
+    if (uint32_t(step) >= w.count[1]) return WideGroup{nullptr, 0, 1};
     uint32_t per = gridDim.x / n < kWideShare ? gridDim.x / n : kWideShare;
     per = 8 * (((per / 8 > 1 ? per / 8 : 1) - 1) | 1);
     const uint32_t k = blockIdx.x / per;
@@ -1049,7 +1051,7 @@ __device__ __forceinline__ WideGroup wide_group(const WideArgs& w) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_wide_bits(WideArgs w) {
-    const WideGroup g = wide_group(w);
+    const WideGroup g = wide_group(w, 0);
     if (!g.m || g.m->n == 0) return;
     const StepArgs a = wide_step(w, g.m, 0);
     const int64_t words_s = int64_t(a.tiles[0]) * kOwners, words_w = int64_t(a.tiles[1]) * kOwners;
@@ -1074,7 +1076,7 @@ __device__ __forceinline__ void wide_blocks(const WideGroup& g, const StepArgs& 
 
 __global__ __launch_bounds__(kThreads) void k_wide_move(WideArgs w, int32_t k) {
     __shared__ uint32_t lds[kThreadWaves];
-    const WideGroup g = wide_group(w);
+    const WideGroup g = wide_group(w, k);
     if (!g.m || k >= g.m->n) return;
     const StepArgs a = wide_step(w, g.m, k);
     if (g.x == 0 && threadIdx.x < 2 * kMarkLanes) a.mark_wr[threadIdx.x] = 0;
@@ -1082,7 +1084,7 @@ __global__ __launch_bounds__(kThreads) void k_wide_move(WideArgs w, int32_t k) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_wide_match(WideArgs w, int32_t k) {
-    const WideGroup g = wide_group(w);
+    const WideGroup g = wide_group(w, k);
     if (!g.m || k >= g.m->n || !g.m->a.multi) return;
     const StepArgs a = wide_step(w, g.m, k);
     for (int64_t j = int64_t(g.x) * kBlock + threadIdx.x; j < a.cap_w; j += int64_t(g.per) * kBlock)
@@ -1091,7 +1093,7 @@ __global__ __launch_bounds__(kBlock) void k_wide_match(WideArgs w, int32_t k) {
 
 __global__ __launch_bounds__(kThreads) void k_wide_eat(WideArgs w, int32_t k) {
     __shared__ EatLds sh;
-    const WideGroup g = wide_group(w);
+    const WideGroup g = wide_group(w, k);
     if (!g.m || k >= g.m->n) return;
     const StepArgs a = wide_step(w, g.m, k);
     wide_blocks(g, a, [&](const Block& b) { eat_breeders(a, b, uint32_t(k) + 1u, sh); });
@@ -1099,7 +1101,7 @@ __global__ __launch_bounds__(kThreads) void k_wide_eat(WideArgs w, int32_t k) {
 
 __global__ __launch_bounds__(kThreads) void k_wide_breed(WideArgs w, int32_t k) {
     __shared__ BreedLds sh;
-    const WideGroup g = wide_group(w);
+    const WideGroup g = wide_group(w, k);
     if (!g.m || k >= g.m->n) return;
     const StepArgs a = wide_step(w, g.m, k);
     if (a.rearm) rearm_slice(a, g.x, g.per);
@@ -1150,8 +1152,10 @@ Species species_of(const abm_species& s) { return Species{s.x, s.y, s.e, s.alive
 
 namespace abm {
 
-// Workgroups of a launch: 12 a CU, eight a model at least.
-constexpr int64_t kWideGroups = 3072;
+// Workgroups of a launch, unless eight a model are more.  (A launch that finds
+// nothing to do costs their dispatch: 2.3 us; with 3072, 3.  96 models of 32^2 to
+// 1024^2 cells x 40 steps: 10.4 ms with either.)
+constexpr int64_t kWideGroups = 1920;
 
 bool wide_fits(int64_t max_cap) {
     // (a descriptor may split the 2 max_cap slots otherwise: a tile more at most)
