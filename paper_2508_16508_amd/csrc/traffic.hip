@@ -281,37 +281,47 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_traffic_run(TrafficArgs a) {
         if (lane == 0)
             s_pre[step_k & 1] = uint4{uint32_t(key), uint32_t(key >> 32), uint32_t(hits), 0u};
     };
-    // ---- load the road: car slots into the cells' words of step 0
-    for (int32_t i = tid; i < 2 * words; i += int32_t(blockDim.x)) grid[i] = kNone;
+    // ---- load the road: car slots into the cells' words of step 0.  (A thread has
+    // R slots at most, read together before the words are cleared)
+    int32_t in_lane[R], in_pos[R], in_alive[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int32_t i = tid + r * int32_t(blockDim.x);
+        in_lane[r] = i < n ? a.lane[base + i] : 0;
+        in_pos[r] = i < n ? a.pos[base + i] : 0;
+        in_alive[r] = i < n ? a.alive[base + i] : 1;
+    }
+    const int32_t sets = a.n_steps > 1 ? 2 : 1;
+    for (int32_t i = tid; i < sets * words; i += int32_t(blockDim.x)) grid[i] = kNone;
     for (int32_t i = tid; i < n; i += int32_t(blockDim.x)) fate[i] = kUntouched;
     if (wave == helper) {
         prepare_step(0);
-        prepare_step(1);
+        if (a.n_steps > 1) prepare_step(1);
     }
     if (tid == 0) s_unplaced = 0;
     __syncthreads();
     int32_t cars = 0;
-    for (int32_t i = tid; i < n; i += int32_t(blockDim.x)) {
-        const int32_t l = a.lane[base + i], x = a.pos[base + i];
-        if (a.alive[base + i] && l >= 0 && l < 3 && x >= 0 && x < L) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int32_t i0 = wave * 64 + r * int32_t(blockDim.x), i = i0 + lane;
+        const int32_t l = in_lane[r], x = in_pos[r];
+        if (i < n && in_alive[r] && l >= 0 && l < 3 && x >= 0 && x < L) {
             grid[(l + 1) * stride + x + 1] = ((i + 1) << 2) | kNone;
             ++cars;
         }
+        const uint64_t f = __ballot(in_alive[r] == 0);
+        if (lane < 2 && i0 < n) free_bits[(i0 >> 5) + lane] = uint32_t(f >> (32 * lane));
     }
-    // the free slots' bits; wave 0 keeps their number and the lowest of them
+    __syncthreads();
+    // wave 0 keeps the number of the free slots and the lowest of them
     int32_t n_free = 0;
     LowSlots low = {};
     if (wave == 0) {
-        for (int32_t r = 0; r * 64 < n; ++r) {
-            const int32_t i = r * 64 + lane;
-            const uint64_t f = __ballot(i < n && a.alive[base + i] == 0);
-            if (lane < 2) free_bits[2 * r + lane] = uint32_t(f >> (32 * lane));
-            n_free += int32_t(__popcll(f));
-        }
-        wave_lds_sync();
+        const int32_t words = free_words(L) / 2;
+        const int32_t here = lane < words ? __popc(free_bits[2 * lane]) + __popc(free_bits[2 * lane + 1]) : 0;
+        n_free = __builtin_amdgcn_readlane(wave_incl_sum(here), 63);
         low.refill(free_bits, n);
     }
-    __syncthreads();
     int32_t sl[R], cell[R], row[R], col[R];       // car slot (-1: none), cell's word index, lane, column
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -513,6 +523,8 @@ extern "C" int abm_traffic_step(const abm_traffic_params* p, abm_traffic_state* 
     a.n_steps = n_steps;
     const int32_t cells = 3 * (p->length - 2);   // between the entry and the exit column
     const int R = cells <= 64 * (kMaxWaves - 2) ? 1 : (cells <= 128 * (kMaxWaves - 2) ? 2 : 4);
+    // (a thread's R slots cover the 3 length ones: the block holds cells / R threads
+    // and two waves more)
     const size_t lds = size_t(8) * grid_words(p->length) + size_t(4) * free_words(p->length) +
                        size_t(3) * p->length;
     const dim3 grid(uint32_t(s->n_roads));
